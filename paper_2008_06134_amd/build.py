@@ -22,7 +22,9 @@ OUT = os.path.join(HERE, "libvi.so")
 # the benchmark's probes (L2 reads, the build's store pattern), a library of its own that only bench.py loads
 PROBE_SRC, PROBE_OUT = "vi_probe.hip", os.path.join(HERE, "libvi_probe.so")
 BUILD_DIR = os.path.join(ROOT, "_build")
-SOURCES = ["vi_api.hip", "vi_build.hip", "vi_render.hip", "vi_layout.hip", "vi_sched.cpp", "vi_server.hip"]
+# the render kernels, one compilation per voxel type and volume layout (vi_internal.h kRenderParts)
+RENDER_SRC, RENDER_PARTS = "vi_render.hip", 12
+SOURCES = ["vi_build.hip", "vi_api.hip", "vi_layout.hip", "vi_sched.cpp", "vi_server.hip"]
 ARCH = os.environ.get("VI_OFFLOAD_ARCH", "gfx950")
 
 
@@ -48,9 +50,11 @@ def build(verbose: bool = False) -> str:
     os.makedirs(BUILD_DIR, exist_ok=True)
     cc = hipcc()
 
-    def compile_one(src):
-        obj = os.path.join(BUILD_DIR, os.path.splitext(src)[0] + ".o")
-        cmd = [cc, *flags(), "-c", os.path.join(CSRC, src), "-o", obj]
+    def compile_one(unit):
+        src, part = unit
+        obj = os.path.join(BUILD_DIR, os.path.splitext(src)[0] + ("" if part is None else f"_{part}") + ".o")
+        extra = [] if part is None else [f"-DVI_RENDER_PART={part}"]
+        cmd = [cc, *flags(), *extra, "-c", os.path.join(CSRC, src), "-o", obj]
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:
             raise RuntimeError(f"hipcc failed on {src}:\n{r.stdout}\n{r.stderr}")
@@ -58,8 +62,9 @@ def build(verbose: bool = False) -> str:
             print(r.stderr, file=sys.stderr)
         return obj
 
-    with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
-        objs = list(ex.map(compile_one, SOURCES))
+    units = [(RENDER_SRC, p) for p in range(RENDER_PARTS)] + [(src, None) for src in SOURCES]
+    with ThreadPoolExecutor(max_workers=max(2, min(8, os.cpu_count() or 2))) as ex:
+        objs = list(ex.map(compile_one, units))
     tmp = OUT + ".tmp"
     cmd = [cc, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs, "-lpthread"]
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -820,6 +820,39 @@ int make_frame(const vi_volume* vol, const vi_tf* tf, const vi_slices* sl, const
     return VI_OK;
 }
 
+// Dispatch over the voxel types and volume layouts (vi_render.hip holds one
+// pair per compilation).
+namespace {
+template <int P>
+hipError_t render_part(int part, const RenderFrame& f, hipStream_t s)
+{
+    if (part == P) return launch_render_part<P>(f, s);
+    if constexpr (P + 1 < kRenderParts) return render_part<P + 1>(part, f, s);
+    return hipErrorInvalidValue;
+}
+template <int P>
+hipError_t batch_part(int part, int sdt, int sl, int mode, const RenderFrame* f, const uint32_t* t, uint32_t n, int K,
+                      uint32_t w, hipStream_t s)
+{
+    if (part == P) return launch_render_batch_part<P>(sdt, sl, mode, f, t, n, K, w, s);
+    if constexpr (P + 1 < kRenderParts) return batch_part<P + 1>(part, sdt, sl, mode, f, t, n, K, w, s);
+    return hipErrorInvalidValue;
+}
+}  // namespace
+
+hipError_t launch_render(const RenderFrame& f, hipStream_t s)
+{
+    return render_part<0>(f.vol_dtype * 3 + f.vol_layout, f, s);
+}
+
+hipError_t launch_render_batch(int vol_dtype, int layout, int stack_dtype, int stack_layout, int mode,
+                               const RenderFrame* d_frames, const uint32_t* d_tiles, uint32_t ntiles, int maxK,
+                               uint32_t max_occ_words, hipStream_t s)
+{
+    return batch_part<0>(vol_dtype * 3 + layout, stack_dtype, stack_layout, mode, d_frames, d_tiles, ntiles, maxK,
+                         max_occ_words, s);
+}
+
 int fail_msg(int code, const char* msg) { return fail(code, "%s", msg); }
 
 }  // namespace vi

@@ -154,6 +154,15 @@ hipError_t launch_render(const RenderFrame& f, hipStream_t s);
 hipError_t launch_render_batch(int vol_dtype, int layout, int stack_dtype, int stack_layout, int mode,
                                const RenderFrame* d_frames, const uint32_t* d_tiles, uint32_t ntiles, int maxK,
                                uint32_t max_occ_words, hipStream_t s);
+// The render kernels of one voxel type and volume layout (P = dtype * 3 +
+// layout), each defined in a compilation of vi_render.hip of its own.
+template <int P>
+hipError_t launch_render_part(const RenderFrame& f, hipStream_t s);
+template <int P>
+hipError_t launch_render_batch_part(int stack_dtype, int stack_layout, int mode, const RenderFrame* d_frames,
+                                    const uint32_t* d_tiles, uint32_t ntiles, int maxK, uint32_t max_occ_words,
+                                    hipStream_t s);
+constexpr int kRenderParts = 12;
 hipError_t launch_to_bricks(const void* src, void* dst, int dtype, int N, hipStream_t s);
 hipError_t launch_to_quads(const void* src, void* dst, int dtype, int N, hipStream_t s);
 hipError_t launch_minmax(const void* vol, int dtype, int layout, uint32_t vsy, uint32_t vsz, int N, float scale,

@@ -1148,30 +1148,6 @@ static hipError_t launch_batch_l(int sdt, int sl, int mode, const RenderFrame* f
                                : launch_batch_t<VT, LAYOUT, VI_F32, VI_STACK_TILED>(mode, f, t, n, K, w, s);
 }
 
-template <typename VT>
-static hipError_t launch_batch_vt(int layout, int sdt, int sl, int mode, const RenderFrame* f, const uint32_t* t,
-                                  uint32_t n, int K, uint32_t w, hipStream_t s)
-{
-    if (layout == VI_LAYOUT_QUAD4) return launch_batch_l<VT, VI_LAYOUT_QUAD4>(sdt, sl, mode, f, t, n, K, w, s);
-    return layout == VI_LAYOUT_BRICK4 ? launch_batch_l<VT, VI_LAYOUT_BRICK4>(sdt, sl, mode, f, t, n, K, w, s)
-                                      : launch_batch_l<VT, VI_LAYOUT_LINEAR>(sdt, sl, mode, f, t, n, K, w, s);
-}
-
-hipError_t launch_render_batch(int vol_dtype, int layout, int stack_dtype, int stack_layout, int mode,
-                               const RenderFrame* d_frames, const uint32_t* d_tiles, uint32_t ntiles, int maxK,
-                               uint32_t max_occ_words, hipStream_t s)
-{
-    const uint32_t w = max_occ_words;
-    switch (vol_dtype) {
-    case VI_U8: return launch_batch_vt<uint8_t>(layout, stack_dtype, stack_layout, mode, d_frames, d_tiles, ntiles, maxK, w, s);
-    case VI_U16:
-        return launch_batch_vt<uint16_t>(layout, stack_dtype, stack_layout, mode, d_frames, d_tiles, ntiles, maxK, w, s);
-    case VI_F16:
-        return launch_batch_vt<__half>(layout, stack_dtype, stack_layout, mode, d_frames, d_tiles, ntiles, maxK, w, s);
-    default: return launch_batch_vt<float>(layout, stack_dtype, stack_layout, mode, d_frames, d_tiles, ntiles, maxK, w, s);
-    }
-}
-
 template <typename VT, int LAYOUT, int SDT, int SL>
 static hipError_t launch_mode(const RenderFrame& f, hipStream_t s)
 {
@@ -1226,22 +1202,31 @@ static hipError_t launch_sdt(const RenderFrame& f, hipStream_t s)
     return q ? launch_mode<VT, LAYOUT, VI_F32, VI_STACK_ROWS>(f, s) : launch_mode<VT, LAYOUT, VI_F32, VI_STACK_TILED>(f, s);
 }
 
-template <typename VT>
-static hipError_t launch_vt(const RenderFrame& f, hipStream_t s)
+// One compilation of this file holds the kernels of one voxel type and volume
+// layout (VI_RENDER_PART = dtype * 3 + layout; the builder compiles all
+// twelve side by side: one compilation of every kernel took six minutes).
+#ifndef VI_RENDER_PART
+#error "compile with -DVI_RENDER_PART=dtype*3+layout (0..11)"
+#endif
+constexpr int kPartDtype = VI_RENDER_PART / 3, kPartLayout = VI_RENDER_PART % 3;
+template <int DT> struct VoxelType { using T = float; };
+template <> struct VoxelType<VI_U8> { using T = uint8_t; };
+template <> struct VoxelType<VI_U16> { using T = uint16_t; };
+template <> struct VoxelType<VI_F16> { using T = __half; };
+
+template <>
+hipError_t launch_render_part<VI_RENDER_PART>(const RenderFrame& f, hipStream_t s)
 {
-    if (f.vol_layout == VI_LAYOUT_QUAD4) return launch_sdt<VT, VI_LAYOUT_QUAD4>(f, s);
-    return f.vol_layout == VI_LAYOUT_BRICK4 ? launch_sdt<VT, VI_LAYOUT_BRICK4>(f, s)
-                                            : launch_sdt<VT, VI_LAYOUT_LINEAR>(f, s);
+    return launch_sdt<VoxelType<kPartDtype>::T, kPartLayout>(f, s);
 }
 
-hipError_t launch_render(const RenderFrame& f, hipStream_t s)
+template <>
+hipError_t launch_render_batch_part<VI_RENDER_PART>(int stack_dtype, int stack_layout, int mode,
+                                                    const RenderFrame* d_frames, const uint32_t* d_tiles,
+                                                    uint32_t ntiles, int maxK, uint32_t max_occ_words, hipStream_t s)
 {
-    switch (f.vol_dtype) {
-    case VI_U8: return launch_vt<uint8_t>(f, s);
-    case VI_U16: return launch_vt<uint16_t>(f, s);
-    case VI_F16: return launch_vt<__half>(f, s);
-    default: return launch_vt<float>(f, s);
-    }
+    return launch_batch_l<VoxelType<kPartDtype>::T, kPartLayout>(stack_dtype, stack_layout, mode, d_frames, d_tiles,
+                                                                 ntiles, maxK, max_occ_words, s);
 }
 
 }  // namespace vi
