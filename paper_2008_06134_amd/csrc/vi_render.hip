@@ -1,8 +1,8 @@
 // vi_render.hip -- eye-space ray march with the slice-based illumination
 // coefficient (sections 3.2.2, 3.2.3 and 4).
 //
-// Four lanes march one ray together (each takes every fourth segment; the
-// four segments of a step are composited by an in-group scan).  Per ray, once
+// The four lanes of a quad march one ray together (each takes every fourth
+// segment; the four segments of a step are composited by a scan over the quad).  Per ray, once
 // (float): the camera ray, the slab test against the unit cube, the entry
 // point in volume and light-grid coordinates and the increments of both per
 // voxel of path; for the cone, the per-ray frame (B, L x B) in texel units.
@@ -429,39 +429,61 @@ __device__ __forceinline__ float gather_point(const RenderFrame& F, float z, flo
     return s;
 }
 
-// G lanes march one ray together: lane g of the group takes segment k + g of
-// every group step, the G segments are composited front to back with a scan
-// over the group (inclusive product of (1 - alpha), then the emission of each
-// segment weighted by the transmittance in front of it), and the ray stops
-// exactly at the first segment after which 1 - alpha_dst <= term_eps.  All
-// lanes of a group carry identical ray state.  G = 1 is the plain sequential
-// march; larger G shortens the longest waves (rays of ~1000 non-empty
-// segments) and packs the G samples of a step within a couple of voxels.
-template <int G>
-__device__ __forceinline__ float group_scan_mul(float x, int g)
+// The four lanes of a quad march one ray together: lane g takes segment k + g
+// of every step.  The opacities of the four segments are composited front to
+// back with a scan over the quad (inclusive product of (1 - alpha)), each
+// segment's emission is weighted by the transmittance in front of it, and the
+// ray stops exactly at the first segment after which 1 - alpha_dst <=
+// term_eps.  All lanes of a quad carry the same ray state but for the colour,
+// of which each lane sums its own segments until the ray ends.  Quads shorten
+// the longest waves (rays of ~1000 non-empty segments) and pack the samples
+// of a step within a couple of voxels.
+//
+// The quad's lanes exchange values by DPP quad permutes, which are operand
+// modifiers of the VALU instruction that uses them; lane shuffles (thirteen
+// LDS permutes a step, each with its index arithmetic and a wait) took a
+// fifth of a frame's VALU instructions and all of its LDS waits.
+template <int A, int B, int C, int D>
+__device__ __forceinline__ float quad_perm(float x)
 {
-    for (int d = 1; d < G; d <<= 1) {
-        const float t = __shfl_up(x, d, G);
-        if (g >= d) x *= t;
-    }
-    return x;
+    return __int_as_float(
+        __builtin_amdgcn_mov_dpp(__float_as_int(x), A | (B << 2) | (C << 4) | (D << 6), 0xf, 0xf, true));
 }
-template <int G>
-__device__ __forceinline__ float group_sum(float x)
+// products of lanes 0..g
+__device__ __forceinline__ float quad_scan_mul(float x, int g)
 {
-    for (int d = G / 2; d >= 1; d >>= 1) x += __shfl_xor(x, d, G);
-    return x;
+    float t = quad_perm<0, 0, 1, 2>(x);
+    x = g >= 1 ? x * t : x;
+    t = quad_perm<0, 1, 0, 1>(x);
+    return g >= 2 ? x * t : x;
 }
-template <int G>
-__device__ __forceinline__ uint32_t group_bits(bool p, int base)
+__device__ __forceinline__ float quad_min(float x)
 {
-    const unsigned long long m = __ballot(p);
-    return (uint32_t)((m >> base) & ((G == 32 ? 0xffffffffull : ((1ull << G) - 1ull))));
+    x = fminf(x, quad_perm<1, 0, 3, 2>(x));
+    return fminf(x, quad_perm<2, 3, 0, 1>(x));
+}
+__device__ __forceinline__ float quad_sum(float x)
+{
+    x += quad_perm<1, 0, 3, 2>(x);
+    return x + quad_perm<2, 3, 0, 1>(x);
+}
+// whether p holds in all four lanes of the quad (scalar arithmetic on the
+// wave's ballot; lanes of finished rays do not matter)
+__device__ __forceinline__ bool quad_all(bool p)
+{
+    unsigned long long m = __ballot(p);
+    m &= m >> 1;
+    m &= m >> 2;
+    m &= 0x1111111111111111ull;
+    m |= m << 1;
+    m |= m << 2;
+    return __builtin_amdgcn_inverse_ballot_w64(m);
 }
 
-// Per-ray march state (identical in the G lanes of a ray's group): the ray
-// in offset-voxel coordinates, its light-grid maps, the cone basis or Phong
-// vectors, the empty-space cache and the compositing state.
+// Per-ray march state (identical in the four lanes of a ray's quad but for
+// the colour): the ray in offset-voxel coordinates, its light-grid maps, the
+// cone basis or Phong vectors, the empty-space cache and the compositing
+// state.
 struct RayState {
     float hx0, hy0, hz0, hdx, hdy, hdz;  // entry point and direction
     float Df;                            // chord length, voxels
@@ -483,7 +505,7 @@ constexpr bool is_point_gather(int mode)
 
 // Ray set-up for pixel (px, py): false if the ray misses the cube (the pixel
 // is then the background).
-template <typename VT, int LAYOUT, int MODE, int SDT, int SL, int G>
+template <typename VT, int LAYOUT, int MODE, int SDT, int SL>
 __device__ __forceinline__ bool ray_setup(const RenderFrame& F, int px, int py, RayState& S)
 {
     // ---- camera ray, in offset-voxel coordinates, in float pairs (the
@@ -647,33 +669,27 @@ __device__ __forceinline__ bool ray_setup(const RenderFrame& F, int px, int py, 
     return true;
 }
 
-// One step of G segments of the ray's march (the G lanes of its group take
+// One step of four segments of the ray's march (the lanes of its quad take
 // one segment each); true once the ray is done.
-template <typename VT, int LAYOUT, int MODE, int SDT, int SL, int G>
+template <typename VT, int LAYOUT, int MODE, int SDT, int SL>
 __device__ __forceinline__ bool ray_step(const RenderFrame& F, const float4* __restrict__ s_tf,
                                          const int* __restrict__ s_next, const uint32_t* __restrict__ s_bits,
                                          RayState& S, uint32_t& nop)
 {
-    const int lane = threadIdx.x & 63, g = lane % G, gbase = lane - g;
+    const int g = threadIdx.x & 3;
     constexpr bool PT = is_point_gather(MODE);
     constexpr bool PTP = MODE == kModePointPhong, PHONG = MODE == VI_MODE_PHONG || PTP;
     const float hx0 = S.hx0, hy0 = S.hy0, hz0 = S.hz0, hdx = S.hdx, hdy = S.hdy, hdz = S.hdz;
-    const float qz0 = S.qz0, qx0 = S.qx0, qy0 = S.qy0, qdz = S.qdz, qdx = S.qdx, qdy = S.qdy, pd0 = S.pd0,
-                pdd = S.pdd;
-    const ConeFrame cf = S.cf;
-    const float lx = S.lx, ly = S.ly, lz = S.lz, vx = S.vx, vy = S.vy, vz = S.vz, lv = S.lv;
     const float Df = S.Df, ihx = S.ihx, ihy = S.ihy, ihz = S.ihz;
     const int K = S.K;
-    float& Cr = S.Cr; float& Cg = S.Cg; float& Cb = S.Cb; float& T = S.T;
     uint32_t& last_cell = S.last_cell;
     bool& cell_is_empty = S.cell_is_empty;
     int& k = S.k;
-    int& count = S.count;
     const VT* __restrict__ vol = (const VT*)F.vol;
     const VolIndex VI_ = {1u, F.vsy, F.vsz};
     const float dtf = F.dt;
     const float Km1 = (float)(F.K - 1);
-    // Empty-space traversal.  A group whose G segments all lie in
+    // Empty-space traversal.  A step whose four segments all lie in
     // zero-opacity cells jumps to the last segment midpoint inside the empty
     // box around its last segment -- the segment's cell, or the cell's
     // super-cell (4 x 4 x 4 cells) when that is empty too -- with the box's
@@ -685,15 +701,16 @@ __device__ __forceinline__ bool ray_step(const RenderFrame& F, const float4* __r
     const float Mf = (float)F.M;
     const int kk = k + g;
     const bool in = kk < K;
-    float om = 1.f, cr = 0.f, cg = 0.f, cb = 0.f;  // om = 1 - alpha of the segment
+    float om = 1.f, sm = 0.f, hx = 0.f, hy = 0.f, hz = 0.f;  // om = 1 - alpha of the segment
+    float er = 0.f, eg = 0.f, eb = 0.f;                      // its colour
     bool empty = true;
     int cx = 0, cy = 0, cz = 0;  // the segment's cell
     if (in) {
         const float s0 = (float)kk * dtf;
         const float s1 = fminf((float)(kk + 1) * dtf, Df);
         const float len = s1 - s0;
-        const float sm = 0.5f * (s0 + s1);
-        const float hx = fmaf(sm, hdx, hx0), hy = fmaf(sm, hdy, hy0), hz = fmaf(sm, hdz, hz0);
+        sm = 0.5f * (s0 + s1);
+        hx = fmaf(sm, hdx, hx0), hy = fmaf(sm, hdy, hy0), hz = fmaf(sm, hdz, hz0);
         empty = false;
         if (F.occ.mm) {
             const int gx = clampi((int)floorf(hx) + F.M, 0, F.N - 1),
@@ -716,67 +733,18 @@ __device__ __forceinline__ bool ray_step(const RenderFrame& F, const float4* __r
             const float a = clampf01(fmaf(w, tb.w - ta.w, ta.w));
             // (1 - alpha) of a segment of length len: (1 - a)^(len / dref)
             if (len > 0.0f && a > 0.0f) om = fast_exp2(len * fast_log2(1.0f - a));
-            const float alpha = 1.0f - om;
-            if (alpha > 0.0f) {
-                // emission alpha (sd rgb + ss) light: Eq. 7 with the
-                // coefficient A, or the local Phong terms
-                float sd, ss = 0.0f;
-                if (PHONG) {
-                    // central differences one voxel either side (exact
-                    // offsets in voxel units)
-                    const float gx = 0.5f * (sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.scale, hx + 1.f, hy, hz) -
-                                             sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.scale, hx - 1.f, hy, hz));
-                    const float gy = 0.5f * (sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.scale, hx, hy + 1.f, hz) -
-                                             sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.scale, hx, hy - 1.f, hz));
-                    const float gz = 0.5f * (sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.scale, hx, hy, hz + 1.f) -
-                                             sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.scale, hx, hy, hz - 1.f));
-                    const float gn = sqrtf(fmaf(gx, gx, fmaf(gy, gy, gz * gz)));
-                    const float inv = -1.0f / fmaxf(gn, F.grad_eps);  // n = -g / max(|g|, eps)
-                    const float nx = gx * inv, ny = gy * inv, nz = gz * inv;
-                    float llx = lx, lly = ly, llz = lz, llv = lv;
-                    if (PTP) {
-                        // l = (P - p) / |P - p|
-                        const float rx = fmaf(sm, -vx, lx), ry = fmaf(sm, -vy, ly), rz = fmaf(sm, -vz, lz);
-                        const float ir = -__builtin_amdgcn_rsqf(fmaf(rx, rx, fmaf(ry, ry, rz * rz)));
-                        llx = rx * ir;
-                        lly = ry * ir;
-                        llz = rz * ir;
-                        llv = fmaf(llx, vx, fmaf(lly, vy, llz * vz));
-                    }
-                    const float nl = fmaf(nx, llx, fmaf(ny, lly, nz * llz));
-                    const float nv = fmaf(nx, vx, fmaf(ny, vy, nz * vz));
-                    const float nn = fmaf(nx, nx, fmaf(ny, ny, nz * nz));
-                    const float rv = fmaf(2.0f * nl, nv, -nn * llv);  // r.v, r = 2(n.l)n - (n.n)l
-                    sd = fmaf(F.phong_kd, fmaxf(nl, 0.0f), F.phong_ka);
-                    if (rv > 0.0f) ss = F.phong_ks * fast_exp2(F.phong_shin * fast_log2(rv));
-                } else {
-                    // (the nearest-face form is a second copy of the
-                    // gather behind a branch that is uniform per frame)
-                    float A = 1.0f;
-                    const float qz = fmaf(sm, qdz, qz0), qx = fmaf(sm, qdx, qx0), qy = fmaf(sm, qdy, qy0);
-                    if (PT) {
-                        const float pd = fmaf(sm, pdd, pd0);
-                        A = F.nearest ? gather_point<MODE, SDT, SL, true>(F, qz, pd, qx, qy, -pdd, -qdx, -qdy)
-                                      : gather_point<MODE, SDT, SL, false>(F, qz, pd, qx, qy, -pdd, -qdx, -qdy);
-                    } else if (MODE != VI_MODE_NONE) {
-                        A = F.nearest ? gather<MODE, SDT, SL, true>(F, cf, qz, qx, qy)
-                                      : gather<MODE, SDT, SL, false>(F, cf, qz, qx, qy);
-                    }
-                    sd = fmaf(1.0f - F.ambient, A, F.ambient);
-                }
-                cr = alpha * F.light[0] * fmaf(sd, fmaf(w, tb.x - ta.x, ta.x), ss);
-                cg = alpha * F.light[1] * fmaf(sd, fmaf(w, tb.y - ta.y, ta.y), ss);
-                cb = alpha * F.light[2] * fmaf(sd, fmaf(w, tb.z - ta.z, ta.z), ss);
-            }
+            er = fmaf(w, tb.x - ta.x, ta.x);
+            eg = fmaf(w, tb.y - ta.y, ta.y);
+            eb = fmaf(w, tb.z - ta.z, ta.z);
         }
     }
-    if (group_bits<G>(empty, gbase) == ((G == 32) ? 0xffffffffu : ((1u << G) - 1u))) {
+    if (quad_all(empty)) {
         // every segment of this step is empty (or past the exit): jump,
-        // staying on multiples of G so that the steps group segments as a
+        // staying on multiples of four so that the steps group segments as a
         // march without the map would (the products then round alike and
         // the map changes no bit of the result).  Each lane finds the
         // last segment inside the empty box around its own segment; the
-        // group takes its last lane's.
+        // quad takes its last lane's.
         int jl = K;
         if (in && F.occ.mm) {
             int sh = F.occ.shift, bx = cx, by = cy, bz = cz, last = (int)F.occ.nc - 1;
@@ -803,52 +771,102 @@ __device__ __forceinline__ bool ray_step(const RenderFrame& F, const float4* __r
             const float jf = floorf(fmaf(se, F.idt, -0.5f));
             jl = jf >= (float)(K - 1) ? K - 1 : (int)jf;
         }
-        const int jlast = G == 1 ? jl : __shfl(jl, gbase + G - 1);
-        k = max(k + G, ((jlast + 1) / G) * G);
-        if (k >= K) return true;
-        return false;
+        const int jlast = __builtin_amdgcn_mov_dpp(jl, 0xff, 0xf, 0xf, true);  // lane 3's
+        k = max(k + 4, (jlast + 1) & ~3);
+        return k >= K;
     }
-    // front-to-back over the G segments of this step (Eq. 3 in product form)
-    const float incl = group_scan_mul<G>(om, g);                  // prod_{h<=g} (1 - alpha_h)
-    // every lane of the group takes part in the shuffle (a lane that sat
-    // out would hand its neighbour no value)
-    const float up = G == 1 ? 1.0f : __shfl_up(incl, 1, G);
-    const float excl = g == 0 ? 1.0f : up;
-    const uint32_t tb_ = group_bits<G>(in && T * incl <= F.term_eps, gbase);
-    const int gs = tb_ ? __ffs(tb_) - 1 : G;                     // terminating segment, G if none
-    const float keep = (g <= gs) ? T * excl : 0.0f;
-    nop += (in && g <= gs && om < 1.0f) ? 1u : 0u;  // composited with non-zero opacity
-    Cr += group_sum<G>(keep * cr);
-    Cg += group_sum<G>(keep * cg);
-    Cb += group_sum<G>(keep * cb);
-    const float prod = G == 1 ? incl : __shfl(incl, gbase + min(gs, G - 1));
-    T *= prod;
-    if (gs < G) {
-        count = k + gs + 1;
+    // front to back over the four segments of this step (Eq. 3 in product
+    // form): a segment is composited while the transmittance in front of it
+    // is above term_eps, and the ray's transmittance becomes the last
+    // composited segment's
+    const float incl = quad_scan_mul(om, g);  // prod_{h<=g} (1 - alpha_h)
+    const float up = quad_perm<0, 0, 1, 2>(incl);
+    const float before = g == 0 ? S.T : S.T * up, after = S.T * incl;
+    const bool seen = before > F.term_eps;
+    S.T = quad_min(seen ? after : 2.0f);
+    if (seen && om < 1.0f) {
+        // emission alpha (sd rgb + ss) light: Eq. 7 with the coefficient A,
+        // or the local Phong terms
+        ++nop;
+        const float wgt = before * (1.0f - om);
+        float sd, ss = 0.0f;
+        if (PHONG) {
+            // central differences one voxel either side (exact
+            // offsets in voxel units)
+            const float gx = 0.5f * (sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.scale, hx + 1.f, hy, hz) -
+                                     sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.scale, hx - 1.f, hy, hz));
+            const float gy = 0.5f * (sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.scale, hx, hy + 1.f, hz) -
+                                     sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.scale, hx, hy - 1.f, hz));
+            const float gz = 0.5f * (sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.scale, hx, hy, hz + 1.f) -
+                                     sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.scale, hx, hy, hz - 1.f));
+            const float gn = sqrtf(fmaf(gx, gx, fmaf(gy, gy, gz * gz)));
+            const float inv = -1.0f / fmaxf(gn, F.grad_eps);  // n = -g / max(|g|, eps)
+            const float nx = gx * inv, ny = gy * inv, nz = gz * inv;
+            const float vx = S.vx, vy = S.vy, vz = S.vz;
+            float llx = S.lx, lly = S.ly, llz = S.lz, llv = S.lv;
+            if (PTP) {
+                // l = (P - p) / |P - p|
+                const float rx = fmaf(sm, -vx, llx), ry = fmaf(sm, -vy, lly), rz = fmaf(sm, -vz, llz);
+                const float ir = -__builtin_amdgcn_rsqf(fmaf(rx, rx, fmaf(ry, ry, rz * rz)));
+                llx = rx * ir;
+                lly = ry * ir;
+                llz = rz * ir;
+                llv = fmaf(llx, vx, fmaf(lly, vy, llz * vz));
+            }
+            const float nl = fmaf(nx, llx, fmaf(ny, lly, nz * llz));
+            const float nv = fmaf(nx, vx, fmaf(ny, vy, nz * vz));
+            const float nn = fmaf(nx, nx, fmaf(ny, ny, nz * nz));
+            const float rv = fmaf(2.0f * nl, nv, -nn * llv);  // r.v, r = 2(n.l)n - (n.n)l
+            sd = fmaf(F.phong_kd, fmaxf(nl, 0.0f), F.phong_ka);
+            if (rv > 0.0f) ss = F.phong_ks * fast_exp2(F.phong_shin * fast_log2(rv));
+        } else {
+            // (the nearest-face form is a second copy of the
+            // gather behind a branch that is uniform per frame)
+            float A = 1.0f;
+            const float qz = fmaf(sm, S.qdz, S.qz0), qx = fmaf(sm, S.qdx, S.qx0), qy = fmaf(sm, S.qdy, S.qy0);
+            if (PT) {
+                const float pd = fmaf(sm, S.pdd, S.pd0);
+                A = F.nearest ? gather_point<MODE, SDT, SL, true>(F, qz, pd, qx, qy, -S.pdd, -S.qdx, -S.qdy)
+                              : gather_point<MODE, SDT, SL, false>(F, qz, pd, qx, qy, -S.pdd, -S.qdx, -S.qdy);
+            } else if (MODE != VI_MODE_NONE) {
+                A = F.nearest ? gather<MODE, SDT, SL, true>(F, S.cf, qz, qx, qy)
+                              : gather<MODE, SDT, SL, false>(F, S.cf, qz, qx, qy);
+            }
+            sd = fmaf(1.0f - F.ambient, A, F.ambient);
+        }
+        S.Cr = fmaf(wgt, fmaf(sd, er, ss), S.Cr);
+        S.Cg = fmaf(wgt, fmaf(sd, eg, ss), S.Cg);
+        S.Cb = fmaf(wgt, fmaf(sd, eb, ss), S.Cb);
+    }
+    if (S.T <= F.term_eps) {
+        // composited segments of the step: the quad's lanes that were seen
+        const unsigned long long m = __ballot(seen && in) >> (threadIdx.x & 60);
+        S.count = k + __popc((uint32_t)m & 15u);
         return true;
     }
-    k += G;
+    k += 4;
     return k >= K;
 }
 
 // The finished ray's colour over the background, and its segment count.
 __device__ __forceinline__ float4 ray_result(const RenderFrame& F, const RayState& S)
 {
-    return make_float4(fmaf(S.T, F.bg[0], S.Cr), fmaf(S.T, F.bg[1], S.Cg), fmaf(S.T, F.bg[2], S.Cb),
+    const float r = quad_sum(S.Cr) * F.light[0], g = quad_sum(S.Cg) * F.light[1], b = quad_sum(S.Cb) * F.light[2];
+    return make_float4(fmaf(S.T, F.bg[0], r), fmaf(S.T, F.bg[1], g), fmaf(S.T, F.bg[2], b),
                        fmaf(S.T, F.bg[3], 1.0f - S.T));
 }
 
-template <typename VT, int LAYOUT, int MODE, int SDT, int SL, int G>
+template <typename VT, int LAYOUT, int MODE, int SDT, int SL>
 __device__ __forceinline__ float4 render_ray(const RenderFrame& F, const float4* __restrict__ s_tf,
                                              const int* __restrict__ s_next, const uint32_t* __restrict__ s_bits,
                                              int px, int py, uint32_t& nsamp, uint32_t& nop)
 {
     RayState S;
-    if (!ray_setup<VT, LAYOUT, MODE, SDT, SL, G>(F, px, py, S))
+    if (!ray_setup<VT, LAYOUT, MODE, SDT, SL>(F, px, py, S))
         return make_float4(F.bg[0], F.bg[1], F.bg[2], F.bg[3]);
-    while (!ray_step<VT, LAYOUT, MODE, SDT, SL, G>(F, s_tf, s_next, s_bits, S, nop)) {
+    while (!ray_step<VT, LAYOUT, MODE, SDT, SL>(F, s_tf, s_next, s_bits, S, nop)) {
     }
-    if ((threadIdx.x & 63) % G == 0) nsamp += (uint32_t)min(S.count, S.K);
+    if ((threadIdx.x & 3) == 0) nsamp += (uint32_t)min(S.count, S.K);
     return ray_result(F, S);
 }
 
@@ -863,12 +881,8 @@ __device__ __forceinline__ float4 render_ray(const RenderFrame& F, const float4*
 #else
 #define VI_RENDER_OCCUPANCY
 #endif
-#ifndef VI_RAY_LANES
-#define VI_RAY_LANES 4
-#endif
-constexpr int kG = VI_RAY_LANES;  // lanes per ray: 1, 2, 4, 8 or 16
-static_assert(kG == 1 || kG == 2 || kG == 4 || kG == 8 || kG == 16, "lanes per ray");
-constexpr int kWX = (64 / kG) >= 32 ? 8 : 4, kWY = (64 / kG) / kWX;
+constexpr int kG = 4;  // lanes per ray: a DPP quad
+constexpr int kWX = 4, kWY = 4;
 constexpr int kBX = 2 * kWX, kBY = 2 * kWY;
 
 __device__ __forceinline__ void block_pixel(uint32_t tx, uint32_t ty, int* px, int* py)
@@ -921,65 +935,8 @@ __device__ __forceinline__ void shade_pixel(const RenderFrame& F, const float4* 
     uint32_t ns = 0, nop = 0;
     const int lane = threadIdx.x & 63;
     if (px < F.width && py < F.height) {
-        const float4 c = render_ray<VT, LAYOUT, MODE, SDT, SL, kG>(F, s_tf, s_next, s_bits, px, py, ns, nop);
+        const float4 c = render_ray<VT, LAYOUT, MODE, SDT, SL>(F, s_tf, s_next, s_bits, px, py, ns, nop);
         if (lane % kG == 0) F.out[(size_t)py * F.width + px] = c;
-    }
-    group_count_add(F, gc, ns, nop);
-}
-
-// Ray compaction (VI_RENDER_COMPACT = 1): a wave owns four blocks of
-// (64 / kG) rays and its groups take the next ray of the wave's list as they
-// finish, a refill at a time once at least VI_COMPACT_REFILL groups are idle
-// (a refill runs the set-up code for the whole wave, so one per finished
-// ray would cost more than the idle lanes it saves).  The per-ray
-// arithmetic is unchanged, so the image and counts are the same bits as
-// with one block per wave.
-#ifndef VI_RENDER_COMPACT
-#define VI_RENDER_COMPACT 0
-#endif
-#ifndef VI_COMPACT_REFILL
-#define VI_COMPACT_REFILL 8
-#endif
-constexpr bool kCompact = VI_RENDER_COMPACT != 0;
-
-template <typename VT, int LAYOUT, int MODE, int SDT, int SL>
-__device__ __forceinline__ void shade_region_compact(const RenderFrame& F, const float4* s_tf, const int* s_next,
-                                                     const uint32_t* s_bits, GroupCount* gc, int x0, int y0)
-{
-    constexpr int kGroups = 64 / kG, kRays = 4 * kGroups;
-    const int lane = threadIdx.x & 63, g = lane % kG, grp = lane / kG;
-    RayState S;
-    bool live = false;
-    int px = 0, py = 0, next = 0;  // next: the wave's next ray (uniform)
-    uint32_t ns = 0, nop = 0;
-    for (;;) {
-        const uint64_t idle = __ballot(!live && g == 0);
-        const int nidle = __popcll(idle);
-        if (next < kRays && (nidle >= VI_COMPACT_REFILL || nidle == kGroups)) {
-            if (!live) {
-                const int r = next + __popcll(idle & ((1ull << (grp * kG)) - 1ull));
-                if (r < kRays) {
-                    const int b = r / kGroups, i = r % kGroups;
-                    px = x0 + (b & 1) * kWX + i % kWX;
-                    py = y0 + (b >> 1) * kWY + i / kWX;
-                    if (px < F.width && py < F.height) {
-                        live = ray_setup<VT, LAYOUT, MODE, SDT, SL, kG>(F, px, py, S);
-                        if (!live && g == 0)
-                            F.out[(size_t)py * F.width + px] = make_float4(F.bg[0], F.bg[1], F.bg[2], F.bg[3]);
-                    }
-                }
-            }
-            next += nidle;
-            continue;
-        }
-        if (nidle == kGroups) break;  // nothing live, nothing left
-        if (live && ray_step<VT, LAYOUT, MODE, SDT, SL, kG>(F, s_tf, s_next, s_bits, S, nop)) {
-            if (g == 0) {
-                ns += (uint32_t)min(S.count, S.K);
-                F.out[(size_t)py * F.width + px] = ray_result(F, S);
-            }
-            live = false;
-        }
     }
     group_count_add(F, gc, ns, nop);
 }
@@ -1001,23 +958,12 @@ __device__ __forceinline__ void render_frame(const RenderFrame& F)
     stage_occupancy(F.occ, s_bits);
     __syncthreads();
 
-    if constexpr (kCompact) {
-        // workgroup tile of 2 x 2 waves, each 2 x 2 blocks of kWX x kWY pixels
-        const uint32_t tiles_x = (F.width + 4 * kWX - 1) / (4 * kWX), tiles_y = (F.height + 4 * kWY - 1) / (4 * kWY);
-        uint32_t tx, ty;
-        if (!supertile_of(blockIdx.x, tiles_x, tiles_y, &tx, &ty)) return;
-        const int wave = threadIdx.x >> 6;
-        shade_region_compact<VT, LAYOUT, MODE, SDT, SL>(F, s_tf, s_next, s_bits, &gc,
-                                                        (int)tx * 4 * kWX + (wave & 1) * 2 * kWX,
-                                                        (int)ty * 4 * kWY + (wave >> 1) * 2 * kWY);
-    } else {
-        const uint32_t tiles_x = (F.width + kBX - 1) / kBX, tiles_y = (F.height + kBY - 1) / kBY;
-        uint32_t tx, ty;
-        if (!supertile_of(blockIdx.x, tiles_x, tiles_y, &tx, &ty)) return;
-        int px, py;
-        block_pixel(tx, ty, &px, &py);
-        shade_pixel<VT, LAYOUT, MODE, SDT, SL>(F, s_tf, s_next, s_bits, &gc, px, py);
-    }
+    const uint32_t tiles_x = (F.width + kBX - 1) / kBX, tiles_y = (F.height + kBY - 1) / kBY;
+    uint32_t tx, ty;
+    if (!supertile_of(blockIdx.x, tiles_x, tiles_y, &tx, &ty)) return;
+    int px, py;
+    block_pixel(tx, ty, &px, &py);
+    shade_pixel<VT, LAYOUT, MODE, SDT, SL>(F, s_tf, s_next, s_bits, &gc, px, py);
 }
 
 // --------------------------------------------------------------------------
@@ -1151,8 +1097,7 @@ static hipError_t launch_batch_l(int sdt, int sl, int mode, const RenderFrame* f
 template <typename VT, int LAYOUT, int SDT, int SL>
 static hipError_t launch_mode(const RenderFrame& f, hipStream_t s)
 {
-    const uint32_t tw = kCompact ? 4 * kWX : kBX, th = kCompact ? 4 * kWY : kBY;
-    dim3 grid(supertile_grid((f.width + tw - 1) / tw, (f.height + th - 1) / th)), block(256);
+    dim3 grid(supertile_grid((f.width + kBX - 1) / kBX, (f.height + kBY - 1) / kBY)), block(256);
     const size_t lds =
         (sizeof(float4) + sizeof(int)) * (size_t)f.K + (f.occ.bits ? sizeof(uint32_t) * (f.occ.words + f.occ.swords) : 0);
     switch (kernel_mode(f)) {
