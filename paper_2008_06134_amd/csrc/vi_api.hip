@@ -104,6 +104,9 @@ vi::OccMap occ_of(const vi_volume* v)
     o.words = o.bits ? words : 0;
     o.snc = o.bits ? snc : 0;
     o.swords = o.bits ? swords : 0;
+    o.ic = v->minmax ? 1.0f / (float)v->cell : 0.0f;
+    o.oc = (float)(v->n / 2) * o.ic;
+    o.cmax = (float)o.nc - 0.5f;
     return o;
 }
 
@@ -737,6 +740,8 @@ int make_frame(const vi_volume* vol, const vi_tf* tf, const vi_slices* sl, const
     }
     F.lo = (float)(-hoff);
     F.hi = (float)(Nd - hoff);
+    F.vlo = (float)(-F.M);
+    F.vhi = (float)(F.N - 1 - F.M);
     // segments per ray stay below 2^24, where float segment positions are exact
     if (sqrt(3.0) * Nd / step_vox > 16777216.0)
         return fail(VI_E_INVALID_ARG, "step_vox %g gives more than 2^24 segments per ray", (double)step_vox);

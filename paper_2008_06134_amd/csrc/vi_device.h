@@ -155,45 +155,10 @@ __device__ __forceinline__ uint32_t vol_oz(const VolIndex& I, int z)
     return __umul24((uint32_t)z, I.sz);
 }
 
-// The four normalised values of quad slot `q` (VI_LAYOUT_QUAD4): one load
-// of 4 elements, each converted exactly as voxel_norm converts it.
-template <typename VT>
-__device__ __forceinline__ float4 quad_norm(const VT* __restrict__ v, uint32_t q, float scale);
-template <>
-__device__ __forceinline__ float4 quad_norm<uint8_t>(const uint8_t* __restrict__ v, uint32_t q, float scale)
-{
-    const uint32_t w = ((const uint32_t*)v)[q];
-    return make_float4(clampf01((float)(w & 0xffu) * scale), clampf01((float)((w >> 8) & 0xffu) * scale),
-                       clampf01((float)((w >> 16) & 0xffu) * scale), clampf01((float)(w >> 24) * scale));
-}
-template <>
-__device__ __forceinline__ float4 quad_norm<uint16_t>(const uint16_t* __restrict__ v, uint32_t q, float scale)
-{
-    const uint2 w = ((const uint2*)v)[q];
-    return make_float4(clampf01((float)(w.x & 0xffffu) * scale), clampf01((float)(w.x >> 16) * scale),
-                       clampf01((float)(w.y & 0xffffu) * scale), clampf01((float)(w.y >> 16) * scale));
-}
-template <>
-__device__ __forceinline__ float4 quad_norm<__half>(const __half* __restrict__ v, uint32_t q, float scale)
-{
-    const uint2 w = ((const uint2*)v)[q];
-    return make_float4(clampf01(__half2float(__ushort_as_half((unsigned short)(w.x & 0xffffu))) * scale),
-                       clampf01(__half2float(__ushort_as_half((unsigned short)(w.x >> 16))) * scale),
-                       clampf01(__half2float(__ushort_as_half((unsigned short)(w.y & 0xffffu))) * scale),
-                       clampf01(__half2float(__ushort_as_half((unsigned short)(w.y >> 16))) * scale));
-}
-template <>
-__device__ __forceinline__ float4 quad_norm<float>(const float* __restrict__ v, uint32_t q, float scale)
-{
-    const float4 w = ((const float4*)v)[q];
-    return make_float4(clampf01(w.x * scale), clampf01(w.y * scale), clampf01(w.z * scale), clampf01(w.w * scale));
-}
-
 // A trilinear footprint split into its loads and its arithmetic, so that a
 // caller can issue the loads of several footprints before it needs any of
 // them.  RawFoot holds the raw elements (eight voxels, or the two quad slots
-// at z and z+1); foot_value converts and interpolates them exactly as
-// sample_volume does.
+// at z and z+1); foot_value converts and interpolates them.
 template <typename VT> struct QuadRaw { using T = uint2; };           // 16-bit voxels
 template <> struct QuadRaw<uint8_t> { using T = uint32_t; };
 template <> struct QuadRaw<float> { using T = float4; };
@@ -275,41 +240,50 @@ __device__ __forceinline__ float foot_value(const RawFoot<VT, LAYOUT>& r, float 
     return fmaf(wz, c1 - c0, c0);
 }
 
+// floor(x) as an integer in one instruction (the compiler takes two, and a
+// subtraction for the fraction, which v_fract_f32 gives in one).
+__device__ __forceinline__ int floor_int(float x)
+{
+    int i;
+    asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(i) : "v"(x));
+    return i;
+}
+
 // Trilinear sample at offset-voxel coordinates h = g - M (g = p*N - 1/2),
 // clamp to edge.  M is an integer so floor/fraction are taken on h exactly.
+// The coordinates are clamped to the first and last voxel centre ([lo, hi] =
+// [-M, N - 1 - M]) before they are split, one instruction an axis: beyond
+// them both corners of an axis hold the edge voxel, which the weight 0 there
+// gives exactly.
 template <typename VT, int LAYOUT>
-__device__ __forceinline__ float sample_volume(const VT* __restrict__ vol, const VolIndex& I, int N, int M,
-                                               float scale, float hx, float hy, float hz)
+__device__ __forceinline__ float sample_volume(const VT* __restrict__ vol, const VolIndex& I, int N, int M, float lo,
+                                               float hi, float scale, float hx, float hy, float hz)
 {
-    float fx = floorf(hx), fy = floorf(hy), fz = floorf(hz);
-    float wx = hx - fx, wy = hy - fy, wz = hz - fz;
-    int x0 = (int)fx + M, y0 = (int)fy + M, z0 = (int)fz + M;
-    if (LAYOUT == VI_LAYOUT_QUAD4) {
-        // the slot of the clamped lower corner holds the x/y neighbours,
-        // themselves clamped; below the first voxel both x (or y) corners
-        // clamp to voxel 0, which a zero weight reproduces exactly
-        const uint32_t xy = vol_ox<LAYOUT>(I, clampi(x0, 0, N - 1)) + vol_oy<LAYOUT>(I, clampi(y0, 0, N - 1));
-        const float4 a = quad_norm(vol, vol_oz<LAYOUT>(I, clampi(z0, 0, N - 1)) + xy, scale);
-        const float4 b = quad_norm(vol, vol_oz<LAYOUT>(I, clampi(z0 + 1, 0, N - 1)) + xy, scale);
-        if (x0 < 0) wx = 0.0f;
-        if (y0 < 0) wy = 0.0f;
-        const float c00 = fmaf(wx, a.y - a.x, a.x), c01 = fmaf(wx, a.w - a.z, a.z);
-        const float c10 = fmaf(wx, b.y - b.x, b.x), c11 = fmaf(wx, b.w - b.z, b.z);
-        const float c0 = fmaf(wy, c01 - c00, c00), c1 = fmaf(wy, c11 - c10, c10);
-        return fmaf(wz, c1 - c0, c0);
+    hx = __builtin_amdgcn_fmed3f(hx, lo, hi);
+    hy = __builtin_amdgcn_fmed3f(hy, lo, hi);
+    hz = __builtin_amdgcn_fmed3f(hz, lo, hi);
+    const int x0 = floor_int(hx) + M, y0 = floor_int(hy) + M, z0 = floor_int(hz) + M;
+    const float wx = __builtin_amdgcn_fractf(hx), wy = __builtin_amdgcn_fractf(hy), wz = __builtin_amdgcn_fractf(hz);
+    const uint32_t za = vol_oz<LAYOUT>(I, z0), zb = vol_oz<LAYOUT>(I, min(z0 + 1, N - 1));
+    RawFoot<VT, LAYOUT> r;
+    if constexpr (LAYOUT == VI_LAYOUT_QUAD4) {
+        using Q = typename QuadRaw<VT>::T;
+        const uint32_t xy = vol_ox<LAYOUT>(I, x0) + vol_oy<LAYOUT>(I, y0);
+        r.a = ((const Q*)vol)[za + xy];  // (may pass 4 GiB: 64-bit addressing)
+        r.b = ((const Q*)vol)[zb + xy];
+    } else {
+        const uint32_t xa = vol_ox<LAYOUT>(I, x0), xb = vol_ox<LAYOUT>(I, min(x0 + 1, N - 1));
+        const uint32_t ya = vol_oy<LAYOUT>(I, y0), yb = vol_oy<LAYOUT>(I, min(y0 + 1, N - 1));
+        r.v[0] = ld32<VT>(vol, za + ya + xa);
+        r.v[1] = ld32<VT>(vol, za + ya + xb);
+        r.v[2] = ld32<VT>(vol, za + yb + xa);
+        r.v[3] = ld32<VT>(vol, za + yb + xb);
+        r.v[4] = ld32<VT>(vol, zb + ya + xa);
+        r.v[5] = ld32<VT>(vol, zb + ya + xb);
+        r.v[6] = ld32<VT>(vol, zb + yb + xa);
+        r.v[7] = ld32<VT>(vol, zb + yb + xb);
     }
-    const uint32_t xa = vol_ox<LAYOUT>(I, clampi(x0, 0, N - 1)), xb = vol_ox<LAYOUT>(I, clampi(x0 + 1, 0, N - 1));
-    const uint32_t ya = vol_oy<LAYOUT>(I, clampi(y0, 0, N - 1)), yb = vol_oy<LAYOUT>(I, clampi(y0 + 1, 0, N - 1));
-    const uint32_t za = vol_oz<LAYOUT>(I, clampi(z0, 0, N - 1)), zb = vol_oz<LAYOUT>(I, clampi(z0 + 1, 0, N - 1));
-    const uint32_t raa = za + ya, rab = za + yb, rba = zb + ya, rbb = zb + yb;
-    float v000 = voxel_norm(vol, raa + xa, scale), v001 = voxel_norm(vol, raa + xb, scale);
-    float v010 = voxel_norm(vol, rab + xa, scale), v011 = voxel_norm(vol, rab + xb, scale);
-    float v100 = voxel_norm(vol, rba + xa, scale), v101 = voxel_norm(vol, rba + xb, scale);
-    float v110 = voxel_norm(vol, rbb + xa, scale), v111 = voxel_norm(vol, rbb + xb, scale);
-    float c00 = fmaf(wx, v001 - v000, v000), c01 = fmaf(wx, v011 - v010, v010);
-    float c10 = fmaf(wx, v101 - v100, v100), c11 = fmaf(wx, v111 - v110, v110);
-    float c0 = fmaf(wy, c01 - c00, c00), c1 = fmaf(wy, c11 - c10, c10);
-    return fmaf(wz, c1 - c0, c0);
+    return foot_value<VT, LAYOUT>(r, wx, wy, wz, scale);
 }
 
 // Stack layout: every layer is stored as 8 x 4 texel tiles (one 128-byte
@@ -340,14 +314,7 @@ __device__ __forceinline__ bool cell_empty(const float2 m, const int* s_next, fl
     const int hi = min((int)(m.y * Km1) + 2, K - 1);
     return s_next[lo] > hi;
 }
-// Whether cell c may hold opacity: its occupancy bit (the LDS copy
-// `s_bits`), or the map entry against the transfer function.
-__device__ __forceinline__ bool cell_occupied(const OccMap& o, const uint32_t* s_bits, uint32_t c,
-                                              const int* s_next, float Km1, int K)
-{
-    if (o.bits) return (s_bits[c >> 5] >> (c & 31u)) & 1u;
-    return !cell_empty(o.mm[c], s_next, Km1, K);
-}
+// Whether cell c may hold opacity: its bit in the LDS copy `s_bits`.
 __device__ __forceinline__ bool occupancy_bit(const uint32_t* s_bits, uint32_t c)
 {
     return (s_bits[c >> 5] >> (c & 31u)) & 1u;

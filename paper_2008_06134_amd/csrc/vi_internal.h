@@ -38,6 +38,9 @@ struct OccMap {
     uint32_t words;        // 32-bit words of cell bits (the super-cell bits follow)
     uint32_t snc;          // super-cells per axis, ceil(nc / 4)
     uint32_t swords;       // 32-bit words of super-cell bits
+    // the cell of offset-voxel position h (render): clamp(h ic + oc, 0, cmax)
+    // truncated; ic = 1 / cell and oc = M / cell are exact, cmax = nc - 1/2
+    float ic, oc, cmax;
 };
 constexpr uint32_t kMaxLdsOccWords = 2304;  // 9 KiB of bits (65536 cells and their super-cells)
 
@@ -123,6 +126,7 @@ struct RenderFrame {
     float cam_o[3], cam_ol[3], cam_f[3], cam_fl[3];
     float cam_b[3], cam_bl[3], cam_sx[3], cam_sxl[3], cam_sy[3], cam_syl[3];
     float lo, hi;        // the cube in h coordinates: [-1/2 - M, N - 1/2 - M]
+    float vlo, vhi;      // first and last voxel centre in h coordinates: -M, N - 1 - M
     // march
     int mode;
     float dt;            // step in voxels (= the reference length of Eq. 6's exponent)

@@ -487,16 +487,22 @@ __device__ __forceinline__ bool quad_all(bool p)
 struct RayState {
     float hx0, hy0, hz0, hdx, hdy, hdz;  // entry point and direction
     float Df;                            // chord length, voxels
-    int K;                               // segments
+    float K;                             // segments (an integer below 2^24, as k and count)
     float qz0, qx0, qy0, qdz, qdx, qdy, pd0, pdd;
     ConeFrame cf;
     float lx, ly, lz, vx, vy, vz, lv;
-    float ihx, ihy, ihz;
+    // distance to the face at voxel coordinate f (from the volume's corner)
+    // along an axis: f ih + jb, with the faces moved inward (see ray_step)
+    float ihx, ihy, ihz, jbx, jby, jbz;
     float Cr, Cg, Cb, T;
-    uint32_t last_cell;
+    uint32_t last_cell;                  // map without bits: the last cell looked up
     bool cell_is_empty;
-    int k, count;
+    float k, count;
 };
+
+// how far the faces of an empty box are moved inward, in voxels: two orders
+// above the float position error
+constexpr float kJumpEps = 0.02f;
 
 constexpr bool is_point_gather(int mode)
 {
@@ -563,15 +569,13 @@ __device__ __forceinline__ bool ray_setup(const RenderFrame& F, int px, int py, 
 
     const F2 Dc = f2_sub(tf, ti);  // chord length, voxels
     S.Df = Dc.hi;
-    int K;
     {
         // K = ceil(D / dt), decided on the pair
         const F2 q = f2_mul(Dc, F2{F.idt, F.idtl});
         float c = ceilf(q.hi);
         if (c == q.hi && q.lo > 0.0f) c += 1.0f;
         else if (c - 1.0f - q.hi >= q.lo) c -= 1.0f;
-        K = (int)c;
-        S.K = K;
+        S.K = c;
     }
     // volume: entry point (value, remainder) and direction (value, remainder)
     F2 pin[3];
@@ -659,13 +663,18 @@ __device__ __forceinline__ bool ray_setup(const RenderFrame& F, int px, int py, 
     // factors, which keeps its relative precision down to term_eps).
     S.Cr = S.Cg = S.Cb = 0.f;
     S.T = 1.0f;
-    S.ihx = hdx != 0.f ? __builtin_amdgcn_rcpf(hdx) : 0.f;
-    S.ihy = hdy != 0.f ? __builtin_amdgcn_rcpf(hdy) : 0.f;
-    S.ihz = hdz != 0.f ? __builtin_amdgcn_rcpf(hdz) : 0.f;
+    // (an axis the ray does not move along never limits a jump)
+    const auto jump_axis = [&](float h0, float hd, float& ih, float& jb) {
+        ih = hd != 0.f ? __builtin_amdgcn_rcpf(hd) : 0.f;
+        jb = hd != 0.f ? ((hd > 0.f ? -kJumpEps : kJumpEps) - (float)F.M - h0) * ih : 3.0e38f;
+    };
+    jump_axis(S.hx0, hdx, S.ihx, S.jbx);
+    jump_axis(S.hy0, hdy, S.ihy, S.jby);
+    jump_axis(S.hz0, hdz, S.ihz, S.jbz);
     S.last_cell = 0xffffffffu;
     S.cell_is_empty = false;
-    S.k = 0;
-    S.count = K;
+    S.k = 0.f;
+    S.count = S.K;
     return true;
 }
 
@@ -679,53 +688,47 @@ __device__ __forceinline__ bool ray_step(const RenderFrame& F, const float4* __r
     const int g = threadIdx.x & 3;
     constexpr bool PT = is_point_gather(MODE);
     constexpr bool PTP = MODE == kModePointPhong, PHONG = MODE == VI_MODE_PHONG || PTP;
-    const float hx0 = S.hx0, hy0 = S.hy0, hz0 = S.hz0, hdx = S.hdx, hdy = S.hdy, hdz = S.hdz;
-    const float Df = S.Df, ihx = S.ihx, ihy = S.ihy, ihz = S.ihz;
-    const int K = S.K;
-    uint32_t& last_cell = S.last_cell;
-    bool& cell_is_empty = S.cell_is_empty;
-    int& k = S.k;
     const VT* __restrict__ vol = (const VT*)F.vol;
     const VolIndex VI_ = {1u, F.vsy, F.vsz};
-    const float dtf = F.dt;
     const float Km1 = (float)(F.K - 1);
-    // Empty-space traversal.  A step whose four segments all lie in
-    // zero-opacity cells jumps to the last segment midpoint inside the empty
-    // box around its last segment -- the segment's cell, or the cell's
-    // super-cell (4 x 4 x 4 cells) when that is empty too -- with the box's
-    // faces moved inward by kEps voxels (far above the float position
-    // error), so no segment with non-zero opacity is ever skipped.  Faces of
-    // boxes at the volume's edge toward the outside are at infinity (edge
-    // cells also hold the clamped positions beyond the last voxel centre).
-    const float kEps = 0.02f;
-    const float Mf = (float)F.M;
-    const int kk = k + g;
-    const bool in = kk < K;
+    const float kk = S.k + (float)g;
+    const bool in = kk < S.K;
     float om = 1.f, sm = 0.f, hx = 0.f, hy = 0.f, hz = 0.f;  // om = 1 - alpha of the segment
     float er = 0.f, eg = 0.f, eb = 0.f;                      // its colour
     bool empty = true;
-    int cx = 0, cy = 0, cz = 0;  // the segment's cell
+    float cx = 0.f, cy = 0.f, cz = 0.f;  // the segment's cell
     if (in) {
-        const float s0 = (float)kk * dtf;
-        const float s1 = fminf((float)(kk + 1) * dtf, Df);
+        const float s0 = kk * F.dt;
+        const float s1 = fminf((kk + 1.0f) * F.dt, S.Df);
         const float len = s1 - s0;
         sm = 0.5f * (s0 + s1);
-        hx = fmaf(sm, hdx, hx0), hy = fmaf(sm, hdy, hy0), hz = fmaf(sm, hdz, hz0);
+        hx = fmaf(sm, S.hdx, S.hx0), hy = fmaf(sm, S.hdy, S.hy0), hz = fmaf(sm, S.hdz, S.hz0);
         empty = false;
         if (F.occ.mm) {
-            const int gx = clampi((int)floorf(hx) + F.M, 0, F.N - 1),
-                      gy = clampi((int)floorf(hy) + F.M, 0, F.N - 1),
-                      gz = clampi((int)floorf(hz) + F.M, 0, F.N - 1);
-            cx = gx >> F.occ.shift, cy = gy >> F.occ.shift, cz = gz >> F.occ.shift;
-            const uint32_t c = __umul24(__umul24((uint32_t)cz, F.occ.nc) + (uint32_t)cy, F.occ.nc) + (uint32_t)cx;
-            if (c != last_cell) {
-                last_cell = c;
-                cell_is_empty = !cell_occupied(F.occ, s_bits, c, s_next, Km1, F.K);
+            // The cell, by one multiply-add, clamp and truncation an axis.
+            // Rounding may put a position within 1e-4 voxel of a cell's face
+            // into the neighbour (h ic is exact, the sum rounds at 2^-24 of
+            // at most 2^9 cells): its value is then within 1e-4 of the range
+            // the map has for that cell, a tenth of a table entry for the
+            // 1024 entries a table may have, and the emptiness test leaves
+            // one whole entry on each side.
+            cx = __builtin_amdgcn_fmed3f(fmaf(hx, F.occ.ic, F.occ.oc), 0.f, F.occ.cmax);
+            cy = __builtin_amdgcn_fmed3f(fmaf(hy, F.occ.ic, F.occ.oc), 0.f, F.occ.cmax);
+            cz = __builtin_amdgcn_fmed3f(fmaf(hz, F.occ.ic, F.occ.oc), 0.f, F.occ.cmax);
+            const uint32_t c =
+                __umul24(__umul24((uint32_t)cz, F.occ.nc) + (uint32_t)cy, F.occ.nc) + (uint32_t)cx;
+            if (F.occ.bits) {
+                empty = !occupancy_bit(s_bits, c);
+            } else {
+                if (c != S.last_cell) {
+                    S.last_cell = c;
+                    S.cell_is_empty = cell_empty(F.occ.mm[c], s_next, Km1, F.K);
+                }
+                empty = S.cell_is_empty;
             }
-            empty = cell_is_empty;
         }
         if (!empty) {
-            const float v = sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.scale, hx, hy, hz);
+            const float v = sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.vlo, F.vhi, F.scale, hx, hy, hz);
             const float x = v * Km1;
             const int e0 = min((int)x, F.K - 2);
             const float w = x - (float)e0;
@@ -739,41 +742,40 @@ __device__ __forceinline__ bool ray_step(const RenderFrame& F, const float4* __r
         }
     }
     if (quad_all(empty)) {
-        // every segment of this step is empty (or past the exit): jump,
-        // staying on multiples of four so that the steps group segments as a
-        // march without the map would (the products then round alike and
-        // the map changes no bit of the result).  Each lane finds the
-        // last segment inside the empty box around its own segment; the
-        // quad takes its last lane's.
-        int jl = K;
+        // Every segment of this step is empty (or past the exit): jump to
+        // the last segment midpoint inside the empty box around the step's
+        // last segment -- the segment's cell, or the cell's super-cell (4 x 4
+        // x 4 cells) when that is empty too -- with the box's faces moved
+        // inward by kJumpEps voxels (far above the float position error), so
+        // no segment with non-zero opacity is ever skipped.  The jump stays
+        // on multiples of four so that the steps group segments as a march
+        // without the map would (the products then round alike and the map
+        // changes no bit of the result).  Each lane finds the last segment
+        // inside the box around its own segment; the quad takes its last
+        // lane's.  Per axis the exit face is the box's upper or lower one by
+        // the ray's sign; no branches.  (A ray leaving through a lower face
+        // of the volume takes the last half voxel, where positions clamp to
+        // cell 0, in a step of its own.)
+        float jl = S.K;
         if (in && F.occ.mm) {
-            int sh = F.occ.shift, bx = cx, by = cy, bz = cz, last = (int)F.occ.nc - 1;
+            float size = (float)(1 << F.occ.shift), inv = 1.0f;
             if (F.occ.bits) {
-                const int sx = cx >> 2, sy = cy >> 2, sz = cz >> 2;
-                const uint32_t sc =
-                    __umul24(__umul24((uint32_t)sz, F.occ.snc) + (uint32_t)sy, F.occ.snc) + (uint32_t)sx;
-                if (!occupancy_bit(s_bits + F.occ.words, sc)) {
-                    sh += 2;
-                    bx = sx, by = sy, bz = sz;
-                    last = (int)F.occ.snc - 1;
-                }
+                const uint32_t sx = (uint32_t)cx >> 2, sy = (uint32_t)cy >> 2, sz = (uint32_t)cz >> 2;
+                const uint32_t sc = __umul24(__umul24(sz, F.occ.snc) + sy, F.occ.snc) + sx;
+                if (!occupancy_bit(s_bits + F.occ.words, sc)) size *= 4.0f, inv = 0.25f;
             }
-            // distance along the ray to the box's exit faces, moved inward
-            const float edge = (float)(1 << sh) - kEps;
-            float se = 3.4e38f;
-            if (hdx > 0.f && bx < last) se = fminf(se, ((float)(bx << sh) - Mf + edge - hx0) * ihx);
-            if (hdx < 0.f && bx > 0) se = fminf(se, ((float)(bx << sh) - Mf + kEps - hx0) * ihx);
-            if (hdy > 0.f && by < last) se = fminf(se, ((float)(by << sh) - Mf + edge - hy0) * ihy);
-            if (hdy < 0.f && by > 0) se = fminf(se, ((float)(by << sh) - Mf + kEps - hy0) * ihy);
-            if (hdz > 0.f && bz < last) se = fminf(se, ((float)(bz << sh) - Mf + edge - hz0) * ihz);
-            if (hdz < 0.f && bz > 0) se = fminf(se, ((float)(bz << sh) - Mf + kEps - hz0) * ihz);
+            const float fx = floorf(cx * inv) + (S.ihx > 0.f ? 1.0f : 0.0f);
+            const float fy = floorf(cy * inv) + (S.ihy > 0.f ? 1.0f : 0.0f);
+            const float fz = floorf(cz * inv) + (S.ihz > 0.f ? 1.0f : 0.0f);
+            // distance along the ray to the box's exit faces
+            const float se = fminf(fminf(fmaf(fx * size, S.ihx, S.jbx), fmaf(fy * size, S.ihy, S.jby)),
+                                   fmaf(fz * size, S.ihz, S.jbz));
             // last full segment whose midpoint (j + 1/2) dt is <= se
-            const float jf = floorf(fmaf(se, F.idt, -0.5f));
-            jl = jf >= (float)(K - 1) ? K - 1 : (int)jf;
+            jl = fminf(floorf(fmaf(se, F.idt, -0.5f)), S.K - 1.0f);
         }
-        const int jlast = __builtin_amdgcn_mov_dpp(jl, 0xff, 0xf, 0xf, true);  // lane 3's
-        k = max(k + 4, (jlast + 1) & ~3);
-        return k >= K;
+        const float jlast = quad_perm<3, 3, 3, 3>(jl);
+        S.k = fmaxf(S.k + 4.0f, 4.0f * floorf(0.25f * (jlast + 1.0f)));
+        return S.k >= S.K;
     }
     // front to back over the four segments of this step (Eq. 3 in product
     // form): a segment is composited while the transmittance in front of it
@@ -793,12 +795,12 @@ __device__ __forceinline__ bool ray_step(const RenderFrame& F, const float4* __r
         if (PHONG) {
             // central differences one voxel either side (exact
             // offsets in voxel units)
-            const float gx = 0.5f * (sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.scale, hx + 1.f, hy, hz) -
-                                     sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.scale, hx - 1.f, hy, hz));
-            const float gy = 0.5f * (sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.scale, hx, hy + 1.f, hz) -
-                                     sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.scale, hx, hy - 1.f, hz));
-            const float gz = 0.5f * (sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.scale, hx, hy, hz + 1.f) -
-                                     sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.scale, hx, hy, hz - 1.f));
+            const float gx = 0.5f * (sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.vlo, F.vhi, F.scale, hx + 1.f, hy, hz) -
+                                     sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.vlo, F.vhi, F.scale, hx - 1.f, hy, hz));
+            const float gy = 0.5f * (sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.vlo, F.vhi, F.scale, hx, hy + 1.f, hz) -
+                                     sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.vlo, F.vhi, F.scale, hx, hy - 1.f, hz));
+            const float gz = 0.5f * (sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.vlo, F.vhi, F.scale, hx, hy, hz + 1.f) -
+                                     sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.vlo, F.vhi, F.scale, hx, hy, hz - 1.f));
             const float gn = sqrtf(fmaf(gx, gx, fmaf(gy, gy, gz * gz)));
             const float inv = -1.0f / fmaxf(gn, F.grad_eps);  // n = -g / max(|g|, eps)
             const float nx = gx * inv, ny = gy * inv, nz = gz * inv;
@@ -841,11 +843,11 @@ __device__ __forceinline__ bool ray_step(const RenderFrame& F, const float4* __r
     if (S.T <= F.term_eps) {
         // composited segments of the step: the quad's lanes that were seen
         const unsigned long long m = __ballot(seen && in) >> (threadIdx.x & 60);
-        S.count = k + __popc((uint32_t)m & 15u);
+        S.count = S.k + (float)__popc((uint32_t)m & 15u);
         return true;
     }
-    k += 4;
-    return k >= K;
+    S.k += 4.0f;
+    return S.k >= S.K;
 }
 
 // The finished ray's colour over the background, and its segment count.
@@ -866,7 +868,7 @@ __device__ __forceinline__ float4 render_ray(const RenderFrame& F, const float4*
         return make_float4(F.bg[0], F.bg[1], F.bg[2], F.bg[3]);
     while (!ray_step<VT, LAYOUT, MODE, SDT, SL>(F, s_tf, s_next, s_bits, S, nop)) {
     }
-    if ((threadIdx.x & 3) == 0) nsamp += (uint32_t)min(S.count, S.K);
+    if ((threadIdx.x & 3) == 0) nsamp += (uint32_t)fminf(S.count, S.K);
     return ray_result(F, S);
 }
 
