@@ -658,12 +658,23 @@ int make_frame(const vi_volume* vol, const vi_tf* tf, const vi_slices* sl, const
         F.rlayer = row_layer(sl->res, sl->dtype);
         F.Mz = sl->n / 2;
         F.Mr = sl->res / 2;
-        // rows: the shifted bases and the element of light-grid cell (0, 0, 0)
-        const size_t es = elem_size(sl->dtype);
-        F.stack_r1 = (const char*)sl->data + (size_t)F.rpitch * es;
-        F.stack_l1 = (const char*)sl->data + (size_t)F.rlayer * es;
-        F.stack_l1r1 = (const char*)sl->data + ((size_t)F.rlayer + F.rpitch) * es;
-        F.rbase = F.rorg + (uint32_t)F.Mr * F.rpitch + (uint32_t)F.Mr + (uint32_t)F.Mz * F.rlayer;
+        F.zlo = (float)(-1 - F.Mz);
+        F.zhi = (float)(sl->n - 1 - F.Mz);
+        F.xlo = (float)(-2 - F.Mr);
+        F.xhi = (float)(sl->res - F.Mr);
+        if (sl->layout == VI_STACK_ROWS) {
+            // the element of light-grid cell (0, 0, 0), rounded up to 16
+            // elements with the bases moved back by as much
+            const size_t es = elem_size(sl->dtype);
+            const uint32_t rbase = F.rorg + (uint32_t)F.Mr * F.rpitch + (uint32_t)F.Mr + (uint32_t)F.Mz * F.rlayer;
+            F.rb16 = (int32_t)((rbase + 15u) / 16u);
+            F.rl16 = (int32_t)(F.rlayer / 16u);
+            const char* base = (const char*)sl->data - (size_t)(16u * (uint32_t)F.rb16 - rbase) * es;
+            F.stack = base;
+            F.stack_r1 = base + (size_t)F.rpitch * es;
+            F.stack_l1 = base + (size_t)F.rlayer * es;
+            F.stack_l1r1 = base + ((size_t)F.rlayer + F.rpitch) * es;
+        }
         const double span = sl->dmax - sl->dmin, sc = sl->res / (2.0 * sl->R);
         for (int a = 0; a < 3; ++a) {
             Lq[a] = sl->n * sl->L[a] / span;

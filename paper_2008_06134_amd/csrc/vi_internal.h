@@ -96,7 +96,14 @@ struct RenderFrame {
     const void* stack_r1;
     const void* stack_l1;
     const void* stack_l1r1;
-    uint32_t rbase;  // rows: element of light-grid cell (iz, iy, ix) = rbase + iz rlayer + iy rpitch + ix
+    // rows: element of light-grid cell (iz, iy, ix), from the bases above, is
+    // 16 (rb16 + iz rl16) + iy rpitch + ix: a layer is a multiple of 16
+    // elements, rl16 = rlayer / 16 < 2^23 and |iz| < 2^13 multiply in one 24-bit
+    // multiply-add, and the bases are moved so that the constant is one, too
+    int32_t rb16, rl16;
+    // clamps of light-grid coordinates that keep footprints on stored texels:
+    // z in [-1 - Mz, n - 1 - Mz], x and y in [-2 - Mr, res - Mr]
+    float zlo, zhi, xlo, xhi;
     int stack_dtype;
     int n, res;
     int stack_layout;

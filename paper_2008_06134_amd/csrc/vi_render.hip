@@ -94,45 +94,77 @@ __device__ __forceinline__ float2 pair_value(const PairRaw<VI_BF16>& r)
     return make_float2(fast_exp2(-__uint_as_float(r.w << 16)), fast_exp2(-__uint_as_float(r.w & 0xffff0000u)));
 }
 
-// One row-layout lookup split into its four loads (rows j, j+1 of layers k0
-// and k1) and its arithmetic.  The layout makes every footprint a plain read:
-// layer -1 (face 0) transmits fully, so a depth index in front of the first
-// face needs no test, and the two-texel border lets a footprint that reaches
-// past the grid clamp onto border texels only (a column a < -2 reads the
-// pair (-2, -1), a > res the pair (res, res+1): both 1).  No selects, no
-// branches; the four loads go out together.
-template <int SDT>
-struct RowTap {
-    PairRaw<SDT> a0, a1, b0, b1;  // layer k0 rows j, j+1; layer k1 rows j, j+1
-    float wx, wy, wz;
+// A lookup in three parts, so that the taps of a gather that lie at one depth
+// share the first and a gather can issue the loads of several taps before it
+// needs any of them: the depth part (layers and weight), the loads of the
+// bilinear footprint in both layers, and the two layers' values.
+//
+// Row layout: every footprint is a plain read.  Layer -1 (face 0) transmits
+// fully, so a depth index in front of the first face needs no test; layer n
+// repeats layer n-1, so the second layer needs no clamp; and the two-texel
+// border lets a footprint that reaches past the grid clamp onto border texels
+// only (a column a < -2 reads the pair (-2, -1), a > res the pair (res,
+// res+1): both 1).  Clamping the coordinates (not the texel indices) keeps
+// every footprint on stored texels: beyond the grid both texels of a row are
+// border texels (1), so the value is the same 1 whatever the weight.  One
+// offset serves all four loads, whose next row and next layer come from the
+// shifted bases.
+template <int SL> struct ZPart;
+template <> struct ZPart<VI_STACK_ROWS> {
+    uint32_t e;  // element of the layer's row 0, column 0 (light-grid offsets)
+    float w;
 };
-template <int SDT, bool NEAR>
-__device__ __forceinline__ void rowtap_load(const RenderFrame& F, float z, float x, float y, RowTap<SDT>& t)
+template <> struct ZPart<VI_STACK_TILED> {
+    uint32_t b0, b1;  // elements of the two layers
+    float w;
+    bool front;  // before the first layer: the nearer face is face 0
+};
+template <int SDT, int SL> struct Tap;
+template <int SDT> struct Tap<SDT, VI_STACK_ROWS> {
+    PairRaw<SDT> a0, a1, b0, b1;  // nearer layer rows j, j+1; farther layer rows j, j+1
+    float wx, wy;
+};
+template <int SDT> struct Tap<SDT, VI_STACK_TILED> {
+    float t0, t1;  // the layers' values
+};
+
+template <int SL, bool NEAR>
+__device__ __forceinline__ ZPart<SL> z_part(const RenderFrame& F, float z)
 {
     if (NEAR) z = floorf(z + 0.5f);
-    // clamping the coordinates (not the texel indices) keeps every footprint
-    // on stored texels: beyond the grid both texels of a row are border
-    // texels (1), so the value is the same 1 whatever the weight
-    z = __builtin_amdgcn_fmed3f(z, (float)(-1 - F.Mz), (float)(F.n - 1 - F.Mz));
-    x = __builtin_amdgcn_fmed3f(x, (float)(-2 - F.Mr), (float)(F.res - F.Mr));
-    y = __builtin_amdgcn_fmed3f(y, (float)(-2 - F.Mr), (float)(F.res - F.Mr));
-    const float fz = floorf(z), fx = floorf(x), fy = floorf(y);
-    t.wz = z - fz;
-    t.wx = x - fx;
-    t.wy = y - fy;
-    // texel (k0, b, a) of the footprint, k0 = iz + Mz in -1 .. n-1 and
-    // a, b = ix, iy + Mr in -2 .. res: one offset for all four loads, whose
-    // next row and next layer come from the shifted bases (layer n repeats
-    // layer n-1, so k0 + 1 needs no clamp)
-    const int iz = (int)fz, ix = (int)fx, iy = (int)fy;
-    const uint32_t e = F.rbase + (uint32_t)(iz * (int)F.rlayer) + (uint32_t)__mul24(iy, (int)F.rpitch) + (uint32_t)ix;
+    z = __builtin_amdgcn_fmed3f(z, F.zlo, F.zhi);
+    const int iz = floor_int(z);
+    ZPart<SL> p;
+    p.w = __builtin_amdgcn_fractf(z);
+    if constexpr (SL == VI_STACK_ROWS) {
+        p.e = (uint32_t)(__mul24(iz, F.rl16) + F.rb16) << 4;
+    } else {
+        const int k0 = iz + F.Mz;
+        p.front = k0 < 0;
+        p.b0 = (uint32_t)max(k0, 0) * F.layer;
+        p.b1 = (uint32_t)min(k0 + 1, F.n - 1) * F.layer;
+    }
+    return p;
+}
+
+template <int SDT>
+__device__ __forceinline__ void tap_load(const RenderFrame& F, const ZPart<VI_STACK_ROWS>& p, float x, float y,
+                                         Tap<SDT, VI_STACK_ROWS>& t)
+{
+    x = __builtin_amdgcn_fmed3f(x, F.xlo, F.xhi);
+    y = __builtin_amdgcn_fmed3f(y, F.xlo, F.xhi);
+    const int ix = floor_int(x), iy = floor_int(y);
+    t.wx = __builtin_amdgcn_fractf(x);
+    t.wy = __builtin_amdgcn_fractf(y);
+    const uint32_t e = p.e + (uint32_t)(__mul24(iy, (int)F.rpitch) + ix);
     t.a0 = pair_load<SDT>(F.stack, e);
     t.a1 = pair_load<SDT>(F.stack_r1, e);
     t.b0 = pair_load<SDT>(F.stack_l1, e);
     t.b1 = pair_load<SDT>(F.stack_l1r1, e);
 }
+// the layers' bilinear values, nearer (x) and farther (y)
 template <int SDT>
-__device__ __forceinline__ float rowtap_value(const RowTap<SDT>& t)
+__device__ __forceinline__ float2 tap_layers(const Tap<SDT, VI_STACK_ROWS>& t)
 {
     float2 r0 = pair_value(t.a0), r1 = pair_value(t.a1);
     float ab = fmaf(t.wx, r0.y - r0.x, r0.x), cd = fmaf(t.wx, r1.y - r1.x, r1.x);
@@ -141,8 +173,42 @@ __device__ __forceinline__ float rowtap_value(const RowTap<SDT>& t)
     r1 = pair_value(t.b1);
     ab = fmaf(t.wx, r0.y - r0.x, r0.x);
     cd = fmaf(t.wx, r1.y - r1.x, r1.x);
-    const float t1 = fmaf(t.wy, cd - ab, ab);
-    return fmaf(t.wz, t1 - t0, t0);
+    return make_float2(t0, fmaf(t.wy, cd - ab, ab));
+}
+
+// Tiled layout: eight loads with bounds selects, converted at once.
+template <int SDT>
+__device__ __forceinline__ void tap_load(const RenderFrame& F, const ZPart<VI_STACK_TILED>& p, float x, float y,
+                                         Tap<SDT, VI_STACK_TILED>& t)
+{
+    x = __builtin_amdgcn_fmed3f(x, F.xlo, F.xhi);
+    y = __builtin_amdgcn_fmed3f(y, F.xlo, F.xhi);
+    const int i0 = floor_int(x) + F.Mr, j0 = floor_int(y) + F.Mr;
+    const float wx = __builtin_amdgcn_fractf(x), wy = __builtin_amdgcn_fractf(y);
+    const int res = F.res;
+    const bool vi0 = (unsigned)i0 < (unsigned)res, vi1 = (unsigned)(i0 + 1) < (unsigned)res;
+    const bool vj0 = (unsigned)j0 < (unsigned)res, vj1 = (unsigned)(j0 + 1) < (unsigned)res;
+    const uint32_t oi0 = stack_oi(clampi(i0, 0, res - 1)), oi1 = stack_oi(clampi(i0 + 1, 0, res - 1));
+    const uint32_t oj0 = stack_oj(clampi(j0, 0, res - 1), F.row_tiles32);
+    const uint32_t oj1 = stack_oj(clampi(j0 + 1, 0, res - 1), F.row_tiles32);
+    const auto layer = [&](uint32_t base) {
+        const uint32_t r0 = base + oj0, r1 = base + oj1;
+        float a = stack_texel<SDT>(F.stack, r0 + oi0), b = stack_texel<SDT>(F.stack, r0 + oi1);
+        float c = stack_texel<SDT>(F.stack, r1 + oi0), d = stack_texel<SDT>(F.stack, r1 + oi1);
+        a = (vi0 && vj0) ? a : 1.0f;
+        b = (vi1 && vj0) ? b : 1.0f;
+        c = (vi0 && vj1) ? c : 1.0f;
+        d = (vi1 && vj1) ? d : 1.0f;
+        const float ab = fmaf(wx, b - a, a), cd = fmaf(wx, d - c, c);
+        return fmaf(wy, cd - ab, ab);
+    };
+    t.t0 = p.front ? 1.0f : layer(p.b0);
+    t.t1 = layer(p.b1);
+}
+template <int SDT>
+__device__ __forceinline__ float2 tap_layers(const Tap<SDT, VI_STACK_TILED>& t)
+{
+    return make_float2(t.t0, t.t1);
 }
 
 // Transmittance at light-grid offset coordinates (z, x, y): depth between
@@ -151,53 +217,11 @@ __device__ __forceinline__ float rowtap_value(const RowTap<SDT>& t)
 template <int SDT, int SL, bool NEAR>
 __device__ __forceinline__ float stack_lookup(const RenderFrame& F, float z, float x, float y)
 {
-    if (SL == VI_STACK_ROWS) {
-        RowTap<SDT> t;
-        rowtap_load<SDT, NEAR>(F, z, x, y, t);
-        return rowtap_value<SDT>(t);
-    }
-    if (NEAR) z = floorf(z + 0.5f);
-    z = fminf(fmaxf(z, (float)(-1 - F.Mz)), (float)(F.n - 1 - F.Mz));
-    const float fz = floorf(z), fx = floorf(x), fy = floorf(y);
-    const float wz = z - fz, wx = x - fx, wy = y - fy;
-    const int k0 = (int)fz + F.Mz;
-    const int k1 = min(k0 + 1, F.n - 1);
-    const int i0 = (int)fx + F.Mr, j0 = (int)fy + F.Mr;
-    const int res = F.res;
-    const bool vi0 = (unsigned)i0 < (unsigned)res, vi1 = (unsigned)(i0 + 1) < (unsigned)res;
-    const bool vj0 = (unsigned)j0 < (unsigned)res, vj1 = (unsigned)(j0 + 1) < (unsigned)res;
-    const uint32_t oi0 = stack_oi(clampi(i0, 0, res - 1)), oi1 = stack_oi(clampi(i0 + 1, 0, res - 1));
-    const uint32_t oj0 = stack_oj(clampi(j0, 0, res - 1), F.row_tiles32);
-    const uint32_t oj1 = stack_oj(clampi(j0 + 1, 0, res - 1), F.row_tiles32);
-
-    constexpr float one = 1.0f;
-    float t0 = one;
-    if (k0 >= 0) {
-        const uint32_t base = (uint32_t)k0 * F.layer;
-        const uint32_t r0 = base + oj0, r1 = base + oj1;
-        float a = stack_texel<SDT>(F.stack, r0 + oi0), b = stack_texel<SDT>(F.stack, r0 + oi1);
-        float c = stack_texel<SDT>(F.stack, r1 + oi0), d = stack_texel<SDT>(F.stack, r1 + oi1);
-        a = (vi0 && vj0) ? a : one;
-        b = (vi1 && vj0) ? b : one;
-        c = (vi0 && vj1) ? c : one;
-        d = (vi1 && vj1) ? d : one;
-        const float ab = fmaf(wx, b - a, a), cd = fmaf(wx, d - c, c);
-        t0 = fmaf(wy, cd - ab, ab);
-    }
-    float t1;
-    {
-        const uint32_t base = (uint32_t)k1 * F.layer;
-        const uint32_t r0 = base + oj0, r1 = base + oj1;
-        float a = stack_texel<SDT>(F.stack, r0 + oi0), b = stack_texel<SDT>(F.stack, r0 + oi1);
-        float c = stack_texel<SDT>(F.stack, r1 + oi0), d = stack_texel<SDT>(F.stack, r1 + oi1);
-        a = (vi0 && vj0) ? a : one;
-        b = (vi1 && vj0) ? b : one;
-        c = (vi0 && vj1) ? c : one;
-        d = (vi1 && vj1) ? d : one;
-        const float ab = fmaf(wx, b - a, a), cd = fmaf(wx, d - c, c);
-        t1 = fmaf(wy, cd - ab, ab);
-    }
-    return fmaf(wz, t1 - t0, t0);
+    const ZPart<SL> p = z_part<SL, NEAR>(F, z);
+    Tap<SDT, SL> t;
+    tap_load<SDT>(F, p, x, y, t);
+    const float2 v = tap_layers<SDT>(t);
+    return fmaf(p.w, v.y - v.x, v.x);
 }
 
 // --------------------------------------------------------------------------
@@ -222,90 +246,117 @@ constexpr int tap_batch()
     return (MODE == VI_MODE_CONE || (MODE == VI_MODE_SHELL && SDT == VI_F32)) ? 2 : 1;
 }
 
+// Nothing is scheduled across the end of a batch: the scheduler would issue
+// the next batches' loads ahead of it and take the registers of one or two
+// more waves a SIMD (point shell 122 VGPRs against 88).
+__device__ __forceinline__ void end_batch() { __builtin_amdgcn_sched_barrier(0); }
+
 template <int SDT, int SL, bool NEAR, int NB>
 __device__ __forceinline__ void lookup_batch(const RenderFrame& F, const float (&z)[NB], const float (&x)[NB],
                                              const float (&y)[NB], float (&out)[NB])
 {
-    if constexpr (SL == VI_STACK_ROWS) {
-        RowTap<SDT> t[NB];
+    Tap<SDT, SL> t[NB];
+    float w[NB];
 #pragma unroll
-        for (int u = 0; u < NB; ++u) rowtap_load<SDT, NEAR>(F, z[u], x[u], y[u], t[u]);
-#pragma unroll
-        for (int u = 0; u < NB; ++u) out[u] = rowtap_value<SDT>(t[u]);
-    } else {
-#pragma unroll
-        for (int u = 0; u < NB; ++u) out[u] = stack_lookup<SDT, SL, NEAR>(F, z[u], x[u], y[u]);
+    for (int u = 0; u < NB; ++u) {
+        const ZPart<SL> p = z_part<SL, NEAR>(F, z[u]);
+        w[u] = p.w;
+        tap_load<SDT>(F, p, x[u], y[u], t[u]);
     }
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+        const float2 v = tap_layers<SDT>(t[u]);
+        out[u] = fmaf(w[u], v.y - v.x, v.x);
+    }
+    end_batch();
+}
+
+// NB taps at one depth added to the two layers' sums.
+template <int SDT, int SL, int NB>
+__device__ __forceinline__ void add_taps(const RenderFrame& F, const ZPart<SL>& p, const float (&x)[NB],
+                                         const float (&y)[NB], float2& s)
+{
+    Tap<SDT, SL> t[NB];
+#pragma unroll
+    for (int u = 0; u < NB; ++u) tap_load<SDT>(F, p, x[u], y[u], t[u]);
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+        const float2 v = tap_layers<SDT>(t[u]);
+        s.x += v.x;
+        s.y += v.y;
+    }
+    end_batch();
 }
 
 template <int MODE, int SDT, int SL, bool NEAR>
 __device__ __forceinline__ float gather(const RenderFrame& F, const ConeFrame& cf, float z, float x, float y)
 {
     if (MODE == VI_MODE_SHADOW) return stack_lookup<SDT, SL, NEAR>(F, z, x, y);
-    // Taps go in batches; a batch running past the last tap repeats it and
-    // leaves the sum alone for the repeats, so every tap is added once, in
-    // order, as a one-at-a-time loop adds it.
     constexpr int NB = tap_batch<MODE, SDT>();
-    float zz[NB], xx[NB], yy[NB], v[NB];
     if (MODE == VI_MODE_SHELL) {
-        // weighted taps (shell r's six taps share w_r / (6 sum w))
-        float s = 0.0f;
-        for (int t = 0; t < F.ntaps; t += NB) {
+        // weighted taps (shell r's six taps share w_r / (6 sum w)); the six
+        // are unrolled so that one shell's offsets stay in scalar registers
+        float zz[NB], xx[NB], yy[NB], v[NB], s = 0.0f;
+        for (int t = 0; t < F.ntaps; t += 6) {
 #pragma unroll
-            for (int u = 0; u < NB; ++u) {
-                const int i = min(t + u, F.ntaps - 1);
-                zz[u] = z + F.tz[i];
-                xx[u] = x + F.tx_[i];
-                yy[u] = y + F.ty_[i];
+            for (int q = 0; q < 6; q += NB) {
+#pragma unroll
+                for (int u = 0; u < NB; ++u) {
+                    zz[u] = z + F.tz[t + q + u];
+                    xx[u] = x + F.tx_[t + q + u];
+                    yy[u] = y + F.ty_[t + q + u];
+                }
+                lookup_batch<SDT, SL, NEAR>(F, zz, xx, yy, v);
+#pragma unroll
+                for (int u = 0; u < NB; ++u) s = fmaf(F.tw[t + q + u], v[u], s);
             }
-            lookup_batch<SDT, SL, NEAR>(F, zz, xx, yy, v);
-#pragma unroll
-            for (int u = 0; u < NB; ++u)
-                if (t + u < F.ntaps) s = fmaf(F.tw[t + u], v[u], s);
         }
         return s;
     }
-    // cone: rings (Eq. 11), or the lattice form in a kernel of its own
-    float s = 0.0f;
+    // Cone: the taps of a ring, and of the whole lattice, lie at one depth, so
+    // their bilinear values are summed per layer and the depth weight is
+    // applied to the sums.
     if (MODE == VI_MODE_CONE) {
+        // rings (Eq. 11)
+        float s = 0.0f;
         for (int m = 1; m <= F.cone_rings; ++m) {
             const float r = (float)m * F.ds * F.cone_tan;
-            for (int q = 0; q < F.cone_angles; q += NB) {
-#pragma unroll
-                for (int u = 0; u < NB; ++u) {
-                    const int i = min(q + u, F.cone_angles - 1);
-                    const float ca = F.cone_cos[i] * r, sa = F.cone_sin[i] * r;
-                    zz[u] = z - (float)m;
-                    xx[u] = x + ca * cf.bx + sa * cf.px;
-                    yy[u] = y + ca * cf.by + sa * cf.py;
+            const float bx = r * cf.bx, by = r * cf.by, px = r * cf.px, py = r * cf.py;
+            const ZPart<SL> p = z_part<SL, NEAR>(F, z - (float)m);
+            float2 t = make_float2(0.0f, 0.0f);
+            if (F.cone_angles == 4) {
+                // a quarter turn apart: +-B and +-(L x B)
+                const float xb[2] = {x + bx, x - bx}, yb[2] = {y + by, y - by};
+                const float xp[2] = {x + px, x - px}, yp[2] = {y + py, y - py};
+                add_taps<SDT, SL>(F, p, xb, yb, t);
+                add_taps<SDT, SL>(F, p, xp, yp, t);
+            } else {
+                for (int q = 0; q < F.cone_angles; ++q) {
+                    const float ca = F.cone_cos[q], sa = F.cone_sin[q];
+                    const float xq[1] = {x + fmaf(ca, bx, sa * px)}, yq[1] = {y + fmaf(ca, by, sa * py)};
+                    add_taps<SDT, SL>(F, p, xq, yq, t);
                 }
-                lookup_batch<SDT, SL, NEAR>(F, zz, xx, yy, v);
-#pragma unroll
-                for (int u = 0; u < NB; ++u)
-                    if (q + u < F.cone_angles) s += v[u];
             }
+            s += fmaf(p.w, t.y - t.x, t.x);
         }
-    } else if (MODE == kModeConeGrid) {
-        const int G = F.cone_grid;
-        const float rho = F.ds * F.cone_tan * 0.5f, half = 0.5f * (float)(G - 1);
-        for (int ia = 0; ia < G; ++ia) {
-            const float a = ((float)ia - half) * rho;
-            for (int ib = 0; ib < G; ib += NB) {
-#pragma unroll
-                for (int u = 0; u < NB; ++u) {
-                    const float b = ((float)min(ib + u, G - 1) - half) * rho;
-                    zz[u] = z - 1.0f;
-                    xx[u] = x + a * cf.bx + b * cf.px;
-                    yy[u] = y + a * cf.by + b * cf.py;
-                }
-                lookup_batch<SDT, SL, NEAR>(F, zz, xx, yy, v);
-#pragma unroll
-                for (int u = 0; u < NB; ++u)
-                    if (ib + u < G) s += v[u];
-            }
+        return s * F.tap_w;
+    }
+    // lattice form, one slab toward the light (a kernel of its own)
+    const int G = F.cone_grid;
+    const float rho = F.ds * F.cone_tan * 0.5f, half = 0.5f * (float)(G - 1);
+    const float bx = rho * cf.bx, by = rho * cf.by, px = rho * cf.px, py = rho * cf.py;
+    const ZPart<SL> p = z_part<SL, NEAR>(F, z - 1.0f);
+    float2 t = make_float2(0.0f, 0.0f);
+    float a = -half;
+    for (int ia = 0; ia < G; ++ia, a += 1.0f) {
+        const float xa = fmaf(a, bx, x), ya = fmaf(a, by, y);
+        float b = -half;
+        for (int ib = 0; ib < G; ++ib, b += 1.0f) {
+            const float xq[1] = {fmaf(b, px, xa)}, yq[1] = {fmaf(b, py, ya)};
+            add_taps<SDT, SL>(F, p, xq, yq, t);
         }
     }
-    return s * F.tap_w;
+    return fmaf(p.w, t.y - t.x, t.x) * F.tap_w;
 }
 
 // Point light: the light grid is a frustum with its apex at P.  A lookup at
@@ -412,19 +463,21 @@ __device__ __forceinline__ float gather_point(const RenderFrame& F, float z, flo
     float s = 0.0f;
     constexpr int NB = tap_batch<MODE, SDT>();
     float zz[NB], xx[NB], yy[NB], val[NB];
-    for (int t = 0; t < F.ntaps; t += NB) {
+    for (int t = 0; t < F.ntaps; t += 6) {
 #pragma unroll
-        for (int q = 0; q < NB; ++q) {
-            const int i = min(t + q, F.ntaps - 1);
-            const float dt = d + F.td_[i], rd = __builtin_amdgcn_rcpf(dt);
-            zz[q] = z + F.tz[i];
-            xx[q] = frustum_col(F, u + F.tx_[i], rd, dt > 0.0f);
-            yy[q] = frustum_col(F, v + F.ty_[i], rd, dt > 0.0f);
+        for (int h = 0; h < 6; h += NB) {
+#pragma unroll
+            for (int q = 0; q < NB; ++q) {
+                const int i = t + h + q;
+                const float dt = d + F.td_[i], rd = __builtin_amdgcn_rcpf(dt);
+                zz[q] = z + F.tz[i];
+                xx[q] = frustum_col(F, u + F.tx_[i], rd, dt > 0.0f);
+                yy[q] = frustum_col(F, v + F.ty_[i], rd, dt > 0.0f);
+            }
+            lookup_batch<SDT, SL, NEAR>(F, zz, xx, yy, val);
+#pragma unroll
+            for (int q = 0; q < NB; ++q) s = fmaf(F.tw[t + h + q], val[q], s);
         }
-        lookup_batch<SDT, SL, NEAR>(F, zz, xx, yy, val);
-#pragma unroll
-        for (int q = 0; q < NB; ++q)
-            if (t + q < F.ntaps) s = fmaf(F.tw[t + q], val[q], s);
     }
     return s;
 }
@@ -1001,9 +1054,12 @@ __device__ __forceinline__ void render_tiles(const RenderFrame* __restrict__ fra
     shade_pixel<VT, LAYOUT, MODE, SDT, SL>(F, s_tf, s_next, s_bits, &gc, px, py);
 }
 
-// The kernels.  The float-stack shell's two-tap batches fit six waves per
-// SIMD (at most 80 VGPRs, no spills), which measured faster than the five
-// the compiler picks for them; the other cases keep the compiler's budget.
+// The kernels.  The shell's two-tap batches over a float row stack fit six
+// waves per SIMD (at most 80 VGPRs, no spills), which measured faster than
+// the five the compiler picks for them; the other cases keep the compiler's
+// budget (the tiled layout's lookups would spill).
+template <int SDT, int SL>
+constexpr bool kShellSixWaves = SDT == VI_F32 && SL == VI_STACK_ROWS;
 template <typename VT, int LAYOUT, int MODE, int SDT, int SL>
 __global__ __launch_bounds__(256) VI_RENDER_OCCUPANCY void render_kernel(RenderFrame F)
 {
@@ -1044,7 +1100,7 @@ static hipError_t launch_batch_t(int mode, const RenderFrame* d_frames, const ui
                            d_tiles, ntiles);
         break;
     case VI_MODE_SHELL:
-        if constexpr (SDT == VI_F32)
+        if constexpr (kShellSixWaves<SDT, SL>)
             hipLaunchKernelGGL((render_batch_kernel_shell<VT, LAYOUT, SDT, SL>), grid, block, lds, s, d_frames,
                                d_tiles, ntiles);
         else
@@ -1110,7 +1166,7 @@ static hipError_t launch_mode(const RenderFrame& f, hipStream_t s)
         hipLaunchKernelGGL((render_kernel<VT, LAYOUT, VI_MODE_SHADOW, SDT, SL>), grid, block, lds, s, f);
         break;
     case VI_MODE_SHELL:
-        if constexpr (SDT == VI_F32)
+        if constexpr (kShellSixWaves<SDT, SL>)
             hipLaunchKernelGGL((render_kernel_shell<VT, LAYOUT, SDT, SL>), grid, block, lds, s, f);
         else
             hipLaunchKernelGGL((render_kernel<VT, LAYOUT, VI_MODE_SHELL, SDT, SL>), grid, block, lds, s, f);
