@@ -647,6 +647,7 @@ int make_frame(const vi_volume* vol, const vi_tf* tf, const vi_slices* sl, const
     double Lq[3] = {0, 0, 0}, Ux[3] = {0, 0, 0}, Vy[3] = {0, 0, 0};  // per world unit
     if (reads_stack) {
         F.stack = sl->data;
+        F.stack_base = sl->data;
         F.stack_dtype = sl->dtype;
         F.n = sl->n;
         F.res = sl->res;
@@ -830,6 +831,41 @@ int make_frame(const vi_volume* vol, const vi_tf* tf, const vi_slices* sl, const
             F.ntaps = o.cone_rings * o.cone_angles;
         }
         F.tap_w = 1.0f / F.ntaps;
+    }
+    const int km = kernel_mode(F), wy = win_y(km), wz = reads_stack ? win_z(km, F.stack_dtype) : 0;
+    if (!point && F.stack_layout == VI_STACK_ROWS && !F.nearest && wz > 0) {
+        // how far the taps reach: texels to any side, layers below and above
+        const double texel = sl->res / (2.0 * sl->R) / Nd;  // texels per voxel
+        double reach = 0.0, zmin = 0.0, zmax = 0.0;
+        if (mode == VI_MODE_SHELL) {
+            for (int t = 0; t < F.ntaps; ++t) {
+                reach = fmax(reach, fmax(fabs((double)F.tx_[t]), fabs((double)F.ty_[t])));
+                zmax = fmax(zmax, fabs((double)F.tz[t]));
+            }
+            zmin = -zmax;
+        } else if (F.cone_grid > 0) {
+            reach = 0.5 * (F.cone_grid - 1) * F.ds * 0.5 * o.cone_tan * texel * sqrt(2.0);
+            zmin = zmax = -1.0;
+        } else {
+            reach = F.cone_rings * F.ds * o.cone_tan * texel;
+            zmin = -F.cone_rings;
+            zmax = -1.0;
+        }
+        // (1e-3: the taps' float rounding)
+        reach += 1e-3;
+        zmin -= 1e-3;
+        zmax += 1e-3;
+        const double room_z = wz - 1 - (zmax - zmin);
+        // the window must lie in the stored range, and leave room for the
+        // samples: two texels and a layer
+        if (F.rpitch >= (uint32_t)kWinX && F.res + 4 >= wy && F.n + 2 >= wz && 2.0 * reach + 2.0 <= wy - 1 &&
+            2.0 * reach + 2.0 <= kWinX - 4 && room_z >= 1.0) {
+            F.stage = 1;
+            F.st_reach = (float)reach;
+            F.st_zmin = (float)zmin;
+            F.st_zmax = (float)zmax;
+            F.st_oz = (int)floor(zmin - 0.5 * room_z + 0.5);
+        }
     }
     F.out = (float4*)d_rgba;
     F.samples = d_samples;

@@ -91,6 +91,7 @@ struct RenderFrame {
     int K;
     // stack
     const void* stack;
+    const void* stack_base;  // the buffer itself (rows: layer -1, row -2, column -2)
     // rows: the stack advanced by one row, one layer, and one layer and one
     // row, so that the four loads of a lookup share one offset
     const void* stack_r1;
@@ -104,6 +105,13 @@ struct RenderFrame {
     // clamps of light-grid coordinates that keep footprints on stored texels:
     // z in [-1 - Mz, n - 1 - Mz], x and y in [-2 - Mr, res - Mr]
     float zlo, zhi, xlo, xhi;
+    // rows, directional gathers: whether a wave may stage the stack texels
+    // its samples' taps can reach in LDS (see kStage), the taps' reach in
+    // texels and in layers below and above the sample, and the first layer
+    // of the window against the sample's
+    int stage;
+    float st_reach, st_zmin, st_zmax;
+    int st_oz;
     int stack_dtype;
     int n, res;
     int stack_layout;
@@ -197,6 +205,27 @@ inline int kernel_mode(const RenderFrame& f)
     if (f.point && f.mode == VI_MODE_CONE) return kModePointCone;
     if (f.mode == VI_MODE_CONE && f.cone_grid > 0) return kModeConeGrid;
     return f.mode;
+}
+
+// The stack window a wave stages in LDS for its gathers: kWinX columns (16
+// texels), win_y rows, win_z layers by kernel mode and stack type; 0 layers:
+// the gather reads the stack.  Staged are the 5 x 5 lattice's 25 taps, which
+// the L1 bounds (medium workload 1690 us a frame from the stack, 1160 from
+// windows), and the gathers of the 2-byte stacks, whose texels are then
+// converted once per window instead of once per tap (1024^3 cone frame with
+// a bfloat16 stack 2.5 -> 2.2 ms).  The float shell and ring cone read the
+// stack: VALU issue bounds them, and finding the window costs what its taps
+// save (large workload, window against stack: shell 1072 us against 951, cone
+// 1266 against 1210).  The sizes hold the taps of the 16 x 4 samples of a
+// step on images of about a pixel per voxel, and five workgroups' windows and
+// tables fit in a CU's LDS.
+constexpr int kWinX = 16;
+constexpr int win_y(int kmode) { return kmode == VI_MODE_SHELL ? 8 : 16; }
+constexpr int win_z(int kmode, int stack_dtype)
+{
+    if (kmode == kModeConeGrid) return 4;
+    if (stack_dtype == VI_F32) return 0;
+    return kmode == VI_MODE_SHELL ? 6 : kmode == VI_MODE_CONE ? 5 : 0;
 }
 
 // host helpers shared by the API and the server

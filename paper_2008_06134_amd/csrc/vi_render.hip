@@ -128,10 +128,14 @@ template <int SDT> struct Tap<SDT, VI_STACK_TILED> {
     float t0, t1;  // the layers' values
 };
 
-template <int SL, bool NEAR>
+// nearest-face lookups: never, always (copies of a gather behind one branch
+// that is uniform per frame), or a uniform branch per depth (the gather that
+// only serves what a window does not)
+enum class Near { kNo, kYes, kAsk };
+template <int SL, Near NEAR>
 __device__ __forceinline__ ZPart<SL> z_part(const RenderFrame& F, float z)
 {
-    if (NEAR) z = floorf(z + 0.5f);
+    if (NEAR == Near::kYes || (NEAR == Near::kAsk && F.nearest)) z = floorf(z + 0.5f);
     z = __builtin_amdgcn_fmed3f(z, F.zlo, F.zhi);
     const int iz = floor_int(z);
     ZPart<SL> p;
@@ -211,10 +215,61 @@ __device__ __forceinline__ float2 tap_layers(const Tap<SDT, VI_STACK_TILED>& t)
     return make_float2(t.t0, t.t1);
 }
 
+// Where a gather reads the stack: device memory, or the window of it that its
+// wave has staged in LDS (see stage_window).
+template <int SDT, int SL, Near NEAR>
+struct FromStack {
+    using Z = ZPart<SL>;
+    using T = Tap<SDT, SL>;
+    const RenderFrame& F;
+    __device__ __forceinline__ Z z_part(float z) const { return vi::z_part<SL, NEAR>(F, z); }
+    __device__ __forceinline__ void load(const Z& p, float x, float y, T& t) const { tap_load<SDT>(F, p, x, y, t); }
+    __device__ __forceinline__ float2 layers(const T& t) const { return tap_layers<SDT>(t); }
+};
+
+// The window holds kWinX x WY texels of WZ layers as floats, transmittance
+// whatever the stack's type.  Taps lie inside it (the fit test), so nothing
+// is clamped; the weights and values are those a read of the stack gives, bit
+// for bit.
+template <int WY>
+struct FromWindow {
+    struct Z {
+        int e;
+        float w;
+    };
+    struct T {
+        float a0, a1, a2, a3, b0, b1, b2, b3, wx, wy;
+    };
+    const float* tile;
+    int org;  // element of light-grid cell (0, 0, 0)
+    __device__ __forceinline__ Z z_part(float z) const
+    {
+        return Z{floor_int(z) * (kWinX * WY) + org, __builtin_amdgcn_fractf(z)};
+    }
+    __device__ __forceinline__ void load(const Z& p, float x, float y, T& t) const
+    {
+        const int ix = floor_int(x), iy = floor_int(y);
+        t.wx = __builtin_amdgcn_fractf(x);
+        t.wy = __builtin_amdgcn_fractf(y);
+        const float* q = tile + (iy * kWinX + ix + p.e);
+        t.a0 = q[0], t.a1 = q[1], t.a2 = q[kWinX], t.a3 = q[kWinX + 1];
+        q += kWinX * WY;
+        t.b0 = q[0], t.b1 = q[1], t.b2 = q[kWinX], t.b3 = q[kWinX + 1];
+    }
+    __device__ __forceinline__ float2 layers(const T& t) const
+    {
+        float ab = fmaf(t.wx, t.a1 - t.a0, t.a0), cd = fmaf(t.wx, t.a3 - t.a2, t.a2);
+        const float v0 = fmaf(t.wy, cd - ab, ab);
+        ab = fmaf(t.wx, t.b1 - t.b0, t.b0);
+        cd = fmaf(t.wx, t.b3 - t.b2, t.b2);
+        return make_float2(v0, fmaf(t.wy, cd - ab, ab));
+    }
+};
+
 // Transmittance at light-grid offset coordinates (z, x, y): depth between
 // faces (layer z and z+1 in stack order, layer -1 = 1), bilinear in the
 // layer, fully transmitting outside the texel grid.
-template <int SDT, int SL, bool NEAR>
+template <int SDT, int SL, Near NEAR>
 __device__ __forceinline__ float stack_lookup(const RenderFrame& F, float z, float x, float y)
 {
     const ZPart<SL> p = z_part<SL, NEAR>(F, z);
@@ -251,48 +306,53 @@ constexpr int tap_batch()
 // more waves a SIMD (point shell 122 VGPRs against 88).
 __device__ __forceinline__ void end_batch() { __builtin_amdgcn_sched_barrier(0); }
 
-template <int SDT, int SL, bool NEAR, int NB>
-__device__ __forceinline__ void lookup_batch(const RenderFrame& F, const float (&z)[NB], const float (&x)[NB],
+template <int NB, typename SRC>
+__device__ __forceinline__ void lookup_batch(const SRC& src, const float (&z)[NB], const float (&x)[NB],
                                              const float (&y)[NB], float (&out)[NB])
 {
-    Tap<SDT, SL> t[NB];
+    typename SRC::T t[NB];
     float w[NB];
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
-        const ZPart<SL> p = z_part<SL, NEAR>(F, z[u]);
+        const typename SRC::Z p = src.z_part(z[u]);
         w[u] = p.w;
-        tap_load<SDT>(F, p, x[u], y[u], t[u]);
+        src.load(p, x[u], y[u], t[u]);
     }
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
-        const float2 v = tap_layers<SDT>(t[u]);
+        const float2 v = src.layers(t[u]);
         out[u] = fmaf(w[u], v.y - v.x, v.x);
     }
     end_batch();
 }
 
 // NB taps at one depth added to the two layers' sums.
-template <int SDT, int SL, int NB>
-__device__ __forceinline__ void add_taps(const RenderFrame& F, const ZPart<SL>& p, const float (&x)[NB],
+template <int NB, typename SRC>
+__device__ __forceinline__ void add_taps(const SRC& src, const typename SRC::Z& p, const float (&x)[NB],
                                          const float (&y)[NB], float2& s)
 {
-    Tap<SDT, SL> t[NB];
+    typename SRC::T t[NB];
 #pragma unroll
-    for (int u = 0; u < NB; ++u) tap_load<SDT>(F, p, x[u], y[u], t[u]);
+    for (int u = 0; u < NB; ++u) src.load(p, x[u], y[u], t[u]);
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
-        const float2 v = tap_layers<SDT>(t[u]);
+        const float2 v = src.layers(t[u]);
         s.x += v.x;
         s.y += v.y;
     }
     end_batch();
 }
 
-template <int MODE, int SDT, int SL, bool NEAR>
-__device__ __forceinline__ float gather(const RenderFrame& F, const ConeFrame& cf, float z, float x, float y)
+template <int MODE, int NB, typename SRC>
+__device__ __forceinline__ float gather(const RenderFrame& F, const SRC& src, const ConeFrame& cf, float z, float x,
+                                        float y)
 {
-    if (MODE == VI_MODE_SHADOW) return stack_lookup<SDT, SL, NEAR>(F, z, x, y);
-    constexpr int NB = tap_batch<MODE, SDT>();
+    if (MODE == VI_MODE_SHADOW) {
+        const float zz[1] = {z}, xx[1] = {x}, yy[1] = {y};
+        float v[1];
+        lookup_batch<1>(src, zz, xx, yy, v);
+        return v[0];
+    }
     if (MODE == VI_MODE_SHELL) {
         // weighted taps (shell r's six taps share w_r / (6 sum w)); the six
         // are unrolled so that one shell's offsets stay in scalar registers
@@ -306,7 +366,7 @@ __device__ __forceinline__ float gather(const RenderFrame& F, const ConeFrame& c
                     xx[u] = x + F.tx_[t + q + u];
                     yy[u] = y + F.ty_[t + q + u];
                 }
-                lookup_batch<SDT, SL, NEAR>(F, zz, xx, yy, v);
+                lookup_batch<NB>(src, zz, xx, yy, v);
 #pragma unroll
                 for (int u = 0; u < NB; ++u) s = fmaf(F.tw[t + q + u], v[u], s);
             }
@@ -322,19 +382,19 @@ __device__ __forceinline__ float gather(const RenderFrame& F, const ConeFrame& c
         for (int m = 1; m <= F.cone_rings; ++m) {
             const float r = (float)m * F.ds * F.cone_tan;
             const float bx = r * cf.bx, by = r * cf.by, px = r * cf.px, py = r * cf.py;
-            const ZPart<SL> p = z_part<SL, NEAR>(F, z - (float)m);
+            const typename SRC::Z p = src.z_part(z - (float)m);
             float2 t = make_float2(0.0f, 0.0f);
             if (F.cone_angles == 4) {
                 // a quarter turn apart: +-B and +-(L x B)
                 const float xb[2] = {x + bx, x - bx}, yb[2] = {y + by, y - by};
                 const float xp[2] = {x + px, x - px}, yp[2] = {y + py, y - py};
-                add_taps<SDT, SL>(F, p, xb, yb, t);
-                add_taps<SDT, SL>(F, p, xp, yp, t);
+                add_taps<2>(src, p, xb, yb, t);
+                add_taps<2>(src, p, xp, yp, t);
             } else {
                 for (int q = 0; q < F.cone_angles; ++q) {
                     const float ca = F.cone_cos[q], sa = F.cone_sin[q];
                     const float xq[1] = {x + fmaf(ca, bx, sa * px)}, yq[1] = {y + fmaf(ca, by, sa * py)};
-                    add_taps<SDT, SL>(F, p, xq, yq, t);
+                    add_taps<1>(src, p, xq, yq, t);
                 }
             }
             s += fmaf(p.w, t.y - t.x, t.x);
@@ -345,7 +405,7 @@ __device__ __forceinline__ float gather(const RenderFrame& F, const ConeFrame& c
     const int G = F.cone_grid;
     const float rho = F.ds * F.cone_tan * 0.5f, half = 0.5f * (float)(G - 1);
     const float bx = rho * cf.bx, by = rho * cf.by, px = rho * cf.px, py = rho * cf.py;
-    const ZPart<SL> p = z_part<SL, NEAR>(F, z - 1.0f);
+    const typename SRC::Z p = src.z_part(z - 1.0f);
     float2 t = make_float2(0.0f, 0.0f);
     float a = -half;
     for (int ia = 0; ia < G; ++ia, a += 1.0f) {
@@ -353,7 +413,7 @@ __device__ __forceinline__ float gather(const RenderFrame& F, const ConeFrame& c
         float b = -half;
         for (int ib = 0; ib < G; ++ib, b += 1.0f) {
             const float xq[1] = {fmaf(b, px, xa)}, yq[1] = {fmaf(b, py, ya)};
-            add_taps<SDT, SL>(F, p, xq, yq, t);
+            add_taps<1>(src, p, xq, yq, t);
         }
     }
     return fmaf(p.w, t.y - t.x, t.x) * F.tap_w;
@@ -381,7 +441,7 @@ __device__ __forceinline__ float frustum_col(const RenderFrame& F, float u, floa
 // tan phi / 2.  The tap's slab index moves with its depth: c slabs, plus
 // the depth part of the lateral offset.  Taps are summed in the order rings
 // (or lattice rows), then angles (or columns), in batches as in gather().
-template <int SDT, int SL, bool NEAR>
+template <int SDT, int SL, Near NEAR>
 __device__ __forceinline__ float gather_point_cone(const RenderFrame& F, float z, float d, float u, float v, float wd,
                                                    float wu, float wv)
 {
@@ -424,7 +484,7 @@ __device__ __forceinline__ float gather_point_cone(const RenderFrame& F, float z
                     const int i = min(t + w, F.cone_angles - 1);
                     tap(c, F.cone_cos[i] * r, F.cone_sin[i] * r, zz[w], xx[w], yy[w]);
                 }
-                lookup_batch<SDT, SL, NEAR>(F, zz, xx, yy, val);
+                lookup_batch<NB>(FromStack<SDT, SL, NEAR>{F}, zz, xx, yy, val);
 #pragma unroll
                 for (int w = 0; w < NB; ++w)
                     if (t + w < F.cone_angles) s += val[w];
@@ -439,7 +499,7 @@ __device__ __forceinline__ float gather_point_cone(const RenderFrame& F, float z
 #pragma unroll
                 for (int w = 0; w < NB; ++w)
                     tap(1.0f, a, ((float)min(ib + w, G - 1) - half) * rho, zz[w], xx[w], yy[w]);
-                lookup_batch<SDT, SL, NEAR>(F, zz, xx, yy, val);
+                lookup_batch<NB>(FromStack<SDT, SL, NEAR>{F}, zz, xx, yy, val);
 #pragma unroll
                 for (int w = 0; w < NB; ++w)
                     if (ib + w < G) s += val[w];
@@ -449,7 +509,7 @@ __device__ __forceinline__ float gather_point_cone(const RenderFrame& F, float z
     return s * F.tap_w;
 }
 
-template <int MODE, int SDT, int SL, bool NEAR>
+template <int MODE, int SDT, int SL, Near NEAR>
 __device__ __forceinline__ float gather_point(const RenderFrame& F, float z, float d, float u, float v, float wd,
                                               float wu, float wv)
 {
@@ -474,7 +534,7 @@ __device__ __forceinline__ float gather_point(const RenderFrame& F, float z, flo
                 xx[q] = frustum_col(F, u + F.tx_[i], rd, dt > 0.0f);
                 yy[q] = frustum_col(F, v + F.ty_[i], rd, dt > 0.0f);
             }
-            lookup_batch<SDT, SL, NEAR>(F, zz, xx, yy, val);
+            lookup_batch<NB>(FromStack<SDT, SL, NEAR>{F}, zz, xx, yy, val);
 #pragma unroll
             for (int q = 0; q < NB; ++q) s = fmaf(F.tw[t + h + q], val[q], s);
         }
@@ -731,21 +791,199 @@ __device__ __forceinline__ bool ray_setup(const RenderFrame& F, int px, int py, 
     return true;
 }
 
-// One step of four segments of the ray's march (the lanes of its quad take
-// one segment each); true once the ray is done.
+// Stage the window of the stack that the taps of the wave's `lit` samples (at
+// light-grid position z, x, y) can reach in the wave's LDS tile; returns
+// whether this lane's taps lie in it, and the tile element of light-grid cell
+// (0, 0, 0).  Called with every lane of the wave.
+//
+// What bounds a gather of device memory is the L1: the 64 lanes of a load
+// touch about 22 lines, one tag look-up each, and a cone's 32 loads took 79 %
+// of the L1's cycles of a frame.  The samples of a step, 4 x 4 pixels by four
+// segments, lie within a few texels, so the window that holds all their taps
+// is read with a few 16-byte loads straight into LDS (one for every 16 rows
+// of 16 texels), and the taps are LDS reads with immediate offsets and no
+// clamps.  The window is centred between the first and the last lit sample;
+// samples whose taps do not fit it (rays that see different depths) read the
+// stack, and so does a wave with few samples.
+constexpr int kStageMin = 12;  // samples
+template <int MODE, int SDT, int SL>
+constexpr bool kStaged = SL == VI_STACK_ROWS && win_z(MODE, SDT) > 0;
+template <int MODE, int SDT>
+__device__ __forceinline__ bool stage_window(const RenderFrame& F, float* __restrict__ tile, bool lit, float z, float x,
+                                             float y, int& org)
+{
+    constexpr int WY = win_y(MODE), WZ = win_z(MODE, SDT);
+    constexpr int kLoads = WY * WZ / 16, kStep = 16 / WY;  // loads of 16 rows; layers per load
+    static_assert(WY * WZ % 16 == 0 && 16 % WY == 0, "a load covers whole layers");
+    const unsigned long long m = __ballot(lit);
+    if (__popcll(m) < kStageMin) return false;
+    // the window's first column, row and layer as stored (border and leading
+    // layer included); columns on 16 bytes
+    const int first = __ffsll(m) - 1, last = 63 - __clzll(m);
+    const int ix = floor_int(x), iy = floor_int(y), iz = floor_int(z);
+    const int mx = (__builtin_amdgcn_readlane(ix, first) + __builtin_amdgcn_readlane(ix, last)) >> 1;
+    const int my = (__builtin_amdgcn_readlane(iy, first) + __builtin_amdgcn_readlane(iy, last)) >> 1;
+    const int mz = (__builtin_amdgcn_readlane(iz, first) + __builtin_amdgcn_readlane(iz, last)) >> 1;
+    const int wx = min(max((mx + F.Mr - 3) & ~3, 0), (int)F.rpitch - kWinX);
+    const int wy = min(max(my + F.Mr + 2 - (WY / 2 - 1), 0), F.res + 4 - WY);
+    const int wz = min(max(mz + F.Mz + 1 + F.st_oz, 0), F.n + 2 - WZ);
+    // the same in light-grid coordinates, and the samples that fit
+    const int ox = wx - 2 - F.Mr, oy = wy - 2 - F.Mr, oz = wz - 1 - F.Mz;
+    const float hx = 0.5f * (float)(kWinX - 1), hy = 0.5f * (float)(WY - 1);
+    const bool fit = lit & (fabsf(x - ((float)ox + hx)) < hx - F.st_reach) &
+                     (fabsf(y - ((float)oy + hy)) < hy - F.st_reach) & (z + F.st_zmin >= (float)oz) &
+                     (z + F.st_zmax < (float)(oz + WZ - 1));
+    if (__popcll(__ballot(fit)) < kStageMin) return false;
+    org = -((oz * WY + oy) * kWinX + ox);
+    // row r of a load is row r % WY of layer r / WY; four lanes a row
+    const uint32_t lane = threadIdx.x & 63u, r = lane >> 2;
+    const uint32_t e0 = (uint32_t)wz * F.rlayer + (uint32_t)wy * F.rpitch + (uint32_t)wx;
+    const uint32_t el = (r / WY) * F.rlayer + (r % WY) * F.rpitch + (lane & 3u) * 4u;
+    // (this wave's reads of the last window have returned)
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if constexpr (SDT == VI_F32) {
+        const char* base = (const char*)F.stack_base + ((size_t)e0 << 2);
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) {
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(base + (el << 2)),
+                                             (__attribute__((address_space(3))) void*)(tile + i * 256), 16, 0, 0);
+            base += (size_t)(kStep * F.rlayer) << 2;
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    } else {
+        const char* base = (const char*)F.stack_base + ((size_t)e0 << 1);
+        uint2 raw[kLoads];
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) {
+            raw[i] = *(const uint2*)(base + (el << 1));
+            base += (size_t)(kStep * F.rlayer) << 1;
+        }
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) {
+            const float2 u = pair_value(PairRaw<SDT>{raw[i].x}), v = pair_value(PairRaw<SDT>{raw[i].y});
+            ((float4*)tile)[i * 64 + lane] = make_float4(u.x, u.y, v.x, v.y);
+        }
+        // one wave writes and reads its tile: the LDS keeps its accesses in
+        // order, only the compiler must
+        asm volatile("" ::: "memory");
+    }
+    return fit;
+}
+
+// Composite the four segments of a step of every live ray (opacity 1 - om,
+// colour er, eg, eb at distance sm), lit by the coefficient.
 template <typename VT, int LAYOUT, int MODE, int SDT, int SL>
-__device__ __forceinline__ bool ray_step(const RenderFrame& F, const float4* __restrict__ s_tf,
-                                         const int* __restrict__ s_next, const uint32_t* __restrict__ s_bits,
-                                         RayState& S, uint32_t& nop)
+__device__ __forceinline__ void ray_shade(const RenderFrame& F, float* __restrict__ tile, RayState& S, bool live,
+                                          bool in, float om, float er, float eg, float eb, float sm, float hx, float hy,
+                                          float hz, uint32_t& nop)
 {
     const int g = threadIdx.x & 3;
     constexpr bool PT = is_point_gather(MODE);
     constexpr bool PTP = MODE == kModePointPhong, PHONG = MODE == VI_MODE_PHONG || PTP;
+    [[maybe_unused]] const VT* __restrict__ vol = (const VT*)F.vol;
+    [[maybe_unused]] const VolIndex VI_ = {1u, F.vsy, F.vsz};
+    // front to back over the four segments of this step (Eq. 3 in product
+    // form): a segment is composited while the transmittance in front of it
+    // is above term_eps, and the ray's transmittance becomes the last
+    // composited segment's
+    const float incl = quad_scan_mul(om, g);  // prod_{h<=g} (1 - alpha_h)
+    const float up = quad_perm<0, 0, 1, 2>(incl);
+    const float before = g == 0 ? S.T : S.T * up, after = S.T * incl;
+    const bool seen = before > F.term_eps;
+    const float Tnew = quad_min(seen ? after : 2.0f);
+    const bool lit = seen && om < 1.0f;
+    if (live) S.T = Tnew;
+    // the taps of the wave's samples, staged in LDS where they lie close
+    bool staged = false;
+    [[maybe_unused]] FromWindow<win_y(MODE)> win{tile, 0};
+    [[maybe_unused]] float qz, qx, qy;
+    if constexpr (MODE != VI_MODE_NONE && !PHONG) {
+        qz = fmaf(sm, S.qdz, S.qz0), qx = fmaf(sm, S.qdx, S.qx0), qy = fmaf(sm, S.qdy, S.qy0);
+        if constexpr (kStaged<MODE, SDT, SL>)
+            if (F.stage) staged = stage_window<MODE, SDT>(F, tile, lit, qz, qx, qy, win.org);
+    }
+    if (lit) {
+        // emission alpha (sd rgb + ss) light: Eq. 7 with the coefficient A,
+        // or the local Phong terms
+        ++nop;
+        const float wgt = before * (1.0f - om);
+        float sd, ss = 0.0f;
+        if (PHONG) {
+            // central differences one voxel either side (exact
+            // offsets in voxel units)
+            const float gx = 0.5f * (sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.vlo, F.vhi, F.scale, hx + 1.f, hy, hz) -
+                                     sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.vlo, F.vhi, F.scale, hx - 1.f, hy, hz));
+            const float gy = 0.5f * (sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.vlo, F.vhi, F.scale, hx, hy + 1.f, hz) -
+                                     sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.vlo, F.vhi, F.scale, hx, hy - 1.f, hz));
+            const float gz = 0.5f * (sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.vlo, F.vhi, F.scale, hx, hy, hz + 1.f) -
+                                     sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.vlo, F.vhi, F.scale, hx, hy, hz - 1.f));
+            const float gn = sqrtf(fmaf(gx, gx, fmaf(gy, gy, gz * gz)));
+            const float inv = -1.0f / fmaxf(gn, F.grad_eps);  // n = -g / max(|g|, eps)
+            const float nx = gx * inv, ny = gy * inv, nz = gz * inv;
+            const float vx = S.vx, vy = S.vy, vz = S.vz;
+            float llx = S.lx, lly = S.ly, llz = S.lz, llv = S.lv;
+            if (PTP) {
+                // l = (P - p) / |P - p|
+                const float rx = fmaf(sm, -vx, llx), ry = fmaf(sm, -vy, lly), rz = fmaf(sm, -vz, llz);
+                const float ir = -__builtin_amdgcn_rsqf(fmaf(rx, rx, fmaf(ry, ry, rz * rz)));
+                llx = rx * ir;
+                lly = ry * ir;
+                llz = rz * ir;
+                llv = fmaf(llx, vx, fmaf(lly, vy, llz * vz));
+            }
+            const float nl = fmaf(nx, llx, fmaf(ny, lly, nz * llz));
+            const float nv = fmaf(nx, vx, fmaf(ny, vy, nz * vz));
+            const float nn = fmaf(nx, nx, fmaf(ny, ny, nz * nz));
+            const float rv = fmaf(2.0f * nl, nv, -nn * llv);  // r.v, r = 2(n.l)n - (n.n)l
+            sd = fmaf(F.phong_kd, fmaxf(nl, 0.0f), F.phong_ka);
+            if (rv > 0.0f) ss = F.phong_ks * fast_exp2(F.phong_shin * fast_log2(rv));
+        } else {
+            // (the nearest-face form is a second copy of the
+            // gather behind a branch that is uniform per frame)
+            float A = 1.0f;
+            if (PT) {
+                const float pd = fmaf(sm, S.pdd, S.pd0);
+                A = F.nearest ? gather_point<MODE, SDT, SL, Near::kYes>(F, qz, pd, qx, qy, -S.pdd, -S.qdx, -S.qdy)
+                              : gather_point<MODE, SDT, SL, Near::kNo>(F, qz, pd, qx, qy, -S.pdd, -S.qdx, -S.qdy);
+            } else if (MODE != VI_MODE_NONE) {
+                constexpr int NB = tap_batch<MODE, SDT>();
+                if constexpr (kStaged<MODE, SDT, SL>) {
+                    if (staged) A = gather<MODE, NB>(F, win, S.cf, qz, qx, qy);
+                    else A = gather<MODE, 1>(F, FromStack<SDT, SL, Near::kAsk>{F}, S.cf, qz, qx, qy);
+                } else {
+                    if (F.nearest) A = gather<MODE, NB>(F, FromStack<SDT, SL, Near::kYes>{F}, S.cf, qz, qx, qy);
+                    else A = gather<MODE, NB>(F, FromStack<SDT, SL, Near::kNo>{F}, S.cf, qz, qx, qy);
+                }
+            }
+            sd = fmaf(1.0f - F.ambient, A, F.ambient);
+        }
+        S.Cr = fmaf(wgt, fmaf(sd, er, ss), S.Cr);
+        S.Cg = fmaf(wgt, fmaf(sd, eg, ss), S.Cg);
+        S.Cb = fmaf(wgt, fmaf(sd, eb, ss), S.Cb);
+    }
+    if (live && S.T <= F.term_eps) {
+        // composited segments of the step: the quad's lanes that were seen
+        const unsigned long long m = __ballot(seen && in) >> (threadIdx.x & 60);
+        S.count = S.k + (float)__popc((uint32_t)m & 15u);
+    }
+}
+
+// One step of four segments of the march of every live ray of the wave (the
+// lanes of a ray's quad take one segment each); clears `live` once a ray is
+// done.  Where the gather stages windows the wave's lanes stay together
+// (finished rays' lanes take part in the staging); elsewhere a quad leaves
+// the loop with its ray.
+template <typename VT, int LAYOUT, int MODE, int SDT, int SL>
+__device__ __forceinline__ void ray_step(const RenderFrame& F, const float4* __restrict__ s_tf,
+                                         const int* __restrict__ s_next, const uint32_t* __restrict__ s_bits,
+                                         float* __restrict__ tile, RayState& S, bool& live, uint32_t& nop)
+{
+    const int g = threadIdx.x & 3;
     const VT* __restrict__ vol = (const VT*)F.vol;
     const VolIndex VI_ = {1u, F.vsy, F.vsz};
     const float Km1 = (float)(F.K - 1);
     const float kk = S.k + (float)g;
-    const bool in = kk < S.K;
+    const bool in = live && kk < S.K;
     float om = 1.f, sm = 0.f, hx = 0.f, hy = 0.f, hz = 0.f;  // om = 1 - alpha of the segment
     float er = 0.f, eg = 0.f, eb = 0.f;                      // its colour
     bool empty = true;
@@ -794,7 +1032,9 @@ __device__ __forceinline__ bool ray_step(const RenderFrame& F, const float4* __r
             eb = fmaf(w, tb.z - ta.z, ta.z);
         }
     }
-    if (quad_all(empty)) {
+    const bool jump = live && quad_all(empty);
+    float knext = S.k + 4.0f;
+    if (jump) {
         // Every segment of this step is empty (or past the exit): jump to
         // the last segment midpoint inside the empty box around the step's
         // last segment -- the segment's cell, or the cell's super-cell (4 x 4
@@ -827,80 +1067,12 @@ __device__ __forceinline__ bool ray_step(const RenderFrame& F, const float4* __r
             jl = fminf(floorf(fmaf(se, F.idt, -0.5f)), S.K - 1.0f);
         }
         const float jlast = quad_perm<3, 3, 3, 3>(jl);
-        S.k = fmaxf(S.k + 4.0f, 4.0f * floorf(0.25f * (jlast + 1.0f)));
-        return S.k >= S.K;
+        knext = fmaxf(knext, 4.0f * floorf(0.25f * (jlast + 1.0f)));
     }
-    // front to back over the four segments of this step (Eq. 3 in product
-    // form): a segment is composited while the transmittance in front of it
-    // is above term_eps, and the ray's transmittance becomes the last
-    // composited segment's
-    const float incl = quad_scan_mul(om, g);  // prod_{h<=g} (1 - alpha_h)
-    const float up = quad_perm<0, 0, 1, 2>(incl);
-    const float before = g == 0 ? S.T : S.T * up, after = S.T * incl;
-    const bool seen = before > F.term_eps;
-    S.T = quad_min(seen ? after : 2.0f);
-    if (seen && om < 1.0f) {
-        // emission alpha (sd rgb + ss) light: Eq. 7 with the coefficient A,
-        // or the local Phong terms
-        ++nop;
-        const float wgt = before * (1.0f - om);
-        float sd, ss = 0.0f;
-        if (PHONG) {
-            // central differences one voxel either side (exact
-            // offsets in voxel units)
-            const float gx = 0.5f * (sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.vlo, F.vhi, F.scale, hx + 1.f, hy, hz) -
-                                     sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.vlo, F.vhi, F.scale, hx - 1.f, hy, hz));
-            const float gy = 0.5f * (sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.vlo, F.vhi, F.scale, hx, hy + 1.f, hz) -
-                                     sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.vlo, F.vhi, F.scale, hx, hy - 1.f, hz));
-            const float gz = 0.5f * (sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.vlo, F.vhi, F.scale, hx, hy, hz + 1.f) -
-                                     sample_volume<VT, LAYOUT>(vol, VI_, F.N, F.M, F.vlo, F.vhi, F.scale, hx, hy, hz - 1.f));
-            const float gn = sqrtf(fmaf(gx, gx, fmaf(gy, gy, gz * gz)));
-            const float inv = -1.0f / fmaxf(gn, F.grad_eps);  // n = -g / max(|g|, eps)
-            const float nx = gx * inv, ny = gy * inv, nz = gz * inv;
-            const float vx = S.vx, vy = S.vy, vz = S.vz;
-            float llx = S.lx, lly = S.ly, llz = S.lz, llv = S.lv;
-            if (PTP) {
-                // l = (P - p) / |P - p|
-                const float rx = fmaf(sm, -vx, llx), ry = fmaf(sm, -vy, lly), rz = fmaf(sm, -vz, llz);
-                const float ir = -__builtin_amdgcn_rsqf(fmaf(rx, rx, fmaf(ry, ry, rz * rz)));
-                llx = rx * ir;
-                lly = ry * ir;
-                llz = rz * ir;
-                llv = fmaf(llx, vx, fmaf(lly, vy, llz * vz));
-            }
-            const float nl = fmaf(nx, llx, fmaf(ny, lly, nz * llz));
-            const float nv = fmaf(nx, vx, fmaf(ny, vy, nz * vz));
-            const float nn = fmaf(nx, nx, fmaf(ny, ny, nz * nz));
-            const float rv = fmaf(2.0f * nl, nv, -nn * llv);  // r.v, r = 2(n.l)n - (n.n)l
-            sd = fmaf(F.phong_kd, fmaxf(nl, 0.0f), F.phong_ka);
-            if (rv > 0.0f) ss = F.phong_ks * fast_exp2(F.phong_shin * fast_log2(rv));
-        } else {
-            // (the nearest-face form is a second copy of the
-            // gather behind a branch that is uniform per frame)
-            float A = 1.0f;
-            const float qz = fmaf(sm, S.qdz, S.qz0), qx = fmaf(sm, S.qdx, S.qx0), qy = fmaf(sm, S.qdy, S.qy0);
-            if (PT) {
-                const float pd = fmaf(sm, S.pdd, S.pd0);
-                A = F.nearest ? gather_point<MODE, SDT, SL, true>(F, qz, pd, qx, qy, -S.pdd, -S.qdx, -S.qdy)
-                              : gather_point<MODE, SDT, SL, false>(F, qz, pd, qx, qy, -S.pdd, -S.qdx, -S.qdy);
-            } else if (MODE != VI_MODE_NONE) {
-                A = F.nearest ? gather<MODE, SDT, SL, true>(F, S.cf, qz, qx, qy)
-                              : gather<MODE, SDT, SL, false>(F, S.cf, qz, qx, qy);
-            }
-            sd = fmaf(1.0f - F.ambient, A, F.ambient);
-        }
-        S.Cr = fmaf(wgt, fmaf(sd, er, ss), S.Cr);
-        S.Cg = fmaf(wgt, fmaf(sd, eg, ss), S.Cg);
-        S.Cb = fmaf(wgt, fmaf(sd, eb, ss), S.Cb);
-    }
-    if (S.T <= F.term_eps) {
-        // composited segments of the step: the quad's lanes that were seen
-        const unsigned long long m = __ballot(seen && in) >> (threadIdx.x & 60);
-        S.count = S.k + (float)__popc((uint32_t)m & 15u);
-        return true;
-    }
-    S.k += 4.0f;
-    return S.k >= S.K;
+    if (kStaged<MODE, SDT, SL> ? __any(live && !jump) : !jump)
+        ray_shade<VT, LAYOUT, MODE, SDT, SL>(F, tile, S, live, in, om, er, eg, eb, sm, hx, hy, hz, nop);
+    S.k = knext;
+    if (S.T <= F.term_eps || S.k >= S.K) live = false;
 }
 
 // The finished ray's colour over the background, and its segment count.
@@ -914,13 +1086,17 @@ __device__ __forceinline__ float4 ray_result(const RenderFrame& F, const RayStat
 template <typename VT, int LAYOUT, int MODE, int SDT, int SL>
 __device__ __forceinline__ float4 render_ray(const RenderFrame& F, const float4* __restrict__ s_tf,
                                              const int* __restrict__ s_next, const uint32_t* __restrict__ s_bits,
-                                             int px, int py, uint32_t& nsamp, uint32_t& nop)
+                                             float* __restrict__ tile, bool inside, int px, int py, uint32_t& nsamp,
+                                             uint32_t& nop)
 {
-    RayState S;
-    if (!ray_setup<VT, LAYOUT, MODE, SDT, SL>(F, px, py, S))
-        return make_float4(F.bg[0], F.bg[1], F.bg[2], F.bg[3]);
-    while (!ray_step<VT, LAYOUT, MODE, SDT, SL>(F, s_tf, s_next, s_bits, S, nop)) {
-    }
+    RayState S = {};
+    S.T = 1.0f;
+    bool live = false;
+    if (inside) live = ray_setup<VT, LAYOUT, MODE, SDT, SL>(F, px, py, S);
+    const bool hit = live;
+    while (kStaged<MODE, SDT, SL> ? __any(live) : live)
+        ray_step<VT, LAYOUT, MODE, SDT, SL>(F, s_tf, s_next, s_bits, tile, S, live, nop);
+    if (!hit) return make_float4(F.bg[0], F.bg[1], F.bg[2], F.bg[3]);
     if ((threadIdx.x & 3) == 0) nsamp += (uint32_t)fminf(S.count, S.K);
     return ray_result(F, S);
 }
@@ -929,13 +1105,6 @@ __device__ __forceinline__ float4 render_ray(const RenderFrame& F, const float4*
 // lane -> pixel mapping: kG lanes per ray; a wave covers WX x WY pixels, a
 // workgroup 2 x 2 waves = BX x BY pixels.
 // --------------------------------------------------------------------------
-// optional lower bound on resident waves per SIMD for the render kernels
-// (caps their registers)
-#ifdef VI_RENDER_WAVES
-#define VI_RENDER_OCCUPANCY __attribute__((amdgpu_waves_per_eu(VI_RENDER_WAVES)))
-#else
-#define VI_RENDER_OCCUPANCY
-#endif
 constexpr int kG = 4;  // lanes per ray: a DPP quad
 constexpr int kWX = 4, kWY = 4;
 constexpr int kBX = 2 * kWX, kBY = 2 * kWY;
@@ -983,16 +1152,33 @@ __device__ __forceinline__ void group_count_add(const RenderFrame& F, GroupCount
     }
 }
 
+// LDS of a workgroup: K table entries, K next-opaque indices, the occupancy
+// bits, then (16-byte aligned) its four waves' stack windows.
+__host__ __device__ inline size_t table_bytes(int K, uint32_t occ_words)
+{
+    return ((sizeof(float4) + sizeof(int)) * (size_t)K + sizeof(uint32_t) * (size_t)occ_words + 15) / 16 * 16;
+}
+constexpr size_t window_bytes(int kmode, int stack_dtype, int SL)
+{
+    return SL == VI_STACK_ROWS ? sizeof(float) * 4 * kWinX * win_y(kmode) * win_z(kmode, stack_dtype) : 0;
+}
+__device__ __forceinline__ float* window_of(const RenderFrame& F, char* lds)
+{
+    return (float*)(lds + table_bytes(F.K, F.occ.words + F.occ.swords));
+}
+
 template <typename VT, int LAYOUT, int MODE, int SDT, int SL>
-__device__ __forceinline__ void shade_pixel(const RenderFrame& F, const float4* s_tf, const int* s_next,
+__device__ __forceinline__ void shade_pixel(const RenderFrame& F, float4* s_tf, const int* s_next,
                                             const uint32_t* s_bits, GroupCount* gc, int px, int py)
 {
     uint32_t ns = 0, nop = 0;
     const int lane = threadIdx.x & 63;
-    if (px < F.width && py < F.height) {
-        const float4 c = render_ray<VT, LAYOUT, MODE, SDT, SL>(F, s_tf, s_next, s_bits, px, py, ns, nop);
-        if (lane % kG == 0) F.out[(size_t)py * F.width + px] = c;
-    }
+    // each wave's stack window lies behind the tables
+    float* tile = window_of(F, (char*)s_tf) +
+                  __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * (kWinX * win_y(MODE) * win_z(MODE, SDT));
+    const bool inside = px < F.width && py < F.height;
+    const float4 c = render_ray<VT, LAYOUT, MODE, SDT, SL>(F, s_tf, s_next, s_bits, tile, inside, px, py, ns, nop);
+    if (inside && lane % kG == 0) F.out[(size_t)py * F.width + px] = c;
     group_count_add(F, gc, ns, nop);
 }
 
@@ -1054,41 +1240,35 @@ __device__ __forceinline__ void render_tiles(const RenderFrame* __restrict__ fra
     shade_pixel<VT, LAYOUT, MODE, SDT, SL>(F, s_tf, s_next, s_bits, &gc, px, py);
 }
 
-// The kernels.  The shell's two-tap batches over a float row stack fit six
-// waves per SIMD (at most 80 VGPRs, no spills), which measured faster than
-// the five the compiler picks for them; the other cases keep the compiler's
-// budget (the tiled layout's lookups would spill).
-template <int SDT, int SL>
-constexpr bool kShellSixWaves = SDT == VI_F32 && SL == VI_STACK_ROWS;
+// The kernels, one per mode.  Over a float row stack the shell, the ring cone
+// and the lattice are held to six waves per SIMD (80 VGPRs, no spills): the
+// lattice 1155 -> 1094 us, the cone 1208 -> 1195; over the other row stacks
+// and modes to five (point cone 737 -> 722 us; six spill, 785).  The tiled
+// layout's lookups keep the compiler's four (1010 us for the default-argument
+// frame; five 1031, six 1083).
+template <int MODE, int SDT, int SL>
+constexpr int kMinWaves = SL != VI_STACK_ROWS ? 1
+                          : SDT == VI_F32 && (MODE == VI_MODE_SHELL || MODE == VI_MODE_CONE || MODE == kModeConeGrid)
+                              ? 6
+                              : 5;
 template <typename VT, int LAYOUT, int MODE, int SDT, int SL>
-__global__ __launch_bounds__(256) VI_RENDER_OCCUPANCY void render_kernel(RenderFrame F)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMinWaves<MODE, SDT, SL>))) void render_kernel(
+    RenderFrame F)
 {
     render_frame<VT, LAYOUT, MODE, SDT, SL>(F);
 }
-template <typename VT, int LAYOUT, int SDT, int SL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void render_kernel_shell(RenderFrame F)
-{
-    render_frame<VT, LAYOUT, VI_MODE_SHELL, SDT, SL>(F);
-}
 template <typename VT, int LAYOUT, int MODE, int SDT, int SL>
-__global__ __launch_bounds__(256) VI_RENDER_OCCUPANCY void render_batch_kernel(const RenderFrame* __restrict__ frames,
-                                                                               const uint32_t* __restrict__ tiles,
-                                                                               uint32_t ntiles)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMinWaves<MODE, SDT, SL>))) void
+render_batch_kernel(const RenderFrame* __restrict__ frames, const uint32_t* __restrict__ tiles, uint32_t ntiles)
 {
     render_tiles<VT, LAYOUT, MODE, SDT, SL>(frames, tiles, ntiles);
-}
-template <typename VT, int LAYOUT, int SDT, int SL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void render_batch_kernel_shell(
-    const RenderFrame* __restrict__ frames, const uint32_t* __restrict__ tiles, uint32_t ntiles)
-{
-    render_tiles<VT, LAYOUT, VI_MODE_SHELL, SDT, SL>(frames, tiles, ntiles);
 }
 
 template <typename VT, int LAYOUT, int SDT, int SL>
 static hipError_t launch_batch_t(int mode, const RenderFrame* d_frames, const uint32_t* d_tiles, uint32_t ntiles,
                                  int maxK, uint32_t occ_words, hipStream_t s)
 {
-    const size_t lds = (sizeof(float4) + sizeof(int)) * (size_t)maxK + sizeof(uint32_t) * (size_t)occ_words;
+    const size_t lds = table_bytes(maxK, occ_words) + window_bytes(mode, SDT, SL);
     const dim3 grid(list_grid(ntiles * kSub)), block(256);
     switch (mode) {
     case VI_MODE_NONE:
@@ -1100,12 +1280,8 @@ static hipError_t launch_batch_t(int mode, const RenderFrame* d_frames, const ui
                            d_tiles, ntiles);
         break;
     case VI_MODE_SHELL:
-        if constexpr (kShellSixWaves<SDT, SL>)
-            hipLaunchKernelGGL((render_batch_kernel_shell<VT, LAYOUT, SDT, SL>), grid, block, lds, s, d_frames,
-                               d_tiles, ntiles);
-        else
-            hipLaunchKernelGGL((render_batch_kernel<VT, LAYOUT, VI_MODE_SHELL, SDT, SL>), grid, block, lds, s,
-                               d_frames, d_tiles, ntiles);
+        hipLaunchKernelGGL((render_batch_kernel<VT, LAYOUT, VI_MODE_SHELL, SDT, SL>), grid, block, lds, s, d_frames,
+                           d_tiles, ntiles);
         break;
     case VI_MODE_CONE:
         hipLaunchKernelGGL((render_batch_kernel<VT, LAYOUT, VI_MODE_CONE, SDT, SL>), grid, block, lds, s, d_frames,
@@ -1156,8 +1332,7 @@ template <typename VT, int LAYOUT, int SDT, int SL>
 static hipError_t launch_mode(const RenderFrame& f, hipStream_t s)
 {
     dim3 grid(supertile_grid((f.width + kBX - 1) / kBX, (f.height + kBY - 1) / kBY)), block(256);
-    const size_t lds =
-        (sizeof(float4) + sizeof(int)) * (size_t)f.K + (f.occ.bits ? sizeof(uint32_t) * (f.occ.words + f.occ.swords) : 0);
+    const size_t lds = table_bytes(f.K, f.occ.words + f.occ.swords) + window_bytes(kernel_mode(f), SDT, SL);
     switch (kernel_mode(f)) {
     case VI_MODE_NONE:
         hipLaunchKernelGGL((render_kernel<VT, LAYOUT, VI_MODE_NONE, SDT, SL>), grid, block, lds, s, f);
@@ -1166,10 +1341,7 @@ static hipError_t launch_mode(const RenderFrame& f, hipStream_t s)
         hipLaunchKernelGGL((render_kernel<VT, LAYOUT, VI_MODE_SHADOW, SDT, SL>), grid, block, lds, s, f);
         break;
     case VI_MODE_SHELL:
-        if constexpr (kShellSixWaves<SDT, SL>)
-            hipLaunchKernelGGL((render_kernel_shell<VT, LAYOUT, SDT, SL>), grid, block, lds, s, f);
-        else
-            hipLaunchKernelGGL((render_kernel<VT, LAYOUT, VI_MODE_SHELL, SDT, SL>), grid, block, lds, s, f);
+        hipLaunchKernelGGL((render_kernel<VT, LAYOUT, VI_MODE_SHELL, SDT, SL>), grid, block, lds, s, f);
         break;
     case VI_MODE_CONE:
         hipLaunchKernelGGL((render_kernel<VT, LAYOUT, VI_MODE_CONE, SDT, SL>), grid, block, lds, s, f);
