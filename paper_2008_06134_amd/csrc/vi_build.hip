@@ -5,8 +5,8 @@
 // midpoint, the transfer-function opacity is looked up and corrected to the
 // slab thickness (extinction form, Eq. 6), and the running transmittance is
 // multiplied by (1 - alpha) -- Eq. 4 applied to opacity.  Every layer is
-// written within a few slabs of being known (the row layout holds the layers
-// of four slab pairs in LDS before storing them), so the pass is one
+// written within a few slabs of being known (the row layout holds eight
+// layers in LDS before storing them), so the pass is one
 // streaming sweep: the volume is read through the caches and the stack is
 // written once.
 //
@@ -15,13 +15,13 @@
 // layout a run is a stretch of the layer's element range, border included
 // (build_rows); in the tiled layout a run of one stack row (build_tiled).
 // At every slab a workgroup stores its run as one contiguous stretch of the
-// layer (4 KiB for 1024 float texels); many short runs spread over the layer
+// layer (up to 4 KiB); many short runs spread over the layer
 // (64 x 4 texel tiles per workgroup) measured at half that write rate.  The
 // 64 lanes of a wave hold 64 neighbouring columns (of at most two rows), so
 // each volume gather of a wave stays compact.
 //
 // Per column the slabs whose midpoints lie in the cube form one interval
-// [k_in, k_out], found once by exact integer division; a wave runs the full
+// [k_in, k_out], found once, exactly; a wave runs the full
 // per-slab work (fetch, transfer function, Eq. 6 correction, product) only
 // for slabs in its columns' union of intervals, and otherwise only stores
 // (the unattenuated value in front, the final transmittance behind).
@@ -69,13 +69,9 @@ __device__ __forceinline__ float q_frac(int64_t H)
 }
 __device__ __forceinline__ float q_to_float(int64_t H) { return (float)H * (1.0f / 1099511627776.0f); }
 
-// (NT, C, B): threads per workgroup, columns per lane, slabs per batch;
-// a lane's C columns are NT apart (CONSEC = 0: each store instruction of a
+// Tiled layout, (C, B): columns per lane, slabs per batch; a lane's C columns are NT apart (CONSEC = 0: each store instruction of a
 // wave covers 64 neighbouring texels) or adjacent (CONSEC = 1: one
 // C-element store per lane)
-#ifndef VI_BUILD_NT
-#define VI_BUILD_NT 1024
-#endif
 #ifndef VI_BUILD_C
 #define VI_BUILD_C 1
 #endif
@@ -85,47 +81,47 @@ __device__ __forceinline__ float q_to_float(int64_t H) { return (float)H * (1.0f
 #ifndef VI_BUILD_CONSEC
 #define VI_BUILD_CONSEC 0
 #endif
-// row layout: pairs of slabs per LDS exchange (one barrier each)
-#ifndef VI_BUILD_EXCH
-#define VI_BUILD_EXCH 4
-#endif
-constexpr int kBuildNT = VI_BUILD_NT, kBuildC = VI_BUILD_C, kBuildB = VI_BUILD_BATCH;
+constexpr int kBuildC = VI_BUILD_C, kBuildB = VI_BUILD_BATCH;
 constexpr bool kBuildConsec = VI_BUILD_CONSEC != 0;
-constexpr int kBuildExch = VI_BUILD_EXCH;
-constexpr int kRowsX = 2;  // exchange rows per slab pair: both of its layers
 
 // The slabs of a column whose midpoints lie in the cube: k in [k_in, k_out]
 // (empty when k_in > k_out), exactly as the per-slab test lo <= h_k <= hi
 // on all three axes decides it: per axis a half-line or interval of k from
 // an exact integer division of Q40 values.
-__device__ __forceinline__ int64_t floor_div(int64_t a, int64_t b)
+// floor(a / b) for b > 0, as far as it lies in [-1, n] (otherwise some value
+// beyond that end): an estimate in float, within 2^-21 (n + 1) of the quotient
+// clamped to [-1, n], corrected by the exact remainder.  (A 64-bit division is
+// some hundred instructions, and a column takes six.)
+__device__ __forceinline__ int floor_div(int64_t a, int64_t b, int n)
 {
-    int64_t q = a / b;
-    if ((a % b != 0) && ((a < 0) != (b < 0))) --q;
-    return q;
+    const float q = __builtin_amdgcn_fmed3f((float)a * __builtin_amdgcn_rcpf((float)b), -1.0f, (float)n);
+    int k = (int)floorf(q);
+    const int64_t r = a - k * b;
+    if (r < 0) --k;
+    else if (r >= b) ++k;
+    return k;
 }
-__device__ __forceinline__ int64_t ceil_div(int64_t a, int64_t b) { return -floor_div(-a, b); }
 __device__ __forceinline__ void slab_range(const int64_t H[3], const int64_t A[3], int n, int64_t lo, int64_t hi,
                                            int* k_in, int* k_out)
 {
-    int64_t kl = 0, kh = n - 1;
+    int kl = 0, kh = n - 1;
     for (int a = 0; a < 3; ++a) {
         if (A[a] == 0) {
             if (H[a] < lo || H[a] > hi) kl = n;  // never inside along this axis
-        } else if (A[a] > 0) {
-            kl = max(kl, ceil_div(lo - H[a], A[a]));
-            kh = min(kh, floor_div(hi - H[a], A[a]));
         } else {
-            kl = max(kl, ceil_div(hi - H[a], A[a]));
-            kh = min(kh, floor_div(lo - H[a], A[a]));
+            // k A in [lo - H, hi - H]; for a step against the axis mirrored
+            const int64_t st = A[a] > 0 ? A[a] : -A[a];
+            const int64_t from = A[a] > 0 ? lo - H[a] : H[a] - hi, to = A[a] > 0 ? hi - H[a] : H[a] - lo;
+            kl = max(kl, floor_div(from + (st - 1), st, n));  // the ceiling
+            kh = min(kh, floor_div(to, st, n));
         }
     }
     if (kl > kh) {
         *k_in = n;
         *k_out = -1;
     } else {
-        *k_in = (int)kl;
-        *k_out = (int)kh;
+        *k_in = kl;
+        *k_out = kh;
     }
 }
 
@@ -182,6 +178,12 @@ __device__ __forceinline__ void keep_foot(const RawFoot<VT, LAYOUT>& r)
 #pragma unroll
         for (int i = 0; i < 8; ++i) keep_value(r.v[i]);
     }
+}
+
+// LDS of the tables (K alphas and `words` words of bits), up to 16 bytes.
+__host__ __device__ inline size_t build_table_bytes(int K, uint32_t words)
+{
+    return (sizeof(float) * (size_t)K + sizeof(uint32_t) * (size_t)words + 15) / 16 * 16;
 }
 
 // Shared set-up of both layouts: the TF's opacities and the occupancy bits
@@ -284,10 +286,10 @@ __device__ __forceinline__ void slab_step(const BuildParams& P, const float* s_a
 // batches of B slabs: positions and empty-space verdicts, then every volume
 // load of the batch, and only then the arithmetic and the stores -- one
 // wait per batch, with C * B footprints in flight.
-template <typename VT, int LAYOUT, int OUT_DTYPE, bool PT>
+template <typename VT, int LAYOUT, int OUT_DTYPE, bool PT, int NT>
 __device__ __forceinline__ void build_tiled(const BuildParams& P)
 {
-    constexpr int NT = kBuildNT, C = kBuildC, B = kBuildB;
+    constexpr int C = kBuildC, B = kBuildB;
     constexpr int CS = kBuildConsec ? 1 : NT;  // stride between a lane's columns
     extern __shared__ float s_alpha[];  // K alphas, then the occupancy bits
     uint32_t* s_bits = (uint32_t*)(s_alpha + P.K);
@@ -391,48 +393,87 @@ __device__ __forceinline__ void build_tiled(const BuildParams& P)
 // a buffer aligned to 128 bytes layers -1, 1, 3, ... then start on a line
 // and layers 0, 2, 4, ... half a line past one.
 //
-// The workgroup owns NT consecutive elements of a layer's run, one column
-// per lane, in every layer from the leading layer -1 to the trailing layer n
-// (a copy of layer n - 1); border and padding lanes store the fully
-// transmitting value without touching the volume.  It walks the slabs two at a time, in step
-// across the workgroup: layer k0 + 1 (on the line grid) is stored by the
-// lane that owns each element, layer k0 (half a line off) goes through LDS
-// rotated by half a line, so that every wave's store there starts on a line
-// too; only the two half-lines at the ends of the workgroup's run are
-// written in part.  (Stores straddling lines measured at half the write
-// rate.)  Both layers of E pairs wait in LDS for one barrier, which every
-// wave reaches the same number of times, and all their stores go out after
-// it (E = 4: a barrier per pair held the 2-byte stacks 8 % back): CDNA
-// counts loads and stores on one counter, so a wait for a pair's loads also
-// waits for every store issued before them, and with no store between the
-// batch's loads only its first pair pays for the previous batch's stores
-// (float 0.76 -> 0.73 ms together with the single wait per pair below).  A
-// wave with no slab inside the cube in a pair only stores.  (Issuing the
-// next pair's loads before this pair's stores measured 6-13 % slower: the
-// compiler then waited for every load at each pair.)
-template <typename VT, int LAYOUT, int OUT_DTYPE, bool PT>
+// The workgroup owns NT consecutive elements of a layer's run in every layer
+// from the leading layer -1 to the trailing layer n (a copy of layer n - 1),
+// one column a lane.  It scans kSlabs slabs at a time into LDS (border and
+// padding lanes the fully transmitting texel, without touching the volume), in
+// the stack's own type, and after one barrier its waves share out the rows of
+// that set and store them, 16 bytes a lane; in the layers half a line off the
+// rows are rotated by half a line, so that every store starts on a line there
+// too (stores straddling lines measured at half the write rate; only the two
+// half-lines at the ends of the stretch are written in part).  Two sets of LDS
+// rows in turn, so that one barrier a set keeps writes and reads apart; every
+// wave reaches it the same number of times.  A wave with no slab of the set
+// inside the cube only stores.
+//
+// CDNA counts loads and stores on one counter, so a wave that waits for its
+// volume loads also waits for the stores it issued before them: with no store
+// between a set's loads only its first wait pays for the previous set's
+// stores, of which a lane now has two.  (One element a lane and slab, each
+// with its address and LDS read, were half of the kernel's VALU instructions:
+// 512^3 u16 quads, 512 x 1024^2 float 712 us, now 681; bfloat16 520, now 478.
+// Waves that only store, two to four of sixteen, measured no faster, 732 us.)
+constexpr int kSlabs = 8;
+template <int OUT_DTYPE> struct OutElem { using T = uint16_t; };
+template <> struct OutElem<VI_F32> { using T = float; };
+template <int OUT_DTYPE>
+__device__ __forceinline__ typename OutElem<OUT_DTYPE>::T texel_of(float T, float tau)
+{
+    if constexpr (OUT_DTYPE == VI_F32) return T;
+    else if constexpr (OUT_DTYPE == VI_BF16) return f32_to_bf16(tau);
+    else return __half_as_ushort(__float2half_rn(fast_exp2(-tau)));
+}
+
+// One layer's stretch (or the part of it that lanes first, first + lanes, ...
+// hold), 16 bytes a lane: `row` is its LDS row, L = k + 1 its index as stored.
+// FILL: the fully transmitting texel instead of the row.
+template <int OUT_DTYPE, uint32_t NT, uint32_t LANES, bool FILL = false>
+__device__ __forceinline__ void store_layer(const BuildParams& P, uint32_t unit, uint32_t L, uint32_t lane,
+                                            const typename OutElem<OUT_DTYPE>::T* __restrict__ row)
+{
+    using OT = typename OutElem<OUT_DTYPE>::T;
+    constexpr uint32_t ES = sizeof(OT), CH = 16 / ES, HALF = 64 / ES;  // elements of a chunk, of half a line
+    constexpr uint32_t NC = NT / CH, NI = (NC + LANES - 1) / LANES;    // chunks of a stretch, stores of a lane
+    const uint32_t f0 = unit * NT, rot = (L & 1u) ? HALF : 0u;         // odd L: half a line off
+    char* base = (char*)P.out + ((size_t)L * P.rlayer + f0) * ES;
+    uint4 v[NI];
+    uint32_t el[NI];
+#pragma unroll
+    for (uint32_t i = 0; i < NI; ++i) {
+        // (lanes past the last chunk read the first and store nothing)
+        const uint32_t c = lane + LANES * i, e = (NC % LANES == 0 || c < NC ? c * CH : 0u) + rot;
+        el[i] = e < NT ? e : e - NT;
+        if (!FILL) v[i] = *(const uint4*)(row + el[i]);
+        else v[i].x = v[i].y = v[i].z = v[i].w = OUT_DTYPE == VI_F32 ? 0x3f800000u : OUT_DTYPE == VI_BF16 ? 0u : 0x3c003c00u;
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < NI; ++i)
+        if ((NC % LANES == 0 || lane + LANES * i < NC) && f0 + el[i] < P.rlayer) *(uint4*)(base + el[i] * ES) = v[i];
+}
+
+// NW waves a workgroup, D slabs' footprints in flight a lane.
+template <typename VT, int LAYOUT, int OUT_DTYPE, bool PT, int NW, int D>
 __device__ __forceinline__ void build_rows(const BuildParams& P)
 {
-    static_assert(kBuildC == 1 && !kBuildConsec, "the row-layout build runs one column per lane");
-    constexpr uint32_t NT = kBuildNT;
-    constexpr uint32_t HALF = OUT_DTYPE == VI_F32 ? 16u : 32u;  // half a 128-byte line, in elements
-    extern __shared__ float s_alpha[];  // K alphas, the occupancy bits, then two sets of 2E exchange rows of NT
+    using OT = typename OutElem<OUT_DTYPE>::T;
+    constexpr uint32_t NT = NW * 64u;
+    extern __shared__ __attribute__((aligned(16))) float s_alpha[];  // K alphas, the occupancy bits, two sets of rows
     uint32_t* s_bits = (uint32_t*)(s_alpha + P.K);
-    float* s_x = (float*)(s_bits + stage_build_tables(P, s_alpha, s_bits));
+    const uint32_t words = stage_build_tables(P, s_alpha, s_bits);
+    OT* s_x = (OT*)((char*)s_alpha + build_table_bytes(P.K, words));
     const bool use_bits = P.occ.bits != nullptr;
     const int cshift = use_bits ? P.occ.shift : 30;
     const uint32_t cnc = use_bits ? P.occ.nc : 1u;
     __syncthreads();
 
-    const uint32_t span = P.rlayer;
     uint32_t unit, one;
-    if (!row_run_of(blockIdx.x, (span + NT - 1) / NT, 1u, &unit, &one)) return;  // uniform per workgroup
+    if (!row_run_of(blockIdx.x, (P.rlayer + NT - 1) / NT, 1u, &unit, &one)) return;  // uniform per workgroup
+    const int wave = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // the leading layer -1 (face 0) transmits fully
+    if (wave == 0) store_layer<OUT_DTYPE, NT, 64, true>(P, unit, 0u, threadIdx.x, s_x);
     const uint32_t t = threadIdx.x, f = unit * NT + t;
-    // in layers half a line off, lane t stores the element of lane tr
-    const uint32_t tr = (t + HALF) % NT, fr = unit * NT + tr;
     const int i = (int)(f % P.rpitch) - 2, j = (int)(f / P.rpitch) - 2;
-    const bool col = f < span, col_r = fr < span;
-    const bool grid = col && i >= 0 && i < P.res && j >= 0 && j < P.res;
+    const bool grid = f < P.rlayer && i >= 0 && i < P.res && j >= 0 && j < P.res;
 
     int64_t H[3], A[3];
     float ex;
@@ -441,107 +482,161 @@ __device__ __forceinline__ void build_rows(const BuildParams& P)
     // the wave's slabs with any midpoint in the cube: [kmin, kmax]
     const int kmin = __builtin_amdgcn_readfirstlane(wave_min(kin));
     const int kmax = __builtin_amdgcn_readfirstlane(wave_max(kout));
-    const uint32_t layer = P.rlayer;
-    uint32_t at = layer + f, at_r = layer + fr;  // elements of layer 0
-
-    // the leading layer -1 (face 0) transmits fully
-    if (col) put_texel<OUT_DTYPE>(P.out, f, 1.0f, 0.0f);
 
     const VT* __restrict__ vol = (const VT*)P.vol;
     const VolIndex VI_ = {1u, P.vsy, P.vsz};
     const bool darken = P.darken > 0.0f;
     float T = 1.0f, tau = 0.0f;  // transmittance (float stack), optical depth (2-byte stacks)
-    // E pairs of slabs per exchange: their layers wait in 2E LDS rows and
-    // are stored after one barrier (two sets of rows in turn, so that one
-    // barrier per E pairs keeps writes and reads apart)
-    constexpr int E = kBuildExch;
-    for (int k0 = 0; k0 < P.n; k0 += 2 * E) {
-        float* xs = s_x + ((uint32_t)(k0 / (2 * E)) & 1u) * (kRowsX * E * NT);
+    OT* x = s_x + t;
+    for (int k0 = 0; k0 < P.n; k0 += kSlabs) {
+        if (k0 + kSlabs > kmin && k0 <= kmax) {  // uniform per wave
+#pragma unroll 1
+            for (int q = 0; q < kSlabs; q += D) {
+                SlabProbe sp[D];
+                bool any = false;
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const int kk = k0 + 2 * e;  // this pair: layers kk (half a line off) and kk + 1
-            if (kk >= P.n) break;       // uniform
-            float v0;                   // the value of layer kk: T or tau
-            if (kk + 1 >= kmin && kk <= kmax) {  // uniform per wave
-                SlabProbe sp[2];
-                RawFoot<VT, LAYOUT> raw[2];
+                for (int u = 0; u < D; ++u) {
+                    sp[u] = probe_slab(P, H[0], H[1], H[2], k0 + q + u, kin, kout, s_bits, cshift, cnc);
+                    any = any || sp[u].fetch;
+                    for (int a = 0; a < 3; ++a) H[a] += A[a];
+                }
+                OT* xq = x + q * NT;
+                if (__any(any)) {
+                    // Bricks and quads: every lane loads, the ones with nothing
+                    // to fetch the first voxel.  With loads that only some
+                    // lanes issue the compiler cannot count what is
+                    // outstanding, and keeps the registers of those that were
+                    // not across the loop (76 VGPRs against 45: one workgroup
+                    // of 1024 lanes a CU instead of two).  In a linear volume
+                    // the extra lines cost as much as that saves (512^3 with
+                    // a map: 1050 us against 992).
+                    RawFoot<VT, LAYOUT> raw[D];
+                    constexpr bool kAll = LAYOUT != VI_LAYOUT_LINEAR;
 #pragma unroll
-                for (int u = 0; u < 2; ++u)
-                    sp[u] = probe_slab(P, H[0] + (int64_t)u * A[0], H[1] + (int64_t)u * A[1],
-                                       H[2] + (int64_t)u * A[2], kk + u, kin, kout, s_bits, cshift, cnc);
+                    for (int u = 0; u < D; ++u) {
+                        const bool own = sp[u].fetch;
+                        if (kAll || own)
+                            foot_load_g<VT, LAYOUT>(raw[u], sp[u].wx, sp[u].wy, vol, VI_, P.N, own ? sp[u].gx : 0,
+                                                    own ? sp[u].gy : 0, own ? sp[u].gz : 0);
+                    }
+                    if (!kAll)
 #pragma unroll
-                for (int u = 0; u < 2; ++u)
-                    if (sp[u].fetch)
-                        foot_load_g<VT, LAYOUT>(raw[u], sp[u].wx, sp[u].wy, vol, VI_, P.N, sp[u].gx, sp[u].gy,
-                                                sp[u].gz);
-                keep_foot<VT, LAYOUT>(raw[0]);
-                keep_foot<VT, LAYOUT>(raw[1]);
-                if (sp[0].fetch) slab_step<VT, LAYOUT, OUT_DTYPE>(P, s_alpha, raw[0], sp[0], ex, darken, T, tau);
-                v0 = OUT_DTYPE == VI_F32 ? T : tau;
-                if (sp[1].fetch) slab_step<VT, LAYOUT, OUT_DTYPE>(P, s_alpha, raw[1], sp[1], ex, darken, T, tau);
-            } else {
-                v0 = OUT_DTYPE == VI_F32 ? T : tau;
+                        for (int u = 0; u < D; ++u) keep_foot<VT, LAYOUT>(raw[u]);
+#pragma unroll
+                    for (int u = 0; u < D; ++u) {
+                        if (sp[u].fetch)
+                            slab_step<VT, LAYOUT, OUT_DTYPE>(P, s_alpha, raw[u], sp[u], ex, darken, T, tau);
+                        xq[u * NT] = texel_of<OUT_DTYPE>(T, tau);
+                    }
+                } else {
+                    const OT v = texel_of<OUT_DTYPE>(T, tau);
+#pragma unroll
+                    for (int u = 0; u < D; ++u) xq[u * NT] = v;
+                }
             }
-            for (int a = 0; a < 3; ++a) H[a] += 2 * A[a];
-            xs[e * NT + t] = v0;                                 // layer kk
-            xs[(E + e) * NT + t] = OUT_DTYPE == VI_F32 ? T : tau;  // layer kk + 1
+        } else {
+            const OT v = texel_of<OUT_DTYPE>(T, tau);
+#pragma unroll
+            for (int q = 0; q < kSlabs; ++q) x[q * NT] = v;
+            for (int a = 0; a < 3; ++a) H[a] += kSlabs * A[a];
         }
         __syncthreads();
-        // the layers half a line off, rotated by half a line
+        // every wave stores its share of the set: whole rows, or a part of one
+        const OT* rows = x == s_x + t ? s_x : s_x + kSlabs * NT;
+        constexpr int W = NW > kSlabs ? NW / kSlabs : 1, RW = NW > kSlabs ? 1 : kSlabs / NW;  // waves a row, rows a wave
+        static_assert(NW % kSlabs == 0 || kSlabs % NW == 0, "a wave's share of a set");
+        uint32_t lane = threadIdx.x % (W * 64u);
+        // (opaque: what the stores derive from it would otherwise be kept in
+        // registers across the whole batch, a quarter of the budget)
+        asm volatile("" : "+v"(lane));
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-            if (k0 + 2 * e >= P.n) break;  // uniform
-            const float w = xs[e * NT + tr];
-            if (col_r) put_texel<OUT_DTYPE>(P.out, at_r, w, w);
-            at_r += 2 * layer;
-            // layer kk + 1, on the line grid: each lane its own element
-            const float o = xs[(E + e) * NT + t];
-            if (k0 + 2 * e + 1 < P.n && col) put_texel<OUT_DTYPE>(P.out, at + layer, o, o);
-            at += 2 * layer;
+        for (int r = 0; r < RW; ++r) {
+            const int q = wave / W * RW + r, k = k0 + q;
+            if (k < P.n) store_layer<OUT_DTYPE, NT, W * 64>(P, unit, (uint32_t)k + 1u, lane, rows + q * NT);
+            // the trailing layer n repeats layer n - 1
+            if (k == P.n - 1) store_layer<OUT_DTYPE, NT, W * 64>(P, unit, (uint32_t)k + 2u, lane, rows + q * NT);
         }
+        x = x == s_x + t ? x + kSlabs * NT : s_x + t;
     }
-    // the trailing layer n repeats layer n - 1
-    if (col) put_texel<OUT_DTYPE>(P.out, (uint32_t)(P.n + 1) * layer + f, T, tau);
 }
 
-template <typename VT, int LAYOUT, int OUT_DTYPE, int SL, bool PT>
-__global__ __launch_bounds__(kBuildNT) void build_kernel(BuildParams P)
+template <typename VT, int LAYOUT, int OUT_DTYPE, bool PT, int NW, int D>
+__global__ __launch_bounds__(NW * 64) void build_rows_kernel(BuildParams P)
 {
-    if constexpr (SL == VI_STACK_ROWS) build_rows<VT, LAYOUT, OUT_DTYPE, PT>(P);
-    else build_tiled<VT, LAYOUT, OUT_DTYPE, PT>(P);
+    build_rows<VT, LAYOUT, OUT_DTYPE, PT, NW, D>(P);
+}
+template <typename VT, int LAYOUT, int OUT_DTYPE, bool PT, int NT>
+__global__ __launch_bounds__(NT) void build_tiled_kernel(BuildParams P)
+{
+    build_tiled<VT, LAYOUT, OUT_DTYPE, PT, NT>(P);
 }
 
-template <typename VT, int LAYOUT, int SL, bool PT>
-static void launch_build_k(const BuildParams& p, dim3 grid, size_t lds, hipStream_t s)
+template <typename VT, int LAYOUT, int OUT_DTYPE, bool PT, int NW, int D>
+static hipError_t launch_rows(const BuildParams& p, hipStream_t s)
 {
-    if (p.out_dtype == VI_F32)
-        hipLaunchKernelGGL((build_kernel<VT, LAYOUT, VI_F32, SL, PT>), grid, dim3(kBuildNT), lds, s, p);
-    else if (p.out_dtype == VI_BF16)
-        hipLaunchKernelGGL((build_kernel<VT, LAYOUT, VI_BF16, SL, PT>), grid, dim3(kBuildNT), lds, s, p);
-    else if constexpr (SL == VI_STACK_ROWS)
-        hipLaunchKernelGGL((build_kernel<VT, LAYOUT, VI_F16, SL, PT>), grid, dim3(kBuildNT), lds, s, p);
+    constexpr uint32_t NT = NW * 64u;
+    // (at least one word of bits: without them word 0 says "occupied")
+    const size_t lds = build_table_bytes(p.K, std::max(p.occ.words + p.occ.swords, 1u)) +
+                       2 * kSlabs * NT * sizeof(typename OutElem<OUT_DTYPE>::T);
+    const dim3 grid(row_run_grid((p.rlayer + NT - 1) / NT, 1u));
+    hipLaunchKernelGGL((build_rows_kernel<VT, LAYOUT, OUT_DTYPE, PT, NW, D>), grid, dim3(NW * 64), lds, s, p);
+    return hipGetLastError();
+}
+
+template <typename VT, int LAYOUT, int OUT_DTYPE, bool PT, int NT>
+static hipError_t launch_tiled(const BuildParams& p, hipStream_t s)
+{
+    constexpr uint32_t per_group = (uint32_t)NT * kBuildC;
+    const size_t lds = build_table_bytes(p.K, std::max(p.occ.words + p.occ.swords, 1u));
+    const uint32_t runs = ((uint32_t)p.res + per_group - 1) / per_group;
+    hipLaunchKernelGGL((build_tiled_kernel<VT, LAYOUT, OUT_DTYPE, PT, NT>), dim3(row_run_grid((uint32_t)p.res, runs)),
+                       dim3(NT), lds, s, p);
+    return hipGetLastError();
+}
+
+template <typename VT, int LAYOUT, int OUT_DTYPE, bool PT>
+static hipError_t launch_build_k(const BuildParams& p, hipStream_t s)
+{
+    if (p.out_layout == VI_STACK_ROWS) {
+        // Two workgroups of 1024 lanes fit a CU, 512 of them the chip: up to
+        // about that many columns (600 K) every column is resident whatever
+        // the workgroup, the time is a column's chain of waits, and smaller
+        // workgroups, which spread evenly and leave registers for more loads
+        // in flight, are the faster; beyond it what counts is the write
+        // stream, which wants long stretches and every lane.  Measured (16
+        // waves with 2 slabs in flight | 8 with 4 | 4 with 4), u16 quads, us:
+        // 128^3 and 256^2 97 | 62 | 53, 192^3 and 384^2 115 | 86 | 75, 256^3
+        // and 512^2 167 | 130 | 132, 320^3 and 640^2 231 | 199 | 228, 384^3
+        // and 768^2 344 | 346 | 450, 512^3 and 1024^2 681 | 788 | 892.
+        // Footprints of eight loads (or of two of 16 bytes) keep two slabs in
+        // flight: 256^3 bricks 210 with 16 waves, 147 with 8; linear without
+        // a map 479 and 267; 512^3 bricks 754 and 884.
+        constexpr bool kLight = LAYOUT == VI_LAYOUT_QUAD4 && sizeof(VT) <= 2;
+        if (p.rlayer > 600000u) return launch_rows<VT, LAYOUT, OUT_DTYPE, PT, 16, 2>(p, s);
+        if constexpr (kLight) {
+            if (p.rlayer <= 160000u) return launch_rows<VT, LAYOUT, OUT_DTYPE, PT, 4, 4>(p, s);
+            return launch_rows<VT, LAYOUT, OUT_DTYPE, PT, 8, 4>(p, s);
+        }
+        return launch_rows<VT, LAYOUT, OUT_DTYPE, PT, 8, 2>(p, s);
+    }
+    if constexpr (OUT_DTYPE != VI_F16) {
+        // (a workgroup covers a stretch of one row of texels: 1024 lanes on a
+        // row of 256 left three in four idle)
+        if (p.res > 512) return launch_tiled<VT, LAYOUT, OUT_DTYPE, PT, 1024>(p, s);
+        return launch_tiled<VT, LAYOUT, OUT_DTYPE, PT, 256>(p, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 template <typename VT, int LAYOUT>
 static hipError_t launch_build_t(const BuildParams& p, hipStream_t s)
 {
-    constexpr uint32_t per_group = (uint32_t)kBuildNT * kBuildC;
-    // (at least one word of bits: without them word 0 says "occupied")
-    const size_t lds = sizeof(float) * (size_t)p.K + sizeof(uint32_t) * std::max(p.occ.words + p.occ.swords, 1u);
-    if (p.out_layout == VI_STACK_ROWS) {
-        // runs of a layer's element range, border and padding included; two
-        // sets of exchange rows of floats
-        const dim3 grid(row_run_grid((p.rlayer + per_group - 1) / per_group, 1u));
-        const size_t lds_rows = lds + 2 * sizeof(float) * (size_t)kRowsX * kBuildExch * kBuildNT;
-        if (p.point) launch_build_k<VT, LAYOUT, VI_STACK_ROWS, true>(p, grid, lds_rows, s);
-        else launch_build_k<VT, LAYOUT, VI_STACK_ROWS, false>(p, grid, lds_rows, s);
-    } else {
-        const uint32_t runs = ((uint32_t)p.res + per_group - 1) / per_group;
-        const dim3 grid(row_run_grid((uint32_t)p.res, runs));
-        if (p.point) launch_build_k<VT, LAYOUT, VI_STACK_TILED, true>(p, grid, lds, s);
-        else launch_build_k<VT, LAYOUT, VI_STACK_TILED, false>(p, grid, lds, s);
-    }
-    return hipGetLastError();
+    if (p.out_dtype == VI_F32)
+        return p.point ? launch_build_k<VT, LAYOUT, VI_F32, true>(p, s) : launch_build_k<VT, LAYOUT, VI_F32, false>(p, s);
+    if (p.out_dtype == VI_BF16)
+        return p.point ? launch_build_k<VT, LAYOUT, VI_BF16, true>(p, s)
+                       : launch_build_k<VT, LAYOUT, VI_BF16, false>(p, s);
+    return p.point ? launch_build_k<VT, LAYOUT, VI_F16, true>(p, s) : launch_build_k<VT, LAYOUT, VI_F16, false>(p, s);
 }
 
 template <typename VT>
