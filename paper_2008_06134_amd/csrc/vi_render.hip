@@ -784,10 +784,6 @@ __device__ __forceinline__ bool ray_setup(const RenderFrame& F, int px, int py, 
     jump_axis(S.hx0, hdx, S.ihx, S.jbx);
     jump_axis(S.hy0, hdy, S.ihy, S.jby);
     jump_axis(S.hz0, hdz, S.ihz, S.jbz);
-    S.last_cell = 0xffffffffu;
-    S.cell_is_empty = false;
-    S.k = 0.f;
-    S.count = S.K;
     return true;
 }
 
@@ -1083,23 +1079,24 @@ __device__ __forceinline__ float4 ray_result(const RenderFrame& F, const RayStat
                        fmaf(S.T, F.bg[3], 1.0f - S.T));
 }
 
-template <typename VT, int LAYOUT, int MODE, int SDT, int SL>
-__device__ __forceinline__ float4 render_ray(const RenderFrame& F, const float4* __restrict__ s_tf,
-                                             const int* __restrict__ s_next, const uint32_t* __restrict__ s_bits,
-                                             float* __restrict__ tile, bool inside, int px, int py, uint32_t& nsamp,
-                                             uint32_t& nop)
+// The per-ray values that the set-up hands to the march, in one order for
+// writing and reading.
+template <int MODE, typename FN>
+__device__ __forceinline__ void ray_fields(RayState& S, FN f)
 {
-    RayState S = {};
-    S.T = 1.0f;
-    bool live = false;
-    if (inside) live = ray_setup<VT, LAYOUT, MODE, SDT, SL>(F, px, py, S);
-    const bool hit = live;
-    while (kStaged<MODE, SDT, SL> ? __any(live) : live)
-        ray_step<VT, LAYOUT, MODE, SDT, SL>(F, s_tf, s_next, s_bits, tile, S, live, nop);
-    if (!hit) return make_float4(F.bg[0], F.bg[1], F.bg[2], F.bg[3]);
-    if ((threadIdx.x & 3) == 0) nsamp += (uint32_t)fminf(S.count, S.K);
-    return ray_result(F, S);
+    constexpr bool PHONG = MODE == VI_MODE_PHONG || MODE == kModePointPhong;
+    f(S.K), f(S.Df);
+    f(S.hx0), f(S.hy0), f(S.hz0), f(S.hdx), f(S.hdy), f(S.hdz);
+    f(S.ihx), f(S.ihy), f(S.ihz), f(S.jbx), f(S.jby), f(S.jbz);
+    if constexpr (PHONG) {
+        f(S.lx), f(S.ly), f(S.lz), f(S.lv);
+    } else if constexpr (MODE != VI_MODE_NONE) {
+        f(S.qz0), f(S.qx0), f(S.qy0), f(S.qdz), f(S.qdx), f(S.qdy);
+        if constexpr (is_point_gather(MODE)) f(S.pd0), f(S.pdd);
+        if constexpr (MODE == VI_MODE_CONE || MODE == kModeConeGrid) f(S.cf.bx), f(S.cf.by), f(S.cf.px), f(S.cf.py);
+    }
 }
+constexpr int kRayFields = 24;  // the most of any mode
 
 // --------------------------------------------------------------------------
 // lane -> pixel mapping: kG lanes per ray; a wave covers WX x WY pixels, a
@@ -1109,11 +1106,11 @@ constexpr int kG = 4;  // lanes per ray: a DPP quad
 constexpr int kWX = 4, kWY = 4;
 constexpr int kBX = 2 * kWX, kBY = 2 * kWY;
 
-__device__ __forceinline__ void block_pixel(uint32_t tx, uint32_t ty, int* px, int* py)
+// ray 0..63 of a workgroup, 16 a wave
+__device__ __forceinline__ void ray_pixel(int ray, int* px, int* py)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane / kG;
-    *px = (int)tx * kBX + (wave & 1) * kWX + r % kWX;
-    *py = (int)ty * kBY + (wave >> 1) * kWY + r / kWX;
+    *px += ((ray >> 4) & 1) * kWX + ray % kWX;
+    *py += (ray >> 5) * kWY + (ray & 15) / kWX;
 }
 
 // Segment counters: a wave sums its lanes' counts, the workgroup's waves add
@@ -1153,33 +1150,99 @@ __device__ __forceinline__ void group_count_add(const RenderFrame& F, GroupCount
 }
 
 // LDS of a workgroup: K table entries, K next-opaque indices, the occupancy
-// bits, then (16-byte aligned) its four waves' stack windows.
+// bits, then (16-byte aligned) its four waves' areas, each for its stack window
+// and, before the march, its rays.
 __host__ __device__ inline size_t table_bytes(int K, uint32_t occ_words)
 {
     return ((sizeof(float4) + sizeof(int)) * (size_t)K + sizeof(uint32_t) * (size_t)occ_words + 15) / 16 * 16;
 }
-constexpr size_t window_bytes(int kmode, int stack_dtype, int SL)
+constexpr size_t wave_words(int kmode, int stack_dtype, int SL)
 {
-    return SL == VI_STACK_ROWS ? sizeof(float) * 4 * kWinX * win_y(kmode) * win_z(kmode, stack_dtype) : 0;
+    const size_t w = SL == VI_STACK_ROWS ? kWinX * win_y(kmode) * win_z(kmode, stack_dtype) : 0;
+    return w > 16 * kRayFields ? w : 16 * kRayFields;
 }
-__device__ __forceinline__ float* window_of(const RenderFrame& F, char* lds)
+constexpr size_t wave_bytes(int kmode, int stack_dtype, int SL)
 {
-    return (float*)(lds + table_bytes(F.K, F.occ.words + F.occ.swords));
+    return 4 * sizeof(float) * wave_words(kmode, stack_dtype, SL);
 }
 
-template <typename VT, int LAYOUT, int MODE, int SDT, int SL>
-__device__ __forceinline__ void shade_pixel(const RenderFrame& F, float4* s_tf, const int* s_next,
-                                            const uint32_t* s_bits, GroupCount* gc, int px, int py)
+// `n` words from device memory to LDS, by the whole workgroup, without waiting
+// for them (loads straight into LDS, 64 consecutive words each).
+__device__ __forceinline__ void stage_words(const void* src, void* dst, uint32_t n)
 {
+    const uint32_t lane = threadIdx.x & 63u;
+    for (uint32_t at = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 64u; at < n; at += 256u)
+        if (at + lane < n)
+            __builtin_amdgcn_global_load_lds(
+                (const __attribute__((address_space(1))) void*)((const uint32_t*)src + at + lane),
+                (__attribute__((address_space(3))) void*)((uint32_t*)dst + at), 4, 0, 0);
+}
+
+// A workgroup's 8 x 8 pixels from (x0, y0).  While the tables are on their way
+// to LDS one of its waves sets up all 64 rays, one a lane, and leaves them in
+// the waves' areas; after the barrier the four lanes of a quad read their
+// ray.  (Every wave setting up its 16 rays with four lanes each did the same
+// work four times, a tenth of a frame's VALU instructions, after having waited
+// for the tables.)  The waves take turns at it by workgroup, so that no SIMD
+// gets all of it.
+template <typename VT, int LAYOUT, int MODE, int SDT, int SL>
+__device__ __forceinline__ void shade_block(const RenderFrame& F, float4* s_tf, int x0, int y0, uint32_t turn)
+{
+    __shared__ GroupCount gc;
+    group_count_init(&gc);
+    int* s_next = (int*)(s_tf + F.K);
+    uint32_t* s_bits = (uint32_t*)(s_next + F.K);
+    const uint32_t words = F.occ.words + F.occ.swords;
+    stage_words(F.tf, s_tf, 4u * (uint32_t)F.K);
+    if (F.occ.bits) stage_words(F.occ.bits, s_bits, words);
+    else if (F.occ.mm) build_next_opaque(s_next, F.tf, F.K);
+
+    constexpr uint32_t kWords = (uint32_t)wave_words(MODE, SDT, SL);
+    float* areas = (float*)((char*)s_tf + table_bytes(F.K, words));
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
+    RayState S = {};
+    if (wave == (turn & 3u)) {
+        int px = x0, py = y0;
+        ray_pixel((int)lane, &px, &py);
+        bool hit = px < F.width && py < F.height;
+        if (hit) hit = ray_setup<VT, LAYOUT, MODE, SDT, SL>(F, px, py, S);
+        if (!hit) S.K = 0.0f;
+        float* at = areas + (lane >> 4) * kWords + (lane & 15u);
+        int i = 0;
+        ray_fields<MODE>(S, [&](float& v) { at[16 * i++] = v; });
+    }
+    // (the words that this wave has on their way to LDS)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+
+    float* tile = areas + wave * kWords;  // this wave's rays, then its stack window
+    S = {};
+    {
+        const float* at = tile + (lane >> 2);
+        int i = 0;
+        ray_fields<MODE>(S, [&](float& v) { v = at[16 * i++]; });
+    }
+    S.vx = -S.hdx, S.vy = -S.hdy, S.vz = -S.hdz;
+    S.last_cell = 0xffffffffu;
+    S.T = 1.0f;
+    S.count = S.K;
+    const bool hit = S.K > 0.0f;
+    bool live = hit;
     uint32_t ns = 0, nop = 0;
-    const int lane = threadIdx.x & 63;
-    // each wave's stack window lies behind the tables
-    float* tile = window_of(F, (char*)s_tf) +
-                  __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * (kWinX * win_y(MODE) * win_z(MODE, SDT));
-    const bool inside = px < F.width && py < F.height;
-    const float4 c = render_ray<VT, LAYOUT, MODE, SDT, SL>(F, s_tf, s_next, s_bits, tile, inside, px, py, ns, nop);
-    if (inside && lane % kG == 0) F.out[(size_t)py * F.width + px] = c;
-    group_count_add(F, gc, ns, nop);
+    while (kStaged<MODE, SDT, SL> ? __any(live) : live)
+        ray_step<VT, LAYOUT, MODE, SDT, SL>(F, s_tf, s_next, s_bits, tile, S, live, nop);
+    int px = x0, py = y0;
+    ray_pixel((int)(threadIdx.x >> 2), &px, &py);
+    if (hit) {
+        const float4 c = ray_result(F, S);
+        if ((lane & 3u) == 0u) {
+            ns = (uint32_t)fminf(S.count, S.K);
+            F.out[(size_t)py * F.width + px] = c;
+        }
+    } else if (px < F.width && py < F.height && (lane & 3u) == 0u) {
+        F.out[(size_t)py * F.width + px] = make_float4(F.bg[0], F.bg[1], F.bg[2], F.bg[3]);
+    }
+    group_count_add(F, &gc, ns, nop);
 }
 
 // --------------------------------------------------------------------------
@@ -1188,30 +1251,18 @@ __device__ __forceinline__ void shade_pixel(const RenderFrame& F, float4* s_tf, 
 template <typename VT, int LAYOUT, int MODE, int SDT, int SL>
 __device__ __forceinline__ void render_frame(const RenderFrame& F)
 {
-    extern __shared__ float4 s_tf[];  // K entries, K next-opaque indices, then the occupancy bits
-    int* s_next = (int*)(s_tf + F.K);
-    uint32_t* s_bits = (uint32_t*)(s_next + F.K);
-    __shared__ GroupCount gc;
-    group_count_init(&gc);
-    for (int t = threadIdx.x; t < F.K; t += blockDim.x)
-        s_tf[t] = make_float4(F.tf[4 * t], F.tf[4 * t + 1], F.tf[4 * t + 2], F.tf[4 * t + 3]);
-    if (F.occ.mm && !F.occ.bits) build_next_opaque(s_next, F.tf, F.K);
-    stage_occupancy(F.occ, s_bits);
-    __syncthreads();
-
+    extern __shared__ float4 s_tf[];
     const uint32_t tiles_x = (F.width + kBX - 1) / kBX, tiles_y = (F.height + kBY - 1) / kBY;
     uint32_t tx, ty;
     if (!supertile_of(blockIdx.x, tiles_x, tiles_y, &tx, &ty)) return;
-    int px, py;
-    block_pixel(tx, ty, &px, &py);
-    shade_pixel<VT, LAYOUT, MODE, SDT, SL>(F, s_tf, s_next, s_bits, &gc, px, py);
+    shade_block<VT, LAYOUT, MODE, SDT, SL>(F, s_tf, (int)tx * kBX, (int)ty * kBY, blockIdx.x / kXcds);
 }
 
 // --------------------------------------------------------------------------
 // batched kernel (serving): the launch lists 16 x 16-pixel tiles of any frames
 // of one mode; each tile is covered by (16/BX) x (16/BY) workgroups, each
 // reading its frame's parameters from device memory.  Per pixel it runs the
-// same render_ray as render_kernel, so a frame is bit-identical alone and in a
+// same shade_block as render_kernel, so a frame is bit-identical alone and in a
 // mix.  (One kernel per mode keeps each mode's register budget: a kernel
 // holding every mode runs all of them at the occupancy of the largest.)
 // --------------------------------------------------------------------------
@@ -1226,18 +1277,8 @@ __device__ __forceinline__ void render_tiles(const RenderFrame* __restrict__ fra
     if (!list_of(blockIdx.x, ntiles * kSub, &q)) return;
     const uint32_t t = tiles[q / kSub], sub = q % kSub;
     const RenderFrame& F = frames[t >> 22];
-    int* s_next = (int*)(s_tf + F.K);
-    uint32_t* s_bits = (uint32_t*)(s_next + F.K);
-    __shared__ GroupCount gc;
-    group_count_init(&gc);
-    for (int i = threadIdx.x; i < F.K; i += blockDim.x)
-        s_tf[i] = make_float4(F.tf[4 * i], F.tf[4 * i + 1], F.tf[4 * i + 2], F.tf[4 * i + 3]);
-    if (F.occ.mm && !F.occ.bits) build_next_opaque(s_next, F.tf, F.K);
-    stage_occupancy(F.occ, s_bits);
-    __syncthreads();
-    int px, py;
-    block_pixel((t & 2047u) * kSubX + sub % kSubX, ((t >> 11) & 2047u) * kSubY + sub / kSubX, &px, &py);
-    shade_pixel<VT, LAYOUT, MODE, SDT, SL>(F, s_tf, s_next, s_bits, &gc, px, py);
+    shade_block<VT, LAYOUT, MODE, SDT, SL>(F, s_tf, (int)((t & 2047u) * kSubX + sub % kSubX) * kBX,
+                                           (int)(((t >> 11) & 2047u) * kSubY + sub / kSubX) * kBY, blockIdx.x / kXcds);
 }
 
 // The kernels, one per mode.  Over a float row stack the shell, the ring cone
@@ -1268,7 +1309,7 @@ template <typename VT, int LAYOUT, int SDT, int SL>
 static hipError_t launch_batch_t(int mode, const RenderFrame* d_frames, const uint32_t* d_tiles, uint32_t ntiles,
                                  int maxK, uint32_t occ_words, hipStream_t s)
 {
-    const size_t lds = table_bytes(maxK, occ_words) + window_bytes(mode, SDT, SL);
+    const size_t lds = table_bytes(maxK, occ_words) + wave_bytes(mode, SDT, SL);
     const dim3 grid(list_grid(ntiles * kSub)), block(256);
     switch (mode) {
     case VI_MODE_NONE:
@@ -1332,7 +1373,7 @@ template <typename VT, int LAYOUT, int SDT, int SL>
 static hipError_t launch_mode(const RenderFrame& f, hipStream_t s)
 {
     dim3 grid(supertile_grid((f.width + kBX - 1) / kBX, (f.height + kBY - 1) / kBY)), block(256);
-    const size_t lds = table_bytes(f.K, f.occ.words + f.occ.swords) + window_bytes(kernel_mode(f), SDT, SL);
+    const size_t lds = table_bytes(f.K, f.occ.words + f.occ.swords) + wave_bytes(kernel_mode(f), SDT, SL);
     switch (kernel_mode(f)) {
     case VI_MODE_NONE:
         hipLaunchKernelGGL((render_kernel<VT, LAYOUT, VI_MODE_NONE, SDT, SL>), grid, block, lds, s, f);
