@@ -174,6 +174,9 @@ __device__ __forceinline__ void keep_foot(const RawFoot<VT, LAYOUT>& r)
     if constexpr (LAYOUT == VI_LAYOUT_QUAD4) {
         keep_value(r.a);
         keep_value(r.b);
+    } else if constexpr (LAYOUT == VI_LAYOUT_LINEAR) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) keep_value(r.p[i]);
     } else {
 #pragma unroll
         for (int i = 0; i < 8; ++i) keep_value(r.v[i]);
@@ -508,8 +511,8 @@ __device__ __forceinline__ void build_rows(const BuildParams& P)
                     // outstanding, and keeps the registers of those that were
                     // not across the loop (76 VGPRs against 45: one workgroup
                     // of 1024 lanes a CU instead of two).  In a linear volume
-                    // the extra lines cost as much as that saves (512^3 with
-                    // a map: 1050 us against 992).
+                    // the extra lines cost more than that saves (320^3 without
+                    // a map 570 us against 529 with 8 waves).
                     RawFoot<VT, LAYOUT> raw[D];
                     constexpr bool kAll = LAYOUT != VI_LAYOUT_LINEAR;
 #pragma unroll
@@ -609,10 +612,15 @@ static hipError_t launch_build_k(const BuildParams& p, hipStream_t s)
         // and 512^2 167 | 130 | 132, 320^3 and 640^2 231 | 199 | 228, 384^3
         // and 768^2 344 | 346 | 450, 512^3 and 1024^2 681 | 788 | 892.
         // Footprints of eight loads (or of two of 16 bytes) keep two slabs in
-        // flight: 256^3 bricks 210 with 16 waves, 147 with 8; linear without
-        // a map 479 and 267; 512^3 bricks 754 and 884.
-        constexpr bool kLight = LAYOUT == VI_LAYOUT_QUAD4 && sizeof(VT) <= 2;
-        if (p.rlayer > 600000u) return launch_rows<VT, LAYOUT, OUT_DTYPE, PT, 16, 2>(p, s);
+        // flight: 256^3 bricks 210 with 16 waves, 147 with 8; 512^3 754 and
+        // 884.  Linear volumes, whose gathers touch the most lines, change
+        // over a little earlier, to four slabs in flight of 2-byte voxels:
+        // without a map, 320^3 and 640^2 529 with 8 waves, 707 with 16 and
+        // four slabs; 384^3 and 768^2 1197 and 1027; 512^3 2792 and 1876
+        // (2164 with two; float voxels 916 with two, 1089 with four).
+        constexpr bool kLinear = LAYOUT == VI_LAYOUT_LINEAR, kLight = LAYOUT == VI_LAYOUT_QUAD4 && sizeof(VT) <= 2;
+        if (p.rlayer > (kLinear ? 500000u : 600000u))
+            return launch_rows<VT, LAYOUT, OUT_DTYPE, PT, 16, kLinear && sizeof(VT) <= 2 ? 4 : 2>(p, s);
         if constexpr (kLight) {
             if (p.rlayer <= 160000u) return launch_rows<VT, LAYOUT, OUT_DTYPE, PT, 4, 4>(p, s);
             return launch_rows<VT, LAYOUT, OUT_DTYPE, PT, 8, 4>(p, s);

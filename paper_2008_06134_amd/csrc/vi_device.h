@@ -163,12 +163,62 @@ template <typename VT> struct QuadRaw { using T = uint2; };           // 16-bit 
 template <> struct QuadRaw<uint8_t> { using T = uint32_t; };
 template <> struct QuadRaw<float> { using T = float4; };
 template <typename VT, int LAYOUT> struct RawFoot { VT v[8]; };
+// Linear volumes: the two voxels of a row along x are adjacent in memory and
+// come with one load, aligned as its elements are (8 loads a footprint became
+// 4: the address units take a load of any width in the same time).  At the
+// last voxel the pair is the last two and `last` asks for its second.
+template <typename VT> struct Pair2 {
+    typedef uint32_t T __attribute__((aligned(2)));
+};
+template <> struct Pair2<uint8_t> {
+    typedef uint16_t T __attribute__((aligned(1)));
+};
+template <> struct Pair2<float> {
+    typedef uint64_t T __attribute__((aligned(4)));
+};
+template <typename VT> struct RawFoot<VT, VI_LAYOUT_LINEAR> {
+    decltype(typename Pair2<VT>::T() + 0) p[4];  // rows (y, z), (y+1, z), (y, z+1), (y+1, z+1)
+    bool last;
+};
 template <typename VT> struct RawFoot<VT, VI_LAYOUT_QUAD4> { typename QuadRaw<VT>::T a, b; };
 
 __device__ __forceinline__ float norm1(uint8_t x, float scale) { return clampf01((float)x * scale); }
 __device__ __forceinline__ float norm1(uint16_t x, float scale) { return clampf01((float)x * scale); }
 __device__ __forceinline__ float norm1(__half x, float scale) { return clampf01(__half2float(x) * scale); }
 __device__ __forceinline__ float norm1(float x, float scale) { return clampf01(x * scale); }
+
+// the two voxels of a loaded pair, normalised
+__device__ __forceinline__ float2 pair_decode(uint32_t w, float scale, uint8_t)
+{
+    return make_float2(norm1((uint8_t)w, scale), norm1((uint8_t)(w >> 8), scale));
+}
+__device__ __forceinline__ float2 pair_decode(uint32_t w, float scale, uint16_t)
+{
+    return make_float2(norm1((uint16_t)w, scale), norm1((uint16_t)(w >> 16), scale));
+}
+__device__ __forceinline__ float2 pair_decode(uint32_t w, float scale, __half)
+{
+    return make_float2(norm1(__ushort_as_half((unsigned short)w), scale),
+                       norm1(__ushort_as_half((unsigned short)(w >> 16)), scale));
+}
+__device__ __forceinline__ float2 pair_decode(uint64_t w, float scale, float)
+{
+    return make_float2(norm1(__uint_as_float((uint32_t)w), scale), norm1(__uint_as_float((uint32_t)(w >> 32)), scale));
+}
+// the loads of a linear footprint at rows za/zb (z), ya/yb (y), voxel x
+template <typename VT>
+__device__ __forceinline__ void load_pairs(RawFoot<VT, VI_LAYOUT_LINEAR>& r, const VT* __restrict__ vol, uint32_t za,
+                                           uint32_t zb, uint32_t ya, uint32_t yb, int x, int N)
+{
+    using P = typename Pair2<VT>::T;
+    const auto at = [&](uint32_t e) { return *(const P*)((const char*)vol + e * (uint32_t)sizeof(VT)); };
+    const uint32_t xa = (uint32_t)min(x, N - 2);
+    r.last = x > N - 2;
+    r.p[0] = at(za + ya + xa);
+    r.p[1] = at(za + yb + xa);
+    r.p[2] = at(zb + ya + xa);
+    r.p[3] = at(zb + yb + xa);
+}
 
 __device__ __forceinline__ float4 quad_decode(uint32_t w, float scale, uint8_t)
 {
@@ -209,6 +259,10 @@ __device__ __forceinline__ void foot_load_g(RawFoot<VT, LAYOUT>& r, float& wx, f
         r.b = ((const Q*)vol)[zb + xy];
         if (x0 < 0) wx = 0.0f;
         if (y0 < 0) wy = 0.0f;
+    } else if constexpr (LAYOUT == VI_LAYOUT_LINEAR) {
+        const uint32_t ya = vol_oy<LAYOUT>(I, clampi(y0, 0, N - 1)), yb = vol_oy<LAYOUT>(I, clampi(y0 + 1, 0, N - 1));
+        load_pairs<VT>(r, vol, za, zb, ya, yb, max(x0, 0), N);
+        if (x0 < 0) wx = 0.0f;  // both corners clamp to voxel 0
     } else {
         const uint32_t xa = vol_ox<LAYOUT>(I, clampi(x0, 0, N - 1)), xb = vol_ox<LAYOUT>(I, clampi(x0 + 1, 0, N - 1));
         const uint32_t ya = vol_oy<LAYOUT>(I, clampi(y0, 0, N - 1)), yb = vol_oy<LAYOUT>(I, clampi(y0 + 1, 0, N - 1));
@@ -230,6 +284,11 @@ __device__ __forceinline__ float foot_value(const RawFoot<VT, LAYOUT>& r, float 
     if constexpr (LAYOUT == VI_LAYOUT_QUAD4) {
         a = quad_decode(r.a, scale, VT());
         b = quad_decode(r.b, scale, VT());
+    } else if constexpr (LAYOUT == VI_LAYOUT_LINEAR) {
+        const float2 p0 = pair_decode(r.p[0], scale, VT()), p1 = pair_decode(r.p[1], scale, VT());
+        const float2 p2 = pair_decode(r.p[2], scale, VT()), p3 = pair_decode(r.p[3], scale, VT());
+        a = make_float4(r.last ? p0.y : p0.x, p0.y, r.last ? p1.y : p1.x, p1.y);
+        b = make_float4(r.last ? p2.y : p2.x, p2.y, r.last ? p3.y : p3.x, p3.y);
     } else {
         a = make_float4(norm1(r.v[0], scale), norm1(r.v[1], scale), norm1(r.v[2], scale), norm1(r.v[3], scale));
         b = make_float4(norm1(r.v[4], scale), norm1(r.v[5], scale), norm1(r.v[6], scale), norm1(r.v[7], scale));
@@ -271,6 +330,8 @@ __device__ __forceinline__ float sample_volume(const VT* __restrict__ vol, const
         const uint32_t xy = vol_ox<LAYOUT>(I, x0) + vol_oy<LAYOUT>(I, y0);
         r.a = ((const Q*)vol)[za + xy];  // (may pass 4 GiB: 64-bit addressing)
         r.b = ((const Q*)vol)[zb + xy];
+    } else if constexpr (LAYOUT == VI_LAYOUT_LINEAR) {
+        load_pairs<VT>(r, vol, za, zb, vol_oy<LAYOUT>(I, y0), vol_oy<LAYOUT>(I, min(y0 + 1, N - 1)), x0, N);
     } else {
         const uint32_t xa = vol_ox<LAYOUT>(I, x0), xb = vol_ox<LAYOUT>(I, min(x0 + 1, N - 1));
         const uint32_t ya = vol_oy<LAYOUT>(I, y0), yb = vol_oy<LAYOUT>(I, min(y0 + 1, N - 1));

@@ -29,8 +29,8 @@ def _volume(kind):
 
 
 # (slabs, res): a layer holds (res + 4)^2 texels and a little more, against
-# 160 000 and 600 000; 512 and 513 change the tiled build's shape
-SIZES = [(1, 1), (7, 5), (8, 61), (9, 130), (17, 395), (5, 397), (3, 512), (4, 513), (9, 769), (10, 772)]
+# 160 000, 500 000 (linear) and 600 000; 512 and 513 change the tiled build's shape
+SIZES = [(1, 1), (7, 5), (8, 61), (9, 130), (17, 395), (5, 397), (3, 512), (4, 513), (6, 703), (7, 704), (9, 769), (10, 772)]
 
 
 @pytest.mark.parametrize("kind", ["u8 quads", "u16 bricks", "f32 quads", "f16 linear"])
