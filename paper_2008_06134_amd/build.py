@@ -37,7 +37,7 @@ def hipcc() -> str:
 
 def flags() -> list:
     # VI_BUILD_DEFINES: extra -D options for experiments with the kernels'
-    # compile-time switches (e.g. "-DVI_RENDER_COMPACT=1"); empty by default
+    # compile-time switches; empty by default
     extra = os.environ.get("VI_BUILD_DEFINES", "").split()
     if any(not e.startswith("-D") for e in extra):
         raise RuntimeError("VI_BUILD_DEFINES takes -D options only")

@@ -214,11 +214,14 @@ inline int kernel_mode(const RenderFrame& f)
 // windows), and the gathers of the 2-byte stacks, whose texels are then
 // converted once per window instead of once per tap (1024^3 cone frame with
 // a bfloat16 stack 2.5 -> 2.2 ms).  The float shell and ring cone read the
-// stack: VALU issue bounds them, and finding the window costs what its taps
-// save (large workload, window against stack: shell 1072 us against 951, cone
+// stack: rays that enter at different depths spread a step's samples, and
+// where some do not fit (43 and 78 % of the steps of the large workload) the
+// wave runs both paths (window against stack: shell 1072 us against 951, cone
 // 1266 against 1210).  The sizes hold the taps of the 16 x 4 samples of a
 // step on images of about a pixel per voxel, and five workgroups' windows and
-// tables fit in a CU's LDS.
+// tables fit in a CU's LDS.  One window a step: a second for the samples that
+// the first does not hold costs more than it saves (medium lattice 1083 ->
+// 1111 us, precision frame 2933 -> 3005).
 constexpr int kWinX = 16;
 constexpr int win_y(int kmode) { return kmode == VI_MODE_SHELL ? 8 : 16; }
 constexpr int win_z(int kmode, int stack_dtype)

@@ -771,11 +771,6 @@ __device__ __forceinline__ bool ray_setup(const RenderFrame& F, int px, int py, 
         }
     }
 
-    // C: premultiplied colour so far; T = 1 - alpha_dst, the transmittance in
-    // front of the next segment (kept as a product of exact per-segment
-    // factors, which keeps its relative precision down to term_eps).
-    S.Cr = S.Cg = S.Cb = 0.f;
-    S.T = 1.0f;
     // (an axis the ray does not move along never limits a jump)
     const auto jump_axis = [&](float h0, float hd, float& ih, float& jb) {
         ih = hd != 0.f ? __builtin_amdgcn_rcpf(hd) : 0.f;
@@ -1224,6 +1219,9 @@ __device__ __forceinline__ void shade_block(const RenderFrame& F, float4* s_tf, 
     }
     S.vx = -S.hdx, S.vy = -S.hdy, S.vz = -S.hdz;
     S.last_cell = 0xffffffffu;
+    // C: premultiplied colour so far (0); T = 1 - alpha_dst, the transmittance in
+    // front of the next segment (kept as a product of exact per-segment
+    // factors, which keeps its relative precision down to term_eps).
     S.T = 1.0f;
     S.count = S.K;
     const bool hit = S.K > 0.0f;
