@@ -619,7 +619,10 @@ static hipError_t launch_build_k(const BuildParams& p, hipStream_t s)
         // four slabs; 384^3 and 768^2 1197 and 1027; 512^3 2792 and 1876
         // (2164 with two; float voxels 916 with two, 1089 with four).
         constexpr bool kLinear = LAYOUT == VI_LAYOUT_LINEAR, kLight = LAYOUT == VI_LAYOUT_QUAD4 && sizeof(VT) <= 2;
-        if (p.rlayer > (kLinear ? 500000u : 600000u))
+        // Quads without bits, where every slab of every column is fetched, change
+        // over earlier too (16 waves | 8: 380^3 u8 and 600^2 354 | 317, 445^3
+        // half and 520^2 339 | 260, 697^2 321 | 363).
+        if (p.rlayer > (kLinear ? 500000u : kLight && !p.occ.bits ? 430000u : 600000u))
             return launch_rows<VT, LAYOUT, OUT_DTYPE, PT, 16, kLinear && sizeof(VT) <= 2 ? 4 : 2>(p, s);
         if constexpr (kLight) {
             if (p.rlayer <= 160000u) return launch_rows<VT, LAYOUT, OUT_DTYPE, PT, 4, 4>(p, s);
@@ -628,9 +631,12 @@ static hipError_t launch_build_k(const BuildParams& p, hipStream_t s)
         return launch_rows<VT, LAYOUT, OUT_DTYPE, PT, 8, 2>(p, s);
     }
     if constexpr (OUT_DTYPE != VI_F16) {
-        // (a workgroup covers a stretch of one row of texels: 1024 lanes on a
-        // row of 256 left three in four idle)
-        if (p.res > 512) return launch_tiled<VT, LAYOUT, OUT_DTYPE, PT, 1024>(p, s);
+        // A workgroup covers a stretch of one row of texels.  1024 lanes on a
+        // row of 256 leave three in four idle; but beyond 256 a row in one
+        // workgroup is the faster (u16 quads, 1024 | 256 lanes: 366^2 110.7 |
+        // 114.8 us, 480^2 224 | 234; linear 340^2 207 | 221) unless stretches
+        // of 256 fill it (512^2 363 | 347).
+        if (p.res > 512 || (p.res > 256 && p.res % 256 != 0)) return launch_tiled<VT, LAYOUT, OUT_DTYPE, PT, 1024>(p, s);
         return launch_tiled<VT, LAYOUT, OUT_DTYPE, PT, 256>(p, s);
     }
     return hipErrorInvalidValue;

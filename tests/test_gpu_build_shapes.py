@@ -64,3 +64,16 @@ def test_row_and_tiled_builds_agree(kind, slabs, res):
                         assert torch.equal(rows.dense(), tiled.dense()), what
                 off = float((stacks[vi.VI_F16] - stacks[vi.VI_F32]).abs().max())
                 assert off <= 2.0 ** -12 + 2e-5, (what, off)
+
+
+@pytest.mark.parametrize("slabs,res", [(9, 651), (9, 653), (3, 395), (5, 300)])
+def test_builds_without_bits_agree(slabs, res):
+    """The row shapes of a quad volume without bits change at 430 000 texels a
+    layer; the tiled build on rows that 256 does not divide."""
+    tf = vi.TF.from_numpy(W.tf_ramp(), DEV)
+    vol = _volume("u8 quads")
+    for dt in (vi.VI_F32, vi.VI_BF16):
+        rows = vi.build_attenuation(vol, tf, W.DIAGONAL_LIGHT, slabs, res, dt, layout=1)
+        tiled = vi.build_attenuation(vol, tf, W.DIAGONAL_LIGHT, slabs, res, dt, layout=0)
+        torch.cuda.synchronize()
+        assert torch.equal(rows.dense(), tiled.dense()), (slabs, res, dt)
