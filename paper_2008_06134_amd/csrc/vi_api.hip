@@ -836,6 +836,14 @@ int make_frame(const vi_volume* vol, const vi_tf* tf, const vi_slices* sl, const
     if (!point && F.stack_layout == VI_STACK_ROWS && !F.nearest && wz > 0) {
         // how far the taps reach: texels to any side, layers below and above
         const double texel = sl->res / (2.0 * sl->R) / Nd;  // texels per voxel
+        // the cube's edge in pixels, seen at its centre; the pixels that a face
+        // of it covers; texels between the rays of neighbouring pixels
+        double far = 0.0;
+        for (int a = 0; a < 3; ++a) far += (cam->eye[a] - 0.5) * (cam->eye[a] - 0.5);
+        const double half_h = cam->kind == VI_CAM_PERSP ? tan(0.5 * cam->fovy_deg * M_PI / 180.0) * sqrt(far)
+                                                        : (double)cam->ortho_half_h;
+        const double edge = cam->height / fmax(2.0 * half_h, 1e-6);
+        const double covered = fmin(edge, cam->width) * fmin(edge, cam->height), apart = Nd * texel / edge;
         double reach = 0.0, zmin = 0.0, zmax = 0.0;
         if (mode == VI_MODE_SHELL) {
             for (int t = 0; t < F.ntaps; ++t) {
@@ -859,7 +867,8 @@ int make_frame(const vi_volume* vol, const vi_tf* tf, const vi_slices* sl, const
         // the window must lie in the stored range, and leave room for the
         // samples: two texels and a layer
         if (F.rpitch >= (uint32_t)kWinX && F.res + 4 >= wy && F.n + 2 >= wz && 2.0 * reach + 2.0 <= wy - 1 &&
-            2.0 * reach + 2.0 <= kWinX - 4 && room_z >= 1.0) {
+            2.0 * reach + 2.0 <= kWinX - 4 && room_z >= 1.0 &&
+            window_pays(covered, apart, F.stack_dtype)) {
             F.stage = 1;
             F.st_reach = (float)reach;
             F.st_zmin = (float)zmin;

@@ -230,6 +230,25 @@ constexpr int win_z(int kmode, int stack_dtype)
     if (stack_dtype == VI_F32) return 0;
     return kmode == VI_MODE_SHELL ? 6 : kmode == VI_MODE_CONE ? 5 : 0;
 }
+// Whether a frame is better gathered from windows, of which a face of the cube
+// covers `covered` pixels, the rays of neighbouring pixels `apart` texels apart.
+// Up to about 30 K pixels every wave with work is resident, the time is one
+// wave's chain of steps, and a window's load and wait only lengthen it; with
+// several rounds of waves the L1 counts.  And the further the rays are apart
+// the fewer of a step's samples one window holds, and the rest run the other
+// path as well; the 2-byte stacks, for which a window also saves the
+// conversions, bear more of that.  Measured (stack | window, us): 5 x 5 lattice
+// of 100^3, 31 K pixels 208 | 308, 70 K 416 | 322; of 256^3, 31 K pixels 429 |
+// 551, 70 K (1.1 texels apart) 560 | 592, 124 K (0.8) 741 | 629, 500 K (0.4)
+// 1771 | 1220; 3 x 3 lattice of 512^3, 380 K pixels, 1.0 apart 910 | 997,
+// 770 K, 0.7 apart 1511 | 1456; bfloat16 shell of 256^3, 31 K 204 | 235, 70 K
+// 246 | 270, 124 K 299 | 287; of 500^3, 124 K, 1.7 apart 686 | 625; half ring
+// cone of 512^3, 91 K, 2.0 apart 671 | 626.
+inline bool window_pays(double covered, double apart, int stack_dtype)
+{
+    if (covered < 9.4e4) return covered >= 6.3e4 && apart <= 0.5;
+    return apart <= (stack_dtype == VI_F32 ? 0.9 : 2.0);
+}
 
 // host helpers shared by the API and the server
 int make_frame(const vi_volume* vol, const vi_tf* tf, const vi_slices* sl, const vi_camera* cam, int mode,

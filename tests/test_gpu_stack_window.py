@@ -26,8 +26,7 @@ GATHERS = [("cone", {"cone_grid": 2}), ("cone", {"cone_grid": 5}), ("cone", {"co
            ("shell", {}), ("shell", {"shell_count": 3}), ("shell", {"shell_h_vox": 8.0})]
 
 
-@pytest.mark.parametrize("slabs,res", SIZES)
-def test_window_equals_stack(slabs, res):
+def compare(slabs, res, cams, gathers):
     raw = W.sphere_u8(24, radius=9.5, seed=7)
     tf = vi.TF.from_numpy(W.tf_ramp(), DEV)
     vol = vi.Volume.from_numpy(raw, DEV).to_quads().with_minmax(8).with_occupancy(tf)
@@ -35,8 +34,8 @@ def test_window_equals_stack(slabs, res):
         st = {}
         for dt, layout in ((vi.VI_F32, 0), (vi.VI_F32, 1), (vi.VI_BF16, 0), (vi.VI_BF16, 1), (vi.VI_F16, 1)):
             st[dt, layout] = vi.build_attenuation(vol, tf, light, slabs, res, dt, layout=layout)
-        for cam in (W.camera_orbit(41, 37, 0.7, 0.4), W.camera_ortho_front(64, 48), W.camera_ortho_front(9, 7)):
-            for mode, opts in GATHERS:
+        for cam in cams:
+            for mode, opts in gathers:
                 img = {k: vi.render(vol, tf, s, cam, mode, 0.5, opts) for k, s in st.items()}
                 torch.cuda.synchronize()
                 what = f"{slabs} slabs of {res}^2, {mode} {opts}, {cam['width']}x{cam['height']}"
@@ -44,3 +43,17 @@ def test_window_equals_stack(slabs, res):
                     assert torch.equal(img[dt, 0], img[dt, 1]), what
                 off = float((img[vi.VI_F16, 1] - img[vi.VI_F32, 1]).abs().max())
                 assert off <= 2.0 ** -12 + 1e-5, (what, off)
+
+
+@pytest.mark.parametrize("slabs,res", SIZES)
+def test_window_equals_stack(slabs, res):
+    compare(slabs, res, (W.camera_orbit(41, 37, 0.7, 0.4), W.camera_ortho_front(64, 48), W.camera_ortho_front(9, 7)),
+            GATHERS)
+
+
+@pytest.mark.parametrize("slabs,res", SIZES + [(9, 350), (20, 520)])
+def test_window_equals_stack_larger_images(slabs, res):
+    """Images on both sides of the sizes from which a frame stages: cubes of 70 K and
+    110 K pixels, rays 0.01 to 0.9 texels apart, and one of 40 K."""
+    compare(slabs, res, (W.camera_orbit(569, 391, 0.7, 0.4), W.camera_orbit(641, 487, -0.4, 0.9),
+                         W.camera_ortho_front(641, 487), W.camera_orbit(401, 299, 0.7, 0.4)), GATHERS)
