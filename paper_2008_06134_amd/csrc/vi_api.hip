@@ -864,9 +864,9 @@ int make_frame(const vi_volume* vol, const vi_tf* tf, const vi_slices* sl, const
         zmin -= 1e-3;
         zmax += 1e-3;
         const double room_z = wz - 1 - (zmax - zmin);
-        // the window must lie in the stored range, and leave room for the
+        // the window must lie on stored texels, and leave room for the
         // samples: two texels and a layer
-        if (F.rpitch >= (uint32_t)kWinX && F.res + 4 >= wy && F.n + 2 >= wz && 2.0 * reach + 2.0 <= wy - 1 &&
+        if (F.res + 4 >= kWinX && F.res + 4 >= wy && F.n + 2 >= wz && 2.0 * reach + 2.0 <= wy - 1 &&
             2.0 * reach + 2.0 <= kWinX - 4 && room_z >= 1.0 &&
             window_pays(covered, apart, F.stack_dtype)) {
             F.stage = 1;

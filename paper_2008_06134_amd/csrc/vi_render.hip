@@ -815,7 +815,9 @@ __device__ __forceinline__ bool stage_window(const RenderFrame& F, float* __rest
     const int mx = (__builtin_amdgcn_readlane(ix, first) + __builtin_amdgcn_readlane(ix, last)) >> 1;
     const int my = (__builtin_amdgcn_readlane(iy, first) + __builtin_amdgcn_readlane(iy, last)) >> 1;
     const int mz = (__builtin_amdgcn_readlane(iz, first) + __builtin_amdgcn_readlane(iz, last)) >> 1;
-    const int wx = min(max((mx + F.Mr - 3) & ~3, 0), (int)F.rpitch - kWinX);
+    // (its last column at most the last border texel's: a row's elements past
+    // that one are the caller's, whatever they hold)
+    const int wx = min(max((mx + F.Mr - 3) & ~3, 0), (F.res + 4 - kWinX) & ~3);
     const int wy = min(max(my + F.Mr + 2 - (WY / 2 - 1), 0), F.res + 4 - WY);
     const int wz = min(max(mz + F.Mz + 1 + F.st_oz, 0), F.n + 2 - WZ);
     // the same in light-grid coordinates, and the samples that fit
