@@ -670,6 +670,7 @@ int make_frame(const vi_volume* vol, const vi_tf* tf, const vi_slices* sl, const
             const uint32_t rbase = F.rorg + (uint32_t)F.Mr * F.rpitch + (uint32_t)F.Mr + (uint32_t)F.Mz * F.rlayer;
             F.rb16 = (int32_t)((rbase + 15u) / 16u);
             F.rl16 = (int32_t)(F.rlayer / 16u);
+            F.wide = F.rl16 >= 1 << 23 || F.n - F.Mz >= 1 << 23;
             const char* base = (const char*)sl->data - (size_t)(16u * (uint32_t)F.rb16 - rbase) * es;
             F.stack = base;
             F.stack_r1 = base + (size_t)F.rpitch * es;

@@ -99,9 +99,13 @@ struct RenderFrame {
     const void* stack_l1r1;
     // rows: element of light-grid cell (iz, iy, ix), from the bases above, is
     // 16 (rb16 + iz rl16) + iy rpitch + ix: a layer is a multiple of 16
-    // elements, rl16 = rlayer / 16 < 2^23 and |iz| < 2^13 multiply in one 24-bit
-    // multiply-add, and the bases are moved so that the constant is one, too
+    // elements, and the bases are moved so that the constant is one, too.
+    // rl16 = rlayer / 16 and iz multiply in one 24-bit multiply-add, which holds
+    // every stack that the build makes (rl16 < 2^23 up to a grid of 11,580^2,
+    // |iz| < 2^23).  `wide`: a caller's own descriptor beyond that (few huge
+    // layers, or millions of tiny ones, below 4 GiB), multiplied in 32 bits
     int32_t rb16, rl16;
+    int wide;
     // clamps of light-grid coordinates that keep footprints on stored texels:
     // z in [-1 - Mz, n - 1 - Mz], x and y in [-2 - Mr, res - Mr]
     float zlo, zhi, xlo, xhi;

@@ -16,6 +16,8 @@
 //
 // A wave covers 4 x 4 pixels (16 rays x 4 lanes), a workgroup 8 x 8 pixels,
 // so the rays of a wave sample neighbouring voxels and texels.
+#include <type_traits>
+
 #include "vi_device.h"
 #include "vi_internal.h"
 
@@ -130,18 +132,27 @@ template <int SDT> struct Tap<SDT, VI_STACK_TILED> {
 
 // nearest-face lookups: never, always (copies of a gather behind one branch
 // that is uniform per frame), or a uniform branch per depth (the gather that
-// only serves what a window does not)
-enum class Near { kNo, kYes, kAsk };
+// only serves what a window does not); kWide asks without a branch and takes
+// the layer's offset in 32 bits (a copy for wide layers: asking in the others
+// spilled 29 registers of the shell)
+enum class Near { kNo, kYes, kAsk, kWide };
+template <Near V> using NearC = std::integral_constant<Near, V>;
+template <int V> using Count = std::integral_constant<int, V>;
 template <int SL, Near NEAR>
 __device__ __forceinline__ ZPart<SL> z_part(const RenderFrame& F, float z)
 {
     if (NEAR == Near::kYes || (NEAR == Near::kAsk && F.nearest)) z = floorf(z + 0.5f);
+    if (NEAR == Near::kWide) {
+        const float face = floorf(z + 0.5f);
+        z = F.nearest ? face : z;
+    }
     z = __builtin_amdgcn_fmed3f(z, F.zlo, F.zhi);
     const int iz = floor_int(z);
     ZPart<SL> p;
     p.w = __builtin_amdgcn_fractf(z);
     if constexpr (SL == VI_STACK_ROWS) {
-        p.e = (uint32_t)(__mul24(iz, F.rl16) + F.rb16) << 4;
+        if (NEAR == Near::kWide) p.e = ((uint32_t)iz * (uint32_t)F.rl16 + (uint32_t)F.rb16) << 4;
+        else p.e = (uint32_t)(__mul24(iz, F.rl16) + F.rb16) << 4;
     } else {
         const int k0 = iz + F.Mz;
         p.front = k0 < 0;
@@ -931,21 +942,30 @@ __device__ __forceinline__ void ray_shade(const RenderFrame& F, float* __restric
             sd = fmaf(F.phong_kd, fmaxf(nl, 0.0f), F.phong_ka);
             if (rv > 0.0f) ss = F.phong_ks * fast_exp2(F.phong_shin * fast_log2(rv));
         } else {
-            // (the nearest-face form is a second copy of the
-            // gather behind a branch that is uniform per frame)
+            // (the nearest-face and wide forms are copies of the
+            // gather behind branches that are uniform per frame)
             float A = 1.0f;
             if (PT) {
                 const float pd = fmaf(sm, S.pdd, S.pd0);
-                A = F.nearest ? gather_point<MODE, SDT, SL, Near::kYes>(F, qz, pd, qx, qy, -S.pdd, -S.qdx, -S.qdy)
-                              : gather_point<MODE, SDT, SL, Near::kNo>(F, qz, pd, qx, qy, -S.pdd, -S.qdx, -S.qdy);
+                const auto from = [&](auto near) {
+                    return gather_point<MODE, SDT, SL, near()>(F, qz, pd, qx, qy, -S.pdd, -S.qdx, -S.qdy);
+                };
+                if (SL == VI_STACK_ROWS && F.wide) A = from(NearC<Near::kWide>());
+                else if (F.nearest) A = from(NearC<Near::kYes>());
+                else A = from(NearC<Near::kNo>());
             } else if (MODE != VI_MODE_NONE) {
                 constexpr int NB = tap_batch<MODE, SDT>();
+                const auto from = [&](auto near, auto nb) {
+                    return gather<MODE, nb()>(F, FromStack<SDT, SL, near()>{F}, S.cf, qz, qx, qy);
+                };
                 if constexpr (kStaged<MODE, SDT, SL>) {
                     if (staged) A = gather<MODE, NB>(F, win, S.cf, qz, qx, qy);
-                    else A = gather<MODE, 1>(F, FromStack<SDT, SL, Near::kAsk>{F}, S.cf, qz, qx, qy);
+                    else if (F.wide) A = from(NearC<Near::kWide>(), Count<1>());
+                    else A = from(NearC<Near::kAsk>(), Count<1>());
                 } else {
-                    if (F.nearest) A = gather<MODE, NB>(F, FromStack<SDT, SL, Near::kYes>{F}, S.cf, qz, qx, qy);
-                    else A = gather<MODE, NB>(F, FromStack<SDT, SL, Near::kNo>{F}, S.cf, qz, qx, qy);
+                    if (SL == VI_STACK_ROWS && F.wide) A = from(NearC<Near::kWide>(), Count<1>());
+                    else if (F.nearest) A = from(NearC<Near::kYes>(), Count<NB>());
+                    else A = from(NearC<Near::kNo>(), Count<NB>());
                 }
             }
             sd = fmaf(1.0f - F.ambient, A, F.ambient);
