@@ -135,9 +135,12 @@ hipError_t launch_to_quads(const void* src, void* dst, int dtype, int N, hipStre
 
 // --------------------------------------------------------------------------
 // Empty-space map: the least and greatest normalised value over a cell's
-// voxels and the next one along each axis (clamped).  A workgroup of WAVES waves
-// takes 4 / WAVES cells: four waves share a cell of 16^3 voxels and more (few
-// cells, long walks), smaller cells have a wave each.  A lane keeps the range
+// voxels and the next one along each axis (clamped).  A workgroup of four waves
+// takes 4 / WAVES cells: WAVES = 4 share a cell of 16^3 voxels and more (few
+// cells, long walks; see the launch for the quads), smaller cells have a wave
+// each.  A launch dimension holds less than 2^32 work items, which the cells of
+// 4^3 voxels of a volume near 4 GiB pass (1625^3: 407^3 waves), so the
+// workgroups are spread over two.  A lane keeps the range
 // of what it reads; the cells are taken last to first, since a volume that has
 // just been laid out still has its end in the last-level cache.  512^3 u16
 // quads, 16^3 cells: 868 us with a lane a cell, 259 now (1.07 GB, 4.1 TB/s).
@@ -191,8 +194,9 @@ template <typename VT, int LAYOUT, int WAVES>
 __global__ __launch_bounds__(256) void minmax_kernel(const VT* __restrict__ vol, VolIndex I, int N, float scale,
                                                      int shift, uint32_t nc, float2* __restrict__ out)
 {
-    const uint32_t cells = nc * nc * nc, from_end = blockIdx.x * (4u / WAVES) + (threadIdx.x >> 6) / WAVES;
-    if (from_end >= cells) return;  // whole waves (WAVES = 1)
+    const uint32_t cells = nc * nc * nc, block = blockIdx.y * gridDim.x + blockIdx.x;
+    const uint32_t from_end = block * (4u / WAVES) + (threadIdx.x >> 6) / WAVES;
+    if (from_end >= cells) return;  // whole waves (WAVES = 1), whole workgroups (WAVES = 4)
     const uint32_t c = cells - 1u - from_end;
     const int lane = threadIdx.x & 63, wave = (int)(threadIdx.x >> 6) % WAVES;
     const int first = wave * 64 + lane, step = WAVES * 64;
@@ -287,6 +291,7 @@ __global__ __launch_bounds__(256) void minmax_kernel(const VT* __restrict__ vol,
     if (lane == 0 && wave == 0) out[c] = r.ends(scale);
 }
 
+constexpr uint32_t kMapBlocksX = 1u << 23;  // of 256 lanes: 2^31 work items
 template <typename VT, int LAYOUT>
 static hipError_t launch_mm_l(const void* vol, VolIndex I, int N, float scale, int shift, float* out, hipStream_t s)
 {
@@ -294,12 +299,15 @@ static hipError_t launch_mm_l(const void* vol, VolIndex I, int N, float scale, i
     // (a wave a cell, 4096 cells fill the chip's SIMDs four deep; beyond that
     // the quads' one wave a cell is the faster, 265 us against 312 at 512^3,
     // the other layouts' longer walks are not, 1081 against 633 at 1024^3)
-    if (shift >= 4 && (LAYOUT != VI_LAYOUT_QUAD4 || cells <= 4096u))
-        hipLaunchKernelGGL((minmax_kernel<VT, LAYOUT, 4>), dim3(cells), dim3(256), 0, s, (const VT*)vol, I, N, scale,
-                           shift, nc, (float2*)out);
+    const bool shared = shift >= 4 && (LAYOUT != VI_LAYOUT_QUAD4 || cells <= 4096u);
+    const uint32_t blocks = shared ? cells : (cells + 3u) / 4u, rows = (blocks + kMapBlocksX - 1) / kMapBlocksX;
+    const dim3 grid((blocks + rows - 1) / rows, rows);
+    if (shared)
+        hipLaunchKernelGGL((minmax_kernel<VT, LAYOUT, 4>), grid, dim3(256), 0, s, (const VT*)vol, I, N, scale, shift,
+                           nc, (float2*)out);
     else
-        hipLaunchKernelGGL((minmax_kernel<VT, LAYOUT, 1>), dim3((cells + 3) / 4), dim3(256), 0, s, (const VT*)vol, I, N,
-                           scale, shift, nc, (float2*)out);
+        hipLaunchKernelGGL((minmax_kernel<VT, LAYOUT, 1>), grid, dim3(256), 0, s, (const VT*)vol, I, N, scale, shift,
+                           nc, (float2*)out);
     return hipGetLastError();
 }
 
