@@ -868,9 +868,9 @@ int make_frame(const vi_volume* vol, const vi_tf* tf, const vi_slices* sl, const
         // the window must lie on stored texels, and leave room for the
         // samples: two texels and a layer
         if (F.res + 4 >= kWinX && F.res + 4 >= wy && F.n + 2 >= wz && 2.0 * reach + 2.0 <= wy - 1 &&
-            2.0 * reach + 2.0 <= kWinX - 4 && room_z >= 1.0 &&
-            window_pays(covered, apart, F.stack_dtype)) {
-            F.stage = 1;
+            2.0 * reach + 2.0 <= kWinX - 4 && room_z >= 1.0) {
+            F.windowed = 1;
+            F.stage = window_pays(covered, apart, F.stack_dtype);
             F.st_reach = (float)reach;
             F.st_zmin = (float)zmin;
             F.st_zmax = (float)zmax;

@@ -109,11 +109,12 @@ struct RenderFrame {
     // clamps of light-grid coordinates that keep footprints on stored texels:
     // z in [-1 - Mz, n - 1 - Mz], x and y in [-2 - Mr, res - Mr]
     float zlo, zhi, xlo, xhi;
-    // rows, directional gathers: whether a wave may stage the stack texels
-    // its samples' taps can reach in LDS (see kStage), the taps' reach in
-    // texels and in layers below and above the sample, and the first layer
-    // of the window against the sample's
-    int stage;
+    // rows, directional gathers: whether the stack texels that the taps of a
+    // wave's samples can reach fit a window in LDS (windowed, see kStaged),
+    // whether the frame reads them from there (stage: where window_pays, too),
+    // the taps' reach in texels and in layers below and above the sample, and
+    // the first layer of the window against the sample's
+    int windowed, stage;
     float st_reach, st_zmin, st_zmax;
     int st_oz;
     int stack_dtype;
