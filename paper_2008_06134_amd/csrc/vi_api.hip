@@ -834,7 +834,7 @@ int make_frame(const vi_volume* vol, const vi_tf* tf, const vi_slices* sl, const
         F.tap_w = 1.0f / F.ntaps;
     }
     const int km = kernel_mode(F), wy = win_y(km), wz = reads_stack ? win_z(km, F.stack_dtype) : 0;
-    if (!point && F.stack_layout == VI_STACK_ROWS && !F.nearest && wz > 0) {
+    if (!point && F.stack_layout == VI_STACK_ROWS && !F.nearest && !F.wide && wz > 0) {
         // how far the taps reach: texels to any side, layers below and above
         const double texel = sl->res / (2.0 * sl->R) / Nd;  // texels per voxel
         // the cube's edge in pixels, seen at its centre; the pixels that a face
@@ -893,11 +893,11 @@ hipError_t render_part(int part, const RenderFrame& f, hipStream_t s)
     return hipErrorInvalidValue;
 }
 template <int P>
-hipError_t batch_part(int part, int sdt, int sl, int mode, const RenderFrame* f, const uint32_t* t, uint32_t n, int K,
-                      uint32_t w, hipStream_t s)
+hipError_t batch_part(int part, int sdt, int sl, int mode, bool staged, const RenderFrame* f, const uint32_t* t,
+                      uint32_t n, size_t tables, hipStream_t s)
 {
-    if (part == P) return launch_render_batch_part<P>(sdt, sl, mode, f, t, n, K, w, s);
-    if constexpr (P + 1 < kRenderParts) return batch_part<P + 1>(part, sdt, sl, mode, f, t, n, K, w, s);
+    if (part == P) return launch_render_batch_part<P>(sdt, sl, mode, staged, f, t, n, tables, s);
+    if constexpr (P + 1 < kRenderParts) return batch_part<P + 1>(part, sdt, sl, mode, staged, f, t, n, tables, s);
     return hipErrorInvalidValue;
 }
 }  // namespace
@@ -907,12 +907,12 @@ hipError_t launch_render(const RenderFrame& f, hipStream_t s)
     return render_part<0>(f.vol_dtype * 3 + f.vol_layout, f, s);
 }
 
-hipError_t launch_render_batch(int vol_dtype, int layout, int stack_dtype, int stack_layout, int mode,
-                               const RenderFrame* d_frames, const uint32_t* d_tiles, uint32_t ntiles, int maxK,
-                               uint32_t max_occ_words, hipStream_t s)
+hipError_t launch_render_batch(int vol_dtype, int layout, int stack_dtype, int stack_layout, int mode, bool staged,
+                               const RenderFrame* d_frames, const uint32_t* d_tiles, uint32_t ntiles, size_t tables,
+                               hipStream_t s)
 {
-    return batch_part<0>(vol_dtype * 3 + layout, stack_dtype, stack_layout, mode, d_frames, d_tiles, ntiles, maxK,
-                         max_occ_words, s);
+    return batch_part<0>(vol_dtype * 3 + layout, stack_dtype, stack_layout, mode, staged, d_frames, d_tiles, ntiles,
+                         tables, s);
 }
 
 int fail_msg(int code, const char* msg) { return fail(code, "%s", msg); }

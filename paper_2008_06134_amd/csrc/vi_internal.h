@@ -175,17 +175,17 @@ hipError_t launch_render(const RenderFrame& f, hipStream_t s);
 // one launch over `ntiles` tiles whose frames all have kernel_mode() `mode`
 // (maxK / max_occ_words: the largest transfer function and LDS occupancy
 // bits of the frames, which size the launch's LDS)
-hipError_t launch_render_batch(int vol_dtype, int layout, int stack_dtype, int stack_layout, int mode,
-                               const RenderFrame* d_frames, const uint32_t* d_tiles, uint32_t ntiles, int maxK,
-                               uint32_t max_occ_words, hipStream_t s);
+hipError_t launch_render_batch(int vol_dtype, int layout, int stack_dtype, int stack_layout, int mode, bool staged,
+                               const RenderFrame* d_frames, const uint32_t* d_tiles, uint32_t ntiles, size_t tables,
+                               hipStream_t s);
 // The render kernels of one voxel type and volume layout (P = dtype * 3 +
 // layout), each defined in a compilation of vi_render.hip of its own.
 template <int P>
 hipError_t launch_render_part(const RenderFrame& f, hipStream_t s);
 template <int P>
-hipError_t launch_render_batch_part(int stack_dtype, int stack_layout, int mode, const RenderFrame* d_frames,
-                                    const uint32_t* d_tiles, uint32_t ntiles, int maxK, uint32_t max_occ_words,
-                                    hipStream_t s);
+hipError_t launch_render_batch_part(int stack_dtype, int stack_layout, int mode, bool staged,
+                                    const RenderFrame* d_frames, const uint32_t* d_tiles, uint32_t ntiles,
+                                    size_t tables, hipStream_t s);
 constexpr int kRenderParts = 12;
 hipError_t launch_to_bricks(const void* src, void* dst, int dtype, int N, hipStream_t s);
 hipError_t launch_to_quads(const void* src, void* dst, int dtype, int N, hipStream_t s);
@@ -210,6 +210,15 @@ inline int kernel_mode(const RenderFrame& f)
     if (f.point && f.mode == VI_MODE_CONE) return kModePointCone;
     if (f.mode == VI_MODE_CONE && f.cone_grid > 0) return kModeConeGrid;
     return f.mode;
+}
+
+// Bytes of LDS of a frame's tables, up to 16: the K entries of the transfer
+// function, then the occupancy bits, or the K next-opaque indices of a map
+// without bits.
+__host__ __device__ inline size_t table_bytes(const RenderFrame& f)
+{
+    const uint32_t more = f.occ.bits ? f.occ.words + f.occ.swords : f.occ.mm ? (uint32_t)f.K : 0u;
+    return (sizeof(float4) * (size_t)f.K + sizeof(uint32_t) * (size_t)more + 15) / 16 * 16;
 }
 
 // The stack window a wave stages in LDS for its gathers: kWinX columns (16

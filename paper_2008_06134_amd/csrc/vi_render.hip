@@ -131,17 +131,16 @@ template <int SDT> struct Tap<SDT, VI_STACK_TILED> {
 };
 
 // nearest-face lookups: never, always (copies of a gather behind one branch
-// that is uniform per frame), or a uniform branch per depth (the gather that
-// only serves what a window does not); kWide asks without a branch and takes
-// the layer's offset in 32 bits (a copy for wide layers: asking in the others
-// spilled 29 registers of the shell)
-enum class Near { kNo, kYes, kAsk, kWide };
+// that is uniform per frame), or, for wide layers, asked without a branch and
+// with the layer's offset in 32 bits (a copy, too: asking by a branch in the
+// others spilled 29 registers of the shell)
+enum class Near { kNo, kYes, kWide };
 template <Near V> using NearC = std::integral_constant<Near, V>;
 template <int V> using Count = std::integral_constant<int, V>;
 template <int SL, Near NEAR>
 __device__ __forceinline__ ZPart<SL> z_part(const RenderFrame& F, float z)
 {
-    if (NEAR == Near::kYes || (NEAR == Near::kAsk && F.nearest)) z = floorf(z + 0.5f);
+    if (NEAR == Near::kYes) z = floorf(z + 0.5f);
     if (NEAR == Near::kWide) {
         const float face = floorf(z + 0.5f);
         z = F.nearest ? face : z;
@@ -809,7 +808,7 @@ __device__ __forceinline__ bool ray_setup(const RenderFrame& F, int px, int py, 
 // stack, and so does a wave with few samples.
 constexpr int kStageMin = 12;  // samples
 template <int MODE, int SDT, int SL>
-constexpr bool kStaged = SL == VI_STACK_ROWS && win_z(MODE, SDT) > 0;
+constexpr bool kWindowed = SL == VI_STACK_ROWS && win_z(MODE, SDT) > 0;
 template <int MODE, int SDT>
 __device__ __forceinline__ bool stage_window(const RenderFrame& F, float* __restrict__ tile, bool lit, float z, float x,
                                              float y, int& org)
@@ -876,7 +875,7 @@ __device__ __forceinline__ bool stage_window(const RenderFrame& F, float* __rest
 
 // Composite the four segments of a step of every live ray (opacity 1 - om,
 // colour er, eg, eb at distance sm), lit by the coefficient.
-template <typename VT, int LAYOUT, int MODE, int SDT, int SL>
+template <typename VT, int LAYOUT, int MODE, int SDT, int SL, bool STAGED>
 __device__ __forceinline__ void ray_shade(const RenderFrame& F, float* __restrict__ tile, RayState& S, bool live,
                                           bool in, float om, float er, float eg, float eb, float sm, float hx, float hy,
                                           float hz, uint32_t& nop)
@@ -903,8 +902,7 @@ __device__ __forceinline__ void ray_shade(const RenderFrame& F, float* __restric
     [[maybe_unused]] float qz, qx, qy;
     if constexpr (MODE != VI_MODE_NONE && !PHONG) {
         qz = fmaf(sm, S.qdz, S.qz0), qx = fmaf(sm, S.qdx, S.qx0), qy = fmaf(sm, S.qdy, S.qy0);
-        if constexpr (kStaged<MODE, SDT, SL>)
-            if (F.stage) staged = stage_window<MODE, SDT>(F, tile, lit, qz, qx, qy, win.org);
+        if constexpr (STAGED) staged = stage_window<MODE, SDT>(F, tile, lit, qz, qx, qy, win.org);
     }
     if (lit) {
         // emission alpha (sd rgb + ss) light: Eq. 7 with the coefficient A,
@@ -958,10 +956,9 @@ __device__ __forceinline__ void ray_shade(const RenderFrame& F, float* __restric
                 const auto from = [&](auto near, auto nb) {
                     return gather<MODE, nb()>(F, FromStack<SDT, SL, near()>{F}, S.cf, qz, qx, qy);
                 };
-                if constexpr (kStaged<MODE, SDT, SL>) {
+                if constexpr (STAGED) {
                     if (staged) A = gather<MODE, NB>(F, win, S.cf, qz, qx, qy);
-                    else if (F.wide) A = from(NearC<Near::kWide>(), Count<1>());
-                    else A = from(NearC<Near::kAsk>(), Count<1>());
+                    else A = from(NearC<Near::kNo>(), Count<1>());
                 } else {
                     if (SL == VI_STACK_ROWS && F.wide) A = from(NearC<Near::kWide>(), Count<1>());
                     else if (F.nearest) A = from(NearC<Near::kYes>(), Count<NB>());
@@ -986,7 +983,7 @@ __device__ __forceinline__ void ray_shade(const RenderFrame& F, float* __restric
 // done.  Where the gather stages windows the wave's lanes stay together
 // (finished rays' lanes take part in the staging); elsewhere a quad leaves
 // the loop with its ray.
-template <typename VT, int LAYOUT, int MODE, int SDT, int SL>
+template <typename VT, int LAYOUT, int MODE, int SDT, int SL, bool STAGED>
 __device__ __forceinline__ void ray_step(const RenderFrame& F, const float4* __restrict__ s_tf,
                                          const int* __restrict__ s_next, const uint32_t* __restrict__ s_bits,
                                          float* __restrict__ tile, RayState& S, bool& live, uint32_t& nop)
@@ -1082,8 +1079,8 @@ __device__ __forceinline__ void ray_step(const RenderFrame& F, const float4* __r
         const float jlast = quad_perm<3, 3, 3, 3>(jl);
         knext = fmaxf(knext, 4.0f * floorf(0.25f * (jlast + 1.0f)));
     }
-    if (kStaged<MODE, SDT, SL> ? __any(live && !jump) : !jump)
-        ray_shade<VT, LAYOUT, MODE, SDT, SL>(F, tile, S, live, in, om, er, eg, eb, sm, hx, hy, hz, nop);
+    if (STAGED ? __any(live && !jump) : !jump)
+        ray_shade<VT, LAYOUT, MODE, SDT, SL, STAGED>(F, tile, S, live, in, om, er, eg, eb, sm, hx, hy, hz, nop);
     S.k = knext;
     if (S.T <= F.term_eps || S.k >= S.K) live = false;
 }
@@ -1166,21 +1163,17 @@ __device__ __forceinline__ void group_count_add(const RenderFrame& F, GroupCount
     }
 }
 
-// LDS of a workgroup: K table entries, K next-opaque indices, the occupancy
-// bits, then (16-byte aligned) its four waves' areas, each for its stack window
-// and, before the march, its rays.
-__host__ __device__ inline size_t table_bytes(int K, uint32_t occ_words)
+// LDS of a workgroup: the frame's tables (see table_bytes), then its four waves'
+// areas, each for its stack window, if the frame stages, and, before the march,
+// its rays.
+constexpr size_t wave_words(int kmode, int stack_dtype, bool staged)
 {
-    return ((sizeof(float4) + sizeof(int)) * (size_t)K + sizeof(uint32_t) * (size_t)occ_words + 15) / 16 * 16;
-}
-constexpr size_t wave_words(int kmode, int stack_dtype, int SL)
-{
-    const size_t w = SL == VI_STACK_ROWS ? kWinX * win_y(kmode) * win_z(kmode, stack_dtype) : 0;
+    const size_t w = staged ? kWinX * win_y(kmode) * win_z(kmode, stack_dtype) : 0;
     return w > 16 * kRayFields ? w : 16 * kRayFields;
 }
-constexpr size_t wave_bytes(int kmode, int stack_dtype, int SL)
+constexpr size_t wave_bytes(int kmode, int stack_dtype, bool staged)
 {
-    return 4 * sizeof(float) * wave_words(kmode, stack_dtype, SL);
+    return 4 * sizeof(float) * wave_words(kmode, stack_dtype, staged);
 }
 
 // `n` words from device memory to LDS, by the whole workgroup, without waiting
@@ -1202,20 +1195,19 @@ __device__ __forceinline__ void stage_words(const void* src, void* dst, uint32_t
 // work four times, a tenth of a frame's VALU instructions, after having waited
 // for the tables.)  The waves take turns at it by workgroup, so that no SIMD
 // gets all of it.
-template <typename VT, int LAYOUT, int MODE, int SDT, int SL>
+template <typename VT, int LAYOUT, int MODE, int SDT, int SL, bool STAGED>
 __device__ __forceinline__ void shade_block(const RenderFrame& F, float4* s_tf, int x0, int y0, uint32_t turn)
 {
     __shared__ GroupCount gc;
     group_count_init(&gc);
-    int* s_next = (int*)(s_tf + F.K);
-    uint32_t* s_bits = (uint32_t*)(s_next + F.K);
-    const uint32_t words = F.occ.words + F.occ.swords;
+    int* s_next = (int*)(s_tf + F.K);        // of a map without bits
+    uint32_t* s_bits = (uint32_t*)s_next;
     stage_words(F.tf, s_tf, 4u * (uint32_t)F.K);
-    if (F.occ.bits) stage_words(F.occ.bits, s_bits, words);
+    if (F.occ.bits) stage_words(F.occ.bits, s_bits, F.occ.words + F.occ.swords);
     else if (F.occ.mm) build_next_opaque(s_next, F.tf, F.K);
 
-    constexpr uint32_t kWords = (uint32_t)wave_words(MODE, SDT, SL);
-    float* areas = (float*)((char*)s_tf + table_bytes(F.K, words));
+    constexpr uint32_t kWords = (uint32_t)wave_words(MODE, SDT, STAGED);
+    float* areas = (float*)((char*)s_tf + table_bytes(F));
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
     RayState S = {};
     if (wave == (turn & 3u)) {
@@ -1249,8 +1241,8 @@ __device__ __forceinline__ void shade_block(const RenderFrame& F, float4* s_tf, 
     const bool hit = S.K > 0.0f;
     bool live = hit;
     uint32_t ns = 0, nop = 0;
-    while (kStaged<MODE, SDT, SL> ? __any(live) : live)
-        ray_step<VT, LAYOUT, MODE, SDT, SL>(F, s_tf, s_next, s_bits, tile, S, live, nop);
+    while (STAGED ? __any(live) : live)
+        ray_step<VT, LAYOUT, MODE, SDT, SL, STAGED>(F, s_tf, s_next, s_bits, tile, S, live, nop);
     int px = x0, py = y0;
     ray_pixel((int)(threadIdx.x >> 2), &px, &py);
     if (hit) {
@@ -1268,14 +1260,14 @@ __device__ __forceinline__ void shade_block(const RenderFrame& F, float4* s_tf, 
 // --------------------------------------------------------------------------
 // single-frame kernel
 // --------------------------------------------------------------------------
-template <typename VT, int LAYOUT, int MODE, int SDT, int SL>
+template <typename VT, int LAYOUT, int MODE, int SDT, int SL, bool STAGED>
 __device__ __forceinline__ void render_frame(const RenderFrame& F)
 {
     extern __shared__ float4 s_tf[];
     const uint32_t tiles_x = (F.width + kBX - 1) / kBX, tiles_y = (F.height + kBY - 1) / kBY;
     uint32_t tx, ty;
     if (!supertile_of(blockIdx.x, tiles_x, tiles_y, &tx, &ty)) return;
-    shade_block<VT, LAYOUT, MODE, SDT, SL>(F, s_tf, (int)tx * kBX, (int)ty * kBY, blockIdx.x / kXcds);
+    shade_block<VT, LAYOUT, MODE, SDT, SL, STAGED>(F, s_tf, (int)tx * kBX, (int)ty * kBY, blockIdx.x / kXcds);
 }
 
 // --------------------------------------------------------------------------
@@ -1288,7 +1280,7 @@ __device__ __forceinline__ void render_frame(const RenderFrame& F)
 // --------------------------------------------------------------------------
 constexpr uint32_t kSubX = 16 / kBX, kSubY = 16 / kBY, kSub = kSubX * kSubY;
 
-template <typename VT, int LAYOUT, int MODE, int SDT, int SL>
+template <typename VT, int LAYOUT, int MODE, int SDT, int SL, bool STAGED>
 __device__ __forceinline__ void render_tiles(const RenderFrame* __restrict__ frames, const uint32_t* __restrict__ tiles,
                                              uint32_t ntiles)
 {
@@ -1297,7 +1289,7 @@ __device__ __forceinline__ void render_tiles(const RenderFrame* __restrict__ fra
     if (!list_of(blockIdx.x, ntiles * kSub, &q)) return;
     const uint32_t t = tiles[q / kSub], sub = q % kSub;
     const RenderFrame& F = frames[t >> 22];
-    shade_block<VT, LAYOUT, MODE, SDT, SL>(F, s_tf, (int)((t & 2047u) * kSubX + sub % kSubX) * kBX,
+    shade_block<VT, LAYOUT, MODE, SDT, SL, STAGED>(F, s_tf, (int)((t & 2047u) * kSubX + sub % kSubX) * kBX,
                                            (int)(((t >> 11) & 2047u) * kSubY + sub / kSubX) * kBY, blockIdx.x / kXcds);
 }
 
@@ -1312,119 +1304,86 @@ constexpr int kMinWaves = SL != VI_STACK_ROWS ? 1
                           : SDT == VI_F32 && (MODE == VI_MODE_SHELL || MODE == VI_MODE_CONE || MODE == kModeConeGrid)
                               ? 6
                               : 5;
-template <typename VT, int LAYOUT, int MODE, int SDT, int SL>
+template <typename VT, int LAYOUT, int MODE, int SDT, int SL, bool STAGED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMinWaves<MODE, SDT, SL>))) void render_kernel(
     RenderFrame F)
 {
-    render_frame<VT, LAYOUT, MODE, SDT, SL>(F);
+    render_frame<VT, LAYOUT, MODE, SDT, SL, STAGED>(F);
 }
-template <typename VT, int LAYOUT, int MODE, int SDT, int SL>
+template <typename VT, int LAYOUT, int MODE, int SDT, int SL, bool STAGED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMinWaves<MODE, SDT, SL>))) void
 render_batch_kernel(const RenderFrame* __restrict__ frames, const uint32_t* __restrict__ tiles, uint32_t ntiles)
 {
-    render_tiles<VT, LAYOUT, MODE, SDT, SL>(frames, tiles, ntiles);
+    render_tiles<VT, LAYOUT, MODE, SDT, SL, STAGED>(frames, tiles, ntiles);
 }
 
-template <typename VT, int LAYOUT, int SDT, int SL>
-static hipError_t launch_batch_t(int mode, const RenderFrame* d_frames, const uint32_t* d_tiles, uint32_t ntiles,
-                                 int maxK, uint32_t occ_words, hipStream_t s)
+// A frame that stages windows and one that does not are kernels of their own:
+// the staging march keeps a wave's lanes together and takes 12 to 20 KB of LDS
+// a workgroup, which frames without it would pay for nothing.
+template <typename FN>
+static hipError_t with_mode(int mode, FN fn)
 {
-    const size_t lds = table_bytes(maxK, occ_words) + wave_bytes(mode, SDT, SL);
-    const dim3 grid(list_grid(ntiles * kSub)), block(256);
     switch (mode) {
-    case VI_MODE_NONE:
-        hipLaunchKernelGGL((render_batch_kernel<VT, LAYOUT, VI_MODE_NONE, SDT, SL>), grid, block, lds, s, d_frames,
-                           d_tiles, ntiles);
-        break;
-    case VI_MODE_SHADOW:
-        hipLaunchKernelGGL((render_batch_kernel<VT, LAYOUT, VI_MODE_SHADOW, SDT, SL>), grid, block, lds, s, d_frames,
-                           d_tiles, ntiles);
-        break;
-    case VI_MODE_SHELL:
-        hipLaunchKernelGGL((render_batch_kernel<VT, LAYOUT, VI_MODE_SHELL, SDT, SL>), grid, block, lds, s, d_frames,
-                           d_tiles, ntiles);
-        break;
-    case VI_MODE_CONE:
-        hipLaunchKernelGGL((render_batch_kernel<VT, LAYOUT, VI_MODE_CONE, SDT, SL>), grid, block, lds, s, d_frames,
-                           d_tiles, ntiles);
-        break;
-    case kModePointShadow:
-        hipLaunchKernelGGL((render_batch_kernel<VT, LAYOUT, kModePointShadow, SDT, SL>), grid, block, lds, s,
-                           d_frames, d_tiles, ntiles);
-        break;
-    case kModePointShell:
-        hipLaunchKernelGGL((render_batch_kernel<VT, LAYOUT, kModePointShell, SDT, SL>), grid, block, lds, s,
-                           d_frames, d_tiles, ntiles);
-        break;
-    case kModePointPhong:
-        hipLaunchKernelGGL((render_batch_kernel<VT, LAYOUT, kModePointPhong, SDT, SL>), grid, block, lds, s,
-                           d_frames, d_tiles, ntiles);
-        break;
-    case kModeConeGrid:
-        hipLaunchKernelGGL((render_batch_kernel<VT, LAYOUT, kModeConeGrid, SDT, SL>), grid, block, lds, s,
-                           d_frames, d_tiles, ntiles);
-        break;
-    case kModePointCone:
-        hipLaunchKernelGGL((render_batch_kernel<VT, LAYOUT, kModePointCone, SDT, SL>), grid, block, lds, s,
-                           d_frames, d_tiles, ntiles);
-        break;
-    default:
-        hipLaunchKernelGGL((render_batch_kernel<VT, LAYOUT, VI_MODE_PHONG, SDT, SL>), grid, block, lds, s, d_frames,
-                           d_tiles, ntiles);
-        break;
+    case VI_MODE_NONE: fn(std::integral_constant<int, VI_MODE_NONE>()); break;
+    case VI_MODE_SHADOW: fn(std::integral_constant<int, VI_MODE_SHADOW>()); break;
+    case VI_MODE_SHELL: fn(std::integral_constant<int, VI_MODE_SHELL>()); break;
+    case VI_MODE_CONE: fn(std::integral_constant<int, VI_MODE_CONE>()); break;
+    case kModePointShadow: fn(std::integral_constant<int, kModePointShadow>()); break;
+    case kModePointShell: fn(std::integral_constant<int, kModePointShell>()); break;
+    case kModePointPhong: fn(std::integral_constant<int, kModePointPhong>()); break;
+    case kModeConeGrid: fn(std::integral_constant<int, kModeConeGrid>()); break;
+    case kModePointCone: fn(std::integral_constant<int, kModePointCone>()); break;
+    default: fn(std::integral_constant<int, VI_MODE_PHONG>()); break;
     }
     return hipGetLastError();
 }
 
+template <typename VT, int LAYOUT, int SDT, int SL>
+static hipError_t launch_batch_t(int mode, bool staged, const RenderFrame* d_frames, const uint32_t* d_tiles,
+                                 uint32_t ntiles, size_t tables, hipStream_t s)
+{
+    const dim3 grid(list_grid(ntiles * kSub)), block(256);
+    return with_mode(mode, [&](auto m) {
+        constexpr int MODE = m();
+        const size_t lds = tables + wave_bytes(MODE, SDT, staged);
+        if constexpr (kWindowed<MODE, SDT, SL>)
+            if (staged) {
+                hipLaunchKernelGGL((render_batch_kernel<VT, LAYOUT, MODE, SDT, SL, true>), grid, block, lds, s, d_frames,
+                                   d_tiles, ntiles);
+                return;
+            }
+        hipLaunchKernelGGL((render_batch_kernel<VT, LAYOUT, MODE, SDT, SL, false>), grid, block, lds, s, d_frames,
+                           d_tiles, ntiles);
+    });
+}
+
 template <typename VT, int LAYOUT>
-static hipError_t launch_batch_l(int sdt, int sl, int mode, const RenderFrame* f, const uint32_t* t, uint32_t n,
-                                 int K, uint32_t w, hipStream_t s)
+static hipError_t launch_batch_l(int sdt, int sl, int mode, bool staged, const RenderFrame* f, const uint32_t* t,
+                                 uint32_t n, size_t tables, hipStream_t s)
 {
     if (sdt == VI_BF16)
-        return sl == VI_STACK_ROWS ? launch_batch_t<VT, LAYOUT, VI_BF16, VI_STACK_ROWS>(mode, f, t, n, K, w, s)
-                                   : launch_batch_t<VT, LAYOUT, VI_BF16, VI_STACK_TILED>(mode, f, t, n, K, w, s);
+        return sl == VI_STACK_ROWS ? launch_batch_t<VT, LAYOUT, VI_BF16, VI_STACK_ROWS>(mode, staged, f, t, n, tables, s)
+                                   : launch_batch_t<VT, LAYOUT, VI_BF16, VI_STACK_TILED>(mode, staged, f, t, n, tables, s);
     if (sdt == VI_F16)  // row layout only
-        return launch_batch_t<VT, LAYOUT, VI_F16, VI_STACK_ROWS>(mode, f, t, n, K, w, s);
-    return sl == VI_STACK_ROWS ? launch_batch_t<VT, LAYOUT, VI_F32, VI_STACK_ROWS>(mode, f, t, n, K, w, s)
-                               : launch_batch_t<VT, LAYOUT, VI_F32, VI_STACK_TILED>(mode, f, t, n, K, w, s);
+        return launch_batch_t<VT, LAYOUT, VI_F16, VI_STACK_ROWS>(mode, staged, f, t, n, tables, s);
+    return sl == VI_STACK_ROWS ? launch_batch_t<VT, LAYOUT, VI_F32, VI_STACK_ROWS>(mode, staged, f, t, n, tables, s)
+                               : launch_batch_t<VT, LAYOUT, VI_F32, VI_STACK_TILED>(mode, staged, f, t, n, tables, s);
 }
 
 template <typename VT, int LAYOUT, int SDT, int SL>
 static hipError_t launch_mode(const RenderFrame& f, hipStream_t s)
 {
-    dim3 grid(supertile_grid((f.width + kBX - 1) / kBX, (f.height + kBY - 1) / kBY)), block(256);
-    const size_t lds = table_bytes(f.K, f.occ.words + f.occ.swords) + wave_bytes(kernel_mode(f), SDT, SL);
-    switch (kernel_mode(f)) {
-    case VI_MODE_NONE:
-        hipLaunchKernelGGL((render_kernel<VT, LAYOUT, VI_MODE_NONE, SDT, SL>), grid, block, lds, s, f);
-        break;
-    case VI_MODE_SHADOW:
-        hipLaunchKernelGGL((render_kernel<VT, LAYOUT, VI_MODE_SHADOW, SDT, SL>), grid, block, lds, s, f);
-        break;
-    case VI_MODE_SHELL:
-        hipLaunchKernelGGL((render_kernel<VT, LAYOUT, VI_MODE_SHELL, SDT, SL>), grid, block, lds, s, f);
-        break;
-    case VI_MODE_CONE:
-        hipLaunchKernelGGL((render_kernel<VT, LAYOUT, VI_MODE_CONE, SDT, SL>), grid, block, lds, s, f);
-        break;
-    case kModePointShadow:
-        hipLaunchKernelGGL((render_kernel<VT, LAYOUT, kModePointShadow, SDT, SL>), grid, block, lds, s, f);
-        break;
-    case kModePointShell:
-        hipLaunchKernelGGL((render_kernel<VT, LAYOUT, kModePointShell, SDT, SL>), grid, block, lds, s, f);
-        break;
-    case kModePointPhong:
-        hipLaunchKernelGGL((render_kernel<VT, LAYOUT, kModePointPhong, SDT, SL>), grid, block, lds, s, f);
-        break;
-    case kModeConeGrid:
-        hipLaunchKernelGGL((render_kernel<VT, LAYOUT, kModeConeGrid, SDT, SL>), grid, block, lds, s, f);
-        break;
-    case kModePointCone:
-        hipLaunchKernelGGL((render_kernel<VT, LAYOUT, kModePointCone, SDT, SL>), grid, block, lds, s, f);
-        break;
-    default: hipLaunchKernelGGL((render_kernel<VT, LAYOUT, VI_MODE_PHONG, SDT, SL>), grid, block, lds, s, f); break;
-    }
-    return hipGetLastError();
+    const dim3 grid(supertile_grid((f.width + kBX - 1) / kBX, (f.height + kBY - 1) / kBY)), block(256);
+    return with_mode(kernel_mode(f), [&](auto m) {
+        constexpr int MODE = m();
+        const size_t lds = table_bytes(f) + wave_bytes(MODE, SDT, f.stage != 0);
+        if constexpr (kWindowed<MODE, SDT, SL>)
+            if (f.stage) {
+                hipLaunchKernelGGL((render_kernel<VT, LAYOUT, MODE, SDT, SL, true>), grid, block, lds, s, f);
+                return;
+            }
+        hipLaunchKernelGGL((render_kernel<VT, LAYOUT, MODE, SDT, SL, false>), grid, block, lds, s, f);
+    });
 }
 
 template <typename VT, int LAYOUT>
@@ -1457,12 +1416,12 @@ hipError_t launch_render_part<VI_RENDER_PART>(const RenderFrame& f, hipStream_t 
 }
 
 template <>
-hipError_t launch_render_batch_part<VI_RENDER_PART>(int stack_dtype, int stack_layout, int mode,
+hipError_t launch_render_batch_part<VI_RENDER_PART>(int stack_dtype, int stack_layout, int mode, bool staged,
                                                     const RenderFrame* d_frames, const uint32_t* d_tiles,
-                                                    uint32_t ntiles, int maxK, uint32_t max_occ_words, hipStream_t s)
+                                                    uint32_t ntiles, size_t tables, hipStream_t s)
 {
-    return launch_batch_l<VoxelType<kPartDtype>::T, kPartLayout>(stack_dtype, stack_layout, mode, d_frames, d_tiles,
-                                                                 ntiles, maxK, max_occ_words, s);
+    return launch_batch_l<VoxelType<kPartDtype>::T, kPartLayout>(stack_dtype, stack_layout, mode, staged, d_frames,
+                                                                 d_tiles, ntiles, tables, s);
 }
 
 }  // namespace vi

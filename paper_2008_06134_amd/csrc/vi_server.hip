@@ -143,27 +143,29 @@ public:
         uint32_t* h_tiles = (uint32_t*)((char*)S.h_stage + frames_bytes);
         const RenderFrame* d_frames = (const RenderFrame*)S.d_stage;
         const uint32_t* d_tiles = (const uint32_t*)((const char*)S.d_stage + frames_bytes);
-        int maxK = 2;
-        uint32_t occ_words = 0;  // LDS occupancy bits of the largest frame
+        size_t tables = 0;  // LDS of the largest frame's tables
         for (size_t f = 0; f < frames.size(); ++f) {
             const vi_request& r = *frames[f].req;
             const sched::VolumeRec& v = *frames[f].vol;
             int rc = make_frame(&v.vol, &v.tf, &frames[f].stack->desc, &r.camera, r.mode, r.step_vox, &r.opts,
                                 r.d_rgba, r.d_samples, &h_frames[f]);
             if (rc != VI_OK) return rc;
-            maxK = std::max(maxK, v.tf.n_entries);
-            if (h_frames[f].occ.bits)
-                occ_words = std::max(occ_words, h_frames[f].occ.words + h_frames[f].occ.swords);
+            tables = std::max(tables, table_bytes(h_frames[f]));
         }
-        // tiles grouped by kernel mode (stable), one kernel per mode present
-        constexpr int kModes = kKernelModes;
-        uint32_t count[kModes] = {0}, start[kModes + 1] = {0};
-        for (uint32_t t : tiles) count[kernel_mode(h_frames[t >> 22])]++;
-        for (int m = 0; m < kModes; ++m) start[m + 1] = start[m] + count[m];
+        // tiles grouped by kernel mode and staging (stable), one kernel per
+        // group present
+        constexpr int kGroups = 2 * kKernelModes;
+        const auto group = [&](uint32_t t) {
+            const RenderFrame& f = h_frames[t >> 22];
+            return 2 * kernel_mode(f) + (f.stage ? 1 : 0);
+        };
+        uint32_t count[kGroups] = {0}, start[kGroups + 1] = {0};
+        for (uint32_t t : tiles) count[group(t)]++;
+        for (int g = 0; g < kGroups; ++g) start[g + 1] = start[g] + count[g];
         {
-            uint32_t at[kModes];
-            for (int m = 0; m < kModes; ++m) at[m] = start[m];
-            for (uint32_t t : tiles) h_tiles[at[kernel_mode(h_frames[t >> 22])]++] = t;
+            uint32_t at[kGroups];
+            for (int g = 0; g < kGroups; ++g) at[g] = start[g];
+            for (uint32_t t : tiles) h_tiles[at[group(t)]++] = t;
         }
         hipError_t e = hipMemcpyAsync(S.d_stage, S.h_stage, frames_bytes + tiles.size() * sizeof(uint32_t),
                                       hipMemcpyHostToDevice, rs_);
@@ -172,10 +174,10 @@ public:
             if (e == hipSuccess && f.stack->build_handle >= 0)
                 e = hipStreamWaitEvent(rs_, build_events_[f.stack->build_handle], 0);
         const vi_volume& v0 = frames[0].vol->vol;
-        for (int m = 0; m < kModes && e == hipSuccess; ++m)
-            if (count[m])
+        for (int g = 0; g < kGroups && e == hipSuccess; ++g)
+            if (count[g])
                 e = launch_render_batch(v0.dtype, v0.layout, frames[0].req->slice_dtype, frames[0].req->slice_layout,
-                                        m, d_frames, d_tiles + start[m], count[m], maxK, occ_words, rs_);
+                                        g / 2, g % 2 != 0, d_frames, d_tiles + start[g], count[g], tables, rs_);
         if (e == hipSuccess) e = hipEventRecord(S.done, rs_);
         if (e != hipSuccess) return fail_msg(VI_E_DEVICE, hipGetErrorString(e));
         S.busy = true;
