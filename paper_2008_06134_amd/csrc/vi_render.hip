@@ -136,7 +136,6 @@ template <int SDT> struct Tap<SDT, VI_STACK_TILED> {
 // others spilled 29 registers of the shell)
 enum class Near { kNo, kYes, kWide };
 template <Near V> using NearC = std::integral_constant<Near, V>;
-template <int V> using Count = std::integral_constant<int, V>;
 template <int SL, Near NEAR>
 __device__ __forceinline__ ZPart<SL> z_part(const RenderFrame& F, float z)
 {
@@ -190,7 +189,12 @@ __device__ __forceinline__ float2 tap_layers(const Tap<SDT, VI_STACK_ROWS>& t)
     return make_float2(t0, fmaf(t.wy, cd - ab, ab));
 }
 
-// Tiled layout: eight loads with bounds selects, converted at once.
+// Tiled layout: eight loads with bounds selects, converted at once.  The
+// bounds are combined without short circuits and face 0 is selected behind its
+// loads: with `&&` and a branch around the nearer layer the compiler moved the
+// loads of a row or a layer into the branches of the lanes that need them, up to
+// four waits a tap one after the other (256^3 quads, default options: ring cone
+// at 320 x 240 368 us, 320 now; shell at 1024^2 1100, 965).
 template <int SDT>
 __device__ __forceinline__ void tap_load(const RenderFrame& F, const ZPart<VI_STACK_TILED>& p, float x, float y,
                                          Tap<SDT, VI_STACK_TILED>& t)
@@ -209,15 +213,16 @@ __device__ __forceinline__ void tap_load(const RenderFrame& F, const ZPart<VI_ST
         const uint32_t r0 = base + oj0, r1 = base + oj1;
         float a = stack_texel<SDT>(F.stack, r0 + oi0), b = stack_texel<SDT>(F.stack, r0 + oi1);
         float c = stack_texel<SDT>(F.stack, r1 + oi0), d = stack_texel<SDT>(F.stack, r1 + oi1);
-        a = (vi0 && vj0) ? a : 1.0f;
-        b = (vi1 && vj0) ? b : 1.0f;
-        c = (vi0 && vj1) ? c : 1.0f;
-        d = (vi1 && vj1) ? d : 1.0f;
+        a = (vi0 & vj0) ? a : 1.0f;
+        b = (vi1 & vj0) ? b : 1.0f;
+        c = (vi0 & vj1) ? c : 1.0f;
+        d = (vi1 & vj1) ? d : 1.0f;
         const float ab = fmaf(wx, b - a, a), cd = fmaf(wx, d - c, c);
         return fmaf(wy, cd - ab, ab);
     };
-    t.t0 = p.front ? 1.0f : layer(p.b0);
+    const float t0 = layer(p.b0);
     t.t1 = layer(p.b1);
+    t.t0 = p.front ? 1.0f : t0;
 }
 template <int SDT>
 __device__ __forceinline__ float2 tap_layers(const Tap<SDT, VI_STACK_TILED>& t)
@@ -231,6 +236,7 @@ template <int SDT, int SL, Near NEAR>
 struct FromStack {
     using Z = ZPart<SL>;
     using T = Tap<SDT, SL>;
+    static constexpr bool kTiled = SL == VI_STACK_TILED;
     const RenderFrame& F;
     __device__ __forceinline__ Z z_part(float z) const { return vi::z_part<SL, NEAR>(F, z); }
     __device__ __forceinline__ void load(const Z& p, float x, float y, T& t) const { tap_load<SDT>(F, p, x, y, t); }
@@ -250,6 +256,7 @@ struct FromWindow {
     struct T {
         float a0, a1, a2, a3, b0, b1, b2, b3, wx, wy;
     };
+    static constexpr bool kTiled = false;
     const float* tile;
     int org;  // element of light-grid cell (0, 0, 0)
     __device__ __forceinline__ Z z_part(float z) const
@@ -298,18 +305,22 @@ struct ConeFrame {
 };
 
 // NB stack lookups at once: all their loads are issued before any of them
-// is converted (row layout; the tiled layout looks up one at a time), so a
-// gather waits on one round trip per batch of taps.  Larger batches keep
-// more loads in flight per wave but take registers, i.e. resident waves;
-// measured on the 512^3 workload: the ring cone and the float-stack shell
-// (the latter held to six waves per SIMD) run fastest with two taps per
-// batch, the 5 x 5 lattice with one (four loads); the bfloat16 shell, whose
-// decoding takes more registers, keeps one.
+// is converted, so a gather waits on one round trip per batch of taps.  Larger
+// batches keep more loads in flight per wave but take registers, i.e. resident
+// waves; measured on the 512^3 workload: the ring cone and the float-stack shell
+// (held to six waves per SIMD) run fastest with two taps per batch, the 5 x 5
+// lattice with one (four loads); the bfloat16 shell, whose decoding takes more
+// registers, keeps one.
 template <int MODE, int SDT>
-constexpr int tap_batch()
+constexpr int shell_batch()
 {
-    return (MODE == VI_MODE_CONE || (MODE == VI_MODE_SHELL && SDT == VI_F32)) ? 2 : 1;
+    return MODE == VI_MODE_SHELL && SDT == VI_F32 ? 2 : 1;
 }
+// The six taps of a shell are unrolled over a row stack, so that one shell's
+// offsets stay in scalar registers; over a tiled stack, whose taps are long,
+// that costs registers (115 with the branches that tap_load
+// names, a wave a SIMD or two; 256^3 at 1024^2 998 us unrolled, 965 in a loop).
+template <bool TILED> constexpr int kShellUnroll = TILED ? 1 : 6;
 
 // Nothing is scheduled across the end of a batch: the scheduler would issue
 // the next batches' loads ahead of it and take the registers of one or two
@@ -364,11 +375,10 @@ __device__ __forceinline__ float gather(const RenderFrame& F, const SRC& src, co
         return v[0];
     }
     if (MODE == VI_MODE_SHELL) {
-        // weighted taps (shell r's six taps share w_r / (6 sum w)); the six
-        // are unrolled so that one shell's offsets stay in scalar registers
+        // weighted taps (shell r's six taps share w_r / (6 sum w))
         float zz[NB], xx[NB], yy[NB], v[NB], s = 0.0f;
         for (int t = 0; t < F.ntaps; t += 6) {
-#pragma unroll
+#pragma unroll kShellUnroll<SRC::kTiled>
             for (int q = 0; q < 6; q += NB) {
 #pragma unroll
                 for (int u = 0; u < NB; ++u) {
@@ -531,10 +541,10 @@ __device__ __forceinline__ float gather_point(const RenderFrame& F, float z, flo
     // shell taps: world-frame offsets, each projected through its own depth
     // (batched as in gather())
     float s = 0.0f;
-    constexpr int NB = tap_batch<MODE, SDT>();
+    constexpr int NB = shell_batch<MODE, SDT>();
     float zz[NB], xx[NB], yy[NB], val[NB];
     for (int t = 0; t < F.ntaps; t += 6) {
-#pragma unroll
+#pragma unroll kShellUnroll<SL == VI_STACK_TILED>
         for (int h = 0; h < 6; h += NB) {
 #pragma unroll
             for (int q = 0; q < NB; ++q) {
@@ -952,17 +962,17 @@ __device__ __forceinline__ void ray_shade(const RenderFrame& F, float* __restric
                 else if (F.nearest) A = from(NearC<Near::kYes>());
                 else A = from(NearC<Near::kNo>());
             } else if (MODE != VI_MODE_NONE) {
-                constexpr int NB = tap_batch<MODE, SDT>();
-                const auto from = [&](auto near, auto nb) {
-                    return gather<MODE, nb()>(F, FromStack<SDT, SL, near()>{F}, S.cf, qz, qx, qy);
+                constexpr int NB = shell_batch<MODE, SDT>();
+                const auto from = [&](auto near) {
+                    return gather<MODE, near() == Near::kWide ? 1 : NB>(F, FromStack<SDT, SL, near()>{F}, S.cf, qz, qx, qy);
                 };
                 if constexpr (STAGED) {
                     if (staged) A = gather<MODE, NB>(F, win, S.cf, qz, qx, qy);
-                    else A = from(NearC<Near::kNo>(), Count<1>());
+                    else A = from(NearC<Near::kNo>());
                 } else {
-                    if (SL == VI_STACK_ROWS && F.wide) A = from(NearC<Near::kWide>(), Count<1>());
-                    else if (F.nearest) A = from(NearC<Near::kYes>(), Count<NB>());
-                    else A = from(NearC<Near::kNo>(), Count<NB>());
+                    if (SL == VI_STACK_ROWS && F.wide) A = from(NearC<Near::kWide>());
+                    else if (F.nearest) A = from(NearC<Near::kYes>());
+                    else A = from(NearC<Near::kNo>());
                 }
             }
             sd = fmaf(1.0f - F.ambient, A, F.ambient);
