@@ -879,6 +879,8 @@ int make_frame(const vi_volume* vol, const vi_tf* tf, const vi_slices* sl, const
     }
     F.out = (float4*)d_rgba;
     F.samples = d_samples;
+    const uint32_t more = F.occ.bits ? F.occ.words + F.occ.swords : F.occ.mm ? (uint32_t)F.K : 0u;
+    F.tables = round_up(16u * (uint32_t)F.K + 4u * more, 16u);
     return VI_OK;
 }
 

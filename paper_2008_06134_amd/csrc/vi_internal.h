@@ -102,19 +102,18 @@ struct RenderFrame {
     // elements, and the bases are moved so that the constant is one, too.
     // rl16 = rlayer / 16 and iz multiply in one 24-bit multiply-add, which holds
     // every stack that the build makes (rl16 < 2^23 up to a grid of 11,580^2,
-    // |iz| < 2^23).  `wide`: a caller's own descriptor beyond that (few huge
-    // layers, or millions of tiny ones, below 4 GiB), multiplied in 32 bits
+    // |iz| < 2^23).  A caller's own descriptor beyond that (few huge layers, or
+    // millions of tiny ones, below 4 GiB) is multiplied in 32 bits (wide)
     int32_t rb16, rl16;
-    int wide;
     // clamps of light-grid coordinates that keep footprints on stored texels:
     // z in [-1 - Mz, n - 1 - Mz], x and y in [-2 - Mr, res - Mr]
     float zlo, zhi, xlo, xhi;
-    // rows, directional gathers: whether the stack texels that the taps of a
-    // wave's samples can reach fit a window in LDS (windowed, see kStaged),
-    // whether the frame reads them from there (stage: where window_pays, too),
-    // the taps' reach in texels and in layers below and above the sample, and
-    // the first layer of the window against the sample's
-    int windowed, stage;
+    // rows, directional gathers: whether the frame's waves stage the stack
+    // texels that their samples' taps can reach in LDS (where they fit a window,
+    // see windowed, and window_pays), the taps' reach in texels and in layers
+    // below and above the sample, and the first layer of the window against the
+    // sample's
+    int stage;
     float st_reach, st_zmin, st_zmax;
     int st_oz;
     int stack_dtype;
@@ -167,14 +166,18 @@ struct RenderFrame {
     float4* out;
     unsigned long long* samples;  // [0] segments marched, [1] (count_opaque) segments composited with alpha > 0
     int count_opaque;
+    // bytes of LDS of the tables: K entries of the transfer function, then the
+    // occupancy bits, or the K next-opaque indices of a map without bits, up to 16
+    uint32_t tables;
+    int windowed;  // whether the taps fit a stack window (rows, directional)
+    int wide;      // rows: layer offsets need 32-bit products
 };
 
 // launchers (vi_build.hip / vi_render.hip / vi_layout.hip)
 hipError_t launch_build(const BuildParams& p, hipStream_t s);
 hipError_t launch_render(const RenderFrame& f, hipStream_t s);
 // one launch over `ntiles` tiles whose frames all have kernel_mode() `mode`
-// (maxK / max_occ_words: the largest transfer function and LDS occupancy
-// bits of the frames, which size the launch's LDS)
+// and all stage windows or all do not (tables: LDS of the largest frame's)
 hipError_t launch_render_batch(int vol_dtype, int layout, int stack_dtype, int stack_layout, int mode, bool staged,
                                const RenderFrame* d_frames, const uint32_t* d_tiles, uint32_t ntiles, size_t tables,
                                hipStream_t s);
@@ -210,15 +213,6 @@ inline int kernel_mode(const RenderFrame& f)
     if (f.point && f.mode == VI_MODE_CONE) return kModePointCone;
     if (f.mode == VI_MODE_CONE && f.cone_grid > 0) return kModeConeGrid;
     return f.mode;
-}
-
-// Bytes of LDS of a frame's tables, up to 16: the K entries of the transfer
-// function, then the occupancy bits, or the K next-opaque indices of a map
-// without bits.
-__host__ __device__ inline size_t table_bytes(const RenderFrame& f)
-{
-    const uint32_t more = f.occ.bits ? f.occ.words + f.occ.swords : f.occ.mm ? (uint32_t)f.K : 0u;
-    return (sizeof(float4) * (size_t)f.K + sizeof(uint32_t) * (size_t)more + 15) / 16 * 16;
 }
 
 // The stack window a wave stages in LDS for its gathers: kWinX columns (16

@@ -130,10 +130,16 @@ template <int SDT> struct Tap<SDT, VI_STACK_TILED> {
     float t0, t1;  // the layers' values
 };
 
+// A frame's kernel: kStaged where its waves read the stack through windows in
+// LDS, kWide where a layer's offset does not fit a 24-bit product (see rl16).
+// Kernels of their own: the staging march keeps a wave's lanes together and takes
+// 12 to 20 KB of LDS a workgroup, which frames without it would pay for nothing,
+// and a branch to a 32-bit product cost small frames of every mode 2 to 4 %.
+enum class Form { kPlain, kStaged, kWide };
+
 // nearest-face lookups: never, always (copies of a gather behind one branch
-// that is uniform per frame), or, for wide layers, asked without a branch and
-// with the layer's offset in 32 bits (a copy, too: asking by a branch in the
-// others spilled 29 registers of the shell)
+// that is uniform per frame), or, for wide layers, asked of the frame, with the
+// layer's offset in 32 bits
 enum class Near { kNo, kYes, kWide };
 template <Near V> using NearC = std::integral_constant<Near, V>;
 template <int SL, Near NEAR>
@@ -885,7 +891,7 @@ __device__ __forceinline__ bool stage_window(const RenderFrame& F, float* __rest
 
 // Composite the four segments of a step of every live ray (opacity 1 - om,
 // colour er, eg, eb at distance sm), lit by the coefficient.
-template <typename VT, int LAYOUT, int MODE, int SDT, int SL, bool STAGED>
+template <typename VT, int LAYOUT, int MODE, int SDT, int SL, Form FORM>
 __device__ __forceinline__ void ray_shade(const RenderFrame& F, float* __restrict__ tile, RayState& S, bool live,
                                           bool in, float om, float er, float eg, float eb, float sm, float hx, float hy,
                                           float hz, uint32_t& nop)
@@ -912,7 +918,7 @@ __device__ __forceinline__ void ray_shade(const RenderFrame& F, float* __restric
     [[maybe_unused]] float qz, qx, qy;
     if constexpr (MODE != VI_MODE_NONE && !PHONG) {
         qz = fmaf(sm, S.qdz, S.qz0), qx = fmaf(sm, S.qdx, S.qx0), qy = fmaf(sm, S.qdy, S.qy0);
-        if constexpr (STAGED) staged = stage_window<MODE, SDT>(F, tile, lit, qz, qx, qy, win.org);
+        if constexpr (FORM == Form::kStaged) staged = stage_window<MODE, SDT>(F, tile, lit, qz, qx, qy, win.org);
     }
     if (lit) {
         // emission alpha (sd rgb + ss) light: Eq. 7 with the coefficient A,
@@ -950,30 +956,26 @@ __device__ __forceinline__ void ray_shade(const RenderFrame& F, float* __restric
             sd = fmaf(F.phong_kd, fmaxf(nl, 0.0f), F.phong_ka);
             if (rv > 0.0f) ss = F.phong_ks * fast_exp2(F.phong_shin * fast_log2(rv));
         } else {
-            // (the nearest-face and wide forms are copies of the
-            // gather behind branches that are uniform per frame)
+            // (the nearest-face form is a second copy of the
+            // gather behind a branch that is uniform per frame)
             float A = 1.0f;
-            if (PT) {
+            const auto near_or_not = [&](auto from) {
+                if constexpr (FORM == Form::kWide) return from(NearC<Near::kWide>());
+                else return F.nearest ? from(NearC<Near::kYes>()) : from(NearC<Near::kNo>());
+            };
+            if constexpr (PT) {
                 const float pd = fmaf(sm, S.pdd, S.pd0);
-                const auto from = [&](auto near) {
+                A = near_or_not([&](auto near) {
                     return gather_point<MODE, SDT, SL, near()>(F, qz, pd, qx, qy, -S.pdd, -S.qdx, -S.qdy);
-                };
-                if (SL == VI_STACK_ROWS && F.wide) A = from(NearC<Near::kWide>());
-                else if (F.nearest) A = from(NearC<Near::kYes>());
-                else A = from(NearC<Near::kNo>());
-            } else if (MODE != VI_MODE_NONE) {
+                });
+            } else if constexpr (MODE != VI_MODE_NONE) {
                 constexpr int NB = shell_batch<MODE, SDT>();
                 const auto from = [&](auto near) {
-                    return gather<MODE, near() == Near::kWide ? 1 : NB>(F, FromStack<SDT, SL, near()>{F}, S.cf, qz, qx, qy);
+                    return gather<MODE, NB>(F, FromStack<SDT, SL, near()>{F}, S.cf, qz, qx, qy);
                 };
-                if constexpr (STAGED) {
-                    if (staged) A = gather<MODE, NB>(F, win, S.cf, qz, qx, qy);
-                    else A = from(NearC<Near::kNo>());
-                } else {
-                    if (SL == VI_STACK_ROWS && F.wide) A = from(NearC<Near::kWide>());
-                    else if (F.nearest) A = from(NearC<Near::kYes>());
-                    else A = from(NearC<Near::kNo>());
-                }
+                if constexpr (FORM == Form::kStaged) A = staged ? gather<MODE, NB>(F, win, S.cf, qz, qx, qy)
+                                                                : from(NearC<Near::kNo>());
+                else A = near_or_not(from);
             }
             sd = fmaf(1.0f - F.ambient, A, F.ambient);
         }
@@ -993,7 +995,7 @@ __device__ __forceinline__ void ray_shade(const RenderFrame& F, float* __restric
 // done.  Where the gather stages windows the wave's lanes stay together
 // (finished rays' lanes take part in the staging); elsewhere a quad leaves
 // the loop with its ray.
-template <typename VT, int LAYOUT, int MODE, int SDT, int SL, bool STAGED>
+template <typename VT, int LAYOUT, int MODE, int SDT, int SL, Form FORM>
 __device__ __forceinline__ void ray_step(const RenderFrame& F, const float4* __restrict__ s_tf,
                                          const int* __restrict__ s_next, const uint32_t* __restrict__ s_bits,
                                          float* __restrict__ tile, RayState& S, bool& live, uint32_t& nop)
@@ -1089,8 +1091,8 @@ __device__ __forceinline__ void ray_step(const RenderFrame& F, const float4* __r
         const float jlast = quad_perm<3, 3, 3, 3>(jl);
         knext = fmaxf(knext, 4.0f * floorf(0.25f * (jlast + 1.0f)));
     }
-    if (STAGED ? __any(live && !jump) : !jump)
-        ray_shade<VT, LAYOUT, MODE, SDT, SL, STAGED>(F, tile, S, live, in, om, er, eg, eb, sm, hx, hy, hz, nop);
+    if (FORM == Form::kStaged ? __any(live && !jump) : !jump)
+        ray_shade<VT, LAYOUT, MODE, SDT, SL, FORM>(F, tile, S, live, in, om, er, eg, eb, sm, hx, hy, hz, nop);
     S.k = knext;
     if (S.T <= F.term_eps || S.k >= S.K) live = false;
 }
@@ -1173,7 +1175,7 @@ __device__ __forceinline__ void group_count_add(const RenderFrame& F, GroupCount
     }
 }
 
-// LDS of a workgroup: the frame's tables (see table_bytes), then its four waves'
+// LDS of a workgroup: the frame's tables, then its four waves'
 // areas, each for its stack window, if the frame stages, and, before the march,
 // its rays.
 constexpr size_t wave_words(int kmode, int stack_dtype, bool staged)
@@ -1205,7 +1207,7 @@ __device__ __forceinline__ void stage_words(const void* src, void* dst, uint32_t
 // work four times, a tenth of a frame's VALU instructions, after having waited
 // for the tables.)  The waves take turns at it by workgroup, so that no SIMD
 // gets all of it.
-template <typename VT, int LAYOUT, int MODE, int SDT, int SL, bool STAGED>
+template <typename VT, int LAYOUT, int MODE, int SDT, int SL, Form FORM>
 __device__ __forceinline__ void shade_block(const RenderFrame& F, float4* s_tf, int x0, int y0, uint32_t turn)
 {
     __shared__ GroupCount gc;
@@ -1216,8 +1218,8 @@ __device__ __forceinline__ void shade_block(const RenderFrame& F, float4* s_tf, 
     if (F.occ.bits) stage_words(F.occ.bits, s_bits, F.occ.words + F.occ.swords);
     else if (F.occ.mm) build_next_opaque(s_next, F.tf, F.K);
 
-    constexpr uint32_t kWords = (uint32_t)wave_words(MODE, SDT, STAGED);
-    float* areas = (float*)((char*)s_tf + table_bytes(F));
+    constexpr uint32_t kWords = (uint32_t)wave_words(MODE, SDT, FORM == Form::kStaged);
+    float* areas = (float*)((char*)s_tf + F.tables);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
     RayState S = {};
     if (wave == (turn & 3u)) {
@@ -1251,8 +1253,8 @@ __device__ __forceinline__ void shade_block(const RenderFrame& F, float4* s_tf, 
     const bool hit = S.K > 0.0f;
     bool live = hit;
     uint32_t ns = 0, nop = 0;
-    while (STAGED ? __any(live) : live)
-        ray_step<VT, LAYOUT, MODE, SDT, SL, STAGED>(F, s_tf, s_next, s_bits, tile, S, live, nop);
+    while (FORM == Form::kStaged ? __any(live) : live)
+        ray_step<VT, LAYOUT, MODE, SDT, SL, FORM>(F, s_tf, s_next, s_bits, tile, S, live, nop);
     int px = x0, py = y0;
     ray_pixel((int)(threadIdx.x >> 2), &px, &py);
     if (hit) {
@@ -1270,14 +1272,14 @@ __device__ __forceinline__ void shade_block(const RenderFrame& F, float4* s_tf, 
 // --------------------------------------------------------------------------
 // single-frame kernel
 // --------------------------------------------------------------------------
-template <typename VT, int LAYOUT, int MODE, int SDT, int SL, bool STAGED>
+template <typename VT, int LAYOUT, int MODE, int SDT, int SL, Form FORM>
 __device__ __forceinline__ void render_frame(const RenderFrame& F)
 {
     extern __shared__ float4 s_tf[];
     const uint32_t tiles_x = (F.width + kBX - 1) / kBX, tiles_y = (F.height + kBY - 1) / kBY;
     uint32_t tx, ty;
     if (!supertile_of(blockIdx.x, tiles_x, tiles_y, &tx, &ty)) return;
-    shade_block<VT, LAYOUT, MODE, SDT, SL, STAGED>(F, s_tf, (int)tx * kBX, (int)ty * kBY, blockIdx.x / kXcds);
+    shade_block<VT, LAYOUT, MODE, SDT, SL, FORM>(F, s_tf, (int)tx * kBX, (int)ty * kBY, blockIdx.x / kXcds);
 }
 
 // --------------------------------------------------------------------------
@@ -1290,7 +1292,7 @@ __device__ __forceinline__ void render_frame(const RenderFrame& F)
 // --------------------------------------------------------------------------
 constexpr uint32_t kSubX = 16 / kBX, kSubY = 16 / kBY, kSub = kSubX * kSubY;
 
-template <typename VT, int LAYOUT, int MODE, int SDT, int SL, bool STAGED>
+template <typename VT, int LAYOUT, int MODE, int SDT, int SL, Form FORM>
 __device__ __forceinline__ void render_tiles(const RenderFrame* __restrict__ frames, const uint32_t* __restrict__ tiles,
                                              uint32_t ntiles)
 {
@@ -1299,7 +1301,7 @@ __device__ __forceinline__ void render_tiles(const RenderFrame* __restrict__ fra
     if (!list_of(blockIdx.x, ntiles * kSub, &q)) return;
     const uint32_t t = tiles[q / kSub], sub = q % kSub;
     const RenderFrame& F = frames[t >> 22];
-    shade_block<VT, LAYOUT, MODE, SDT, SL, STAGED>(F, s_tf, (int)((t & 2047u) * kSubX + sub % kSubX) * kBX,
+    shade_block<VT, LAYOUT, MODE, SDT, SL, FORM>(F, s_tf, (int)((t & 2047u) * kSubX + sub % kSubX) * kBX,
                                            (int)(((t >> 11) & 2047u) * kSubY + sub / kSubX) * kBY, blockIdx.x / kXcds);
 }
 
@@ -1314,22 +1316,22 @@ constexpr int kMinWaves = SL != VI_STACK_ROWS ? 1
                           : SDT == VI_F32 && (MODE == VI_MODE_SHELL || MODE == VI_MODE_CONE || MODE == kModeConeGrid)
                               ? 6
                               : 5;
-template <typename VT, int LAYOUT, int MODE, int SDT, int SL, bool STAGED>
+template <typename VT, int LAYOUT, int MODE, int SDT, int SL, Form FORM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMinWaves<MODE, SDT, SL>))) void render_kernel(
     RenderFrame F)
 {
-    render_frame<VT, LAYOUT, MODE, SDT, SL, STAGED>(F);
+    render_frame<VT, LAYOUT, MODE, SDT, SL, FORM>(F);
 }
-template <typename VT, int LAYOUT, int MODE, int SDT, int SL, bool STAGED>
+template <typename VT, int LAYOUT, int MODE, int SDT, int SL, Form FORM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMinWaves<MODE, SDT, SL>))) void
 render_batch_kernel(const RenderFrame* __restrict__ frames, const uint32_t* __restrict__ tiles, uint32_t ntiles)
 {
-    render_tiles<VT, LAYOUT, MODE, SDT, SL, STAGED>(frames, tiles, ntiles);
+    render_tiles<VT, LAYOUT, MODE, SDT, SL, FORM>(frames, tiles, ntiles);
 }
 
-// A frame that stages windows and one that does not are kernels of their own:
-// the staging march keeps a wave's lanes together and takes 12 to 20 KB of LDS
-// a workgroup, which frames without it would pay for nothing.
+template <int MODE, int SL>
+constexpr bool kReadsRows = SL == VI_STACK_ROWS && MODE != VI_MODE_NONE && MODE != VI_MODE_PHONG && MODE != kModePointPhong;
+
 template <typename FN>
 static hipError_t with_mode(int mode, FN fn)
 {
@@ -1358,11 +1360,11 @@ static hipError_t launch_batch_t(int mode, bool staged, const RenderFrame* d_fra
         const size_t lds = tables + wave_bytes(MODE, SDT, staged);
         if constexpr (kWindowed<MODE, SDT, SL>)
             if (staged) {
-                hipLaunchKernelGGL((render_batch_kernel<VT, LAYOUT, MODE, SDT, SL, true>), grid, block, lds, s, d_frames,
+                hipLaunchKernelGGL((render_batch_kernel<VT, LAYOUT, MODE, SDT, SL, Form::kStaged>), grid, block, lds, s, d_frames,
                                    d_tiles, ntiles);
                 return;
             }
-        hipLaunchKernelGGL((render_batch_kernel<VT, LAYOUT, MODE, SDT, SL, false>), grid, block, lds, s, d_frames,
+        hipLaunchKernelGGL((render_batch_kernel<VT, LAYOUT, MODE, SDT, SL, Form::kPlain>), grid, block, lds, s, d_frames,
                            d_tiles, ntiles);
     });
 }
@@ -1386,13 +1388,19 @@ static hipError_t launch_mode(const RenderFrame& f, hipStream_t s)
     const dim3 grid(supertile_grid((f.width + kBX - 1) / kBX, (f.height + kBY - 1) / kBY)), block(256);
     return with_mode(kernel_mode(f), [&](auto m) {
         constexpr int MODE = m();
-        const size_t lds = table_bytes(f) + wave_bytes(MODE, SDT, f.stage != 0);
+        const size_t lds = f.tables + wave_bytes(MODE, SDT, f.stage != 0);
         if constexpr (kWindowed<MODE, SDT, SL>)
             if (f.stage) {
-                hipLaunchKernelGGL((render_kernel<VT, LAYOUT, MODE, SDT, SL, true>), grid, block, lds, s, f);
+                hipLaunchKernelGGL((render_kernel<VT, LAYOUT, MODE, SDT, SL, Form::kStaged>), grid, block, lds, s, f);
                 return;
             }
-        hipLaunchKernelGGL((render_kernel<VT, LAYOUT, MODE, SDT, SL, false>), grid, block, lds, s, f);
+        // (no batch has wide layers: the server builds its stacks itself)
+        if constexpr (kReadsRows<MODE, SL>)
+            if (f.wide) {
+                hipLaunchKernelGGL((render_kernel<VT, LAYOUT, MODE, SDT, SL, Form::kWide>), grid, block, lds, s, f);
+                return;
+            }
+        hipLaunchKernelGGL((render_kernel<VT, LAYOUT, MODE, SDT, SL, Form::kPlain>), grid, block, lds, s, f);
     });
 }
 

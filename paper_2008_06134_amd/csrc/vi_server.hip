@@ -150,7 +150,7 @@ public:
             int rc = make_frame(&v.vol, &v.tf, &frames[f].stack->desc, &r.camera, r.mode, r.step_vox, &r.opts,
                                 r.d_rgba, r.d_samples, &h_frames[f]);
             if (rc != VI_OK) return rc;
-            tables = std::max(tables, table_bytes(h_frames[f]));
+            tables = std::max(tables, (size_t)h_frames[f].tables);
         }
         // tiles grouped by kernel mode and staging (stable), one kernel per
         // group present
