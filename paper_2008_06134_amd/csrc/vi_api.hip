@@ -833,6 +833,8 @@ int make_frame(const vi_volume* vol, const vi_tf* tf, const vi_slices* sl, const
         }
         F.tap_w = 1.0f / F.ntaps;
     }
+    const uint32_t more = F.occ.bits ? F.occ.words + F.occ.swords : F.occ.mm ? (uint32_t)F.K : 0u;
+    F.tables = round_up(16u * (uint32_t)F.K + 4u * more, 16u);
     const int km = kernel_mode(F), wy = win_y(km), wz = reads_stack ? win_z(km, F.stack_dtype) : 0;
     if (!point && F.stack_layout == VI_STACK_ROWS && !F.nearest && !F.wide && wz > 0) {
         // how far the taps reach: texels to any side, layers below and above
@@ -870,7 +872,8 @@ int make_frame(const vi_volume* vol, const vi_tf* tf, const vi_slices* sl, const
         if (F.res + 4 >= kWinX && F.res + 4 >= wy && F.n + 2 >= wz && 2.0 * reach + 2.0 <= wy - 1 &&
             2.0 * reach + 2.0 <= kWinX - 4 && room_z >= 1.0) {
             F.windowed = 1;
-            F.stage = window_pays(covered, apart, F.stack_dtype);
+            const int groups = (int)(kLdsBytes / (F.tables + 4u * window_bytes(km, F.stack_dtype) + kStaticLds));
+            F.stage = window_pays(km, F.ntaps, F.stack_dtype, covered, apart, groups);
             F.st_reach = (float)reach;
             F.st_zmin = (float)zmin;
             F.st_zmax = (float)zmax;
@@ -879,8 +882,6 @@ int make_frame(const vi_volume* vol, const vi_tf* tf, const vi_slices* sl, const
     }
     F.out = (float4*)d_rgba;
     F.samples = d_samples;
-    const uint32_t more = F.occ.bits ? F.occ.words + F.occ.swords : F.occ.mm ? (uint32_t)F.K : 0u;
-    F.tables = round_up(16u * (uint32_t)F.K + 4u * more, 16u);
     return VI_OK;
 }
 

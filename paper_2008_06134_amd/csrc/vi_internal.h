@@ -217,8 +217,8 @@ inline int kernel_mode(const RenderFrame& f)
 
 // The stack window a wave stages in LDS for its gathers: kWinX columns (16
 // texels), win_y rows, win_z layers by kernel mode and stack type; 0 layers:
-// the gather reads the stack.  Staged are the 5 x 5 lattice's 25 taps, which
-// the L1 bounds (medium workload 1690 us a frame from the stack, 1160 from
+// the gather reads the stack.  Staged are the lattices, whose 9 to 49 taps the
+// L1 bounds (medium workload, 5 x 5: 1690 us a frame from the stack, 1160 from
 // windows), and the gathers of the 2-byte stacks, whose texels are then
 // converted once per window instead of once per tap (1024^3 cone frame with
 // a bfloat16 stack 2.5 -> 2.2 ms).  The float shell and ring cone read the
@@ -226,10 +226,9 @@ inline int kernel_mode(const RenderFrame& f)
 // where some do not fit (43 and 78 % of the steps of the large workload) the
 // wave runs both paths (window against stack: shell 1072 us against 951, cone
 // 1266 against 1210).  The sizes hold the taps of the 16 x 4 samples of a
-// step on images of about a pixel per voxel, and five workgroups' windows and
-// tables fit in a CU's LDS.  One window a step: a second for the samples that
-// the first does not hold costs more than it saves (medium lattice 1083 ->
-// 1111 us, precision frame 2933 -> 3005).
+// step on images of about a pixel per voxel.  One window a step: a second for
+// the samples that the first does not hold costs more than it saves (medium
+// lattice 1083 -> 1111 us, precision frame 2933 -> 3005).
 constexpr int kWinX = 16;
 constexpr int win_y(int kmode) { return kmode == VI_MODE_SHELL ? 8 : 16; }
 constexpr int win_z(int kmode, int stack_dtype)
@@ -238,25 +237,37 @@ constexpr int win_z(int kmode, int stack_dtype)
     if (stack_dtype == VI_F32) return 0;
     return kmode == VI_MODE_SHELL ? 6 : kmode == VI_MODE_CONE ? 5 : 0;
 }
-// Whether a frame is better gathered from windows, of which a face of the cube
-// covers `covered` pixels, the rays of neighbouring pixels `apart` texels apart.
-// Up to about 30 K pixels every wave with work is resident, the time is one
-// wave's chain of steps, and a window's load and wait only lengthen it; with
-// several rounds of waves the L1 counts.  And the further the rays are apart
-// the fewer of a step's samples one window holds, and the rest run the other
-// path as well; the 2-byte stacks, for which a window also saves the
-// conversions, bear more of that.  Measured (stack | window, us): 5 x 5 lattice
-// of 100^3, 31 K pixels 208 | 308, 70 K 416 | 322; of 256^3, 31 K pixels 429 |
-// 551, 70 K (1.1 texels apart) 560 | 592, 124 K (0.8) 741 | 629, 500 K (0.4)
-// 1771 | 1220; 3 x 3 lattice of 512^3, 380 K pixels, 1.0 apart 910 | 997,
-// 770 K, 0.7 apart 1511 | 1456; bfloat16 shell of 256^3, 31 K 204 | 235, 70 K
-// 246 | 270, 124 K 299 | 287; of 500^3, 124 K, 1.7 apart 686 | 625; half ring
-// cone of 512^3, 91 K, 2.0 apart 671 | 626.
-inline bool window_pays(double covered, double apart, int stack_dtype)
+// Whether a frame is better gathered from windows.  `covered`: pixels that a face
+// of the cube covers, `apart`: texels between neighbouring pixels' rays, `taps`
+// a sample, `groups`: workgroups whose tables and windows fit a CU's LDS.  What a
+// window costs (its loads and one more wait a step) is the same for any number
+// of taps, what it saves grows with them; few pixels are one round of waves,
+// whose time is a wave's chain of waits; the further the rays are apart the fewer
+// of a step's samples one window holds; and where large tables leave room for
+// few workgroups the waves go that hide the wait.  The lines lie where 4,200
+// frames with the window on and off cross over (time without / with it,
+// geometric means; profiles/stack_windows.md):
+//   taps: lattices of 1 and 4 taps 0.77 and 0.89, of 9 1.07, of 25 1.33; 2-byte
+//     rings of at most 4 taps 0.87, of 8 1.04;
+//   covered, from / below: lattices of 9 taps and more 1.26 / 1.00 at 50 K (0.91
+//     below 40 K), 2-byte rings of 8 and more 1.06 / 0.97 at 80 K, shells 1.08 / 0.97;
+//   apart, up to / beyond: float lattices 1.30 / 1.00 at 0.9, 2-byte lattices 1.33 /
+//     1.14 there; 2-byte rings 1.06 / 1.01 at 0.9, shells 1.08 / 0.97 at 1.2;
+//   groups (1024 table entries leave four or five): 3 x 3 lattices 1.10 with five and
+//     more, 1.01 with four; rings of 8 1.06 and 0.99; shells further apart than 0.4
+//     1.05 with six and more, 1.00 with five.
+inline bool window_pays(int kmode, int taps, int stack_dtype, double covered, double apart, int groups)
 {
-    if (covered < 9.4e4) return covered >= 6.3e4 && apart <= 0.5;
-    return apart <= (stack_dtype == VI_F32 ? 0.9 : 2.0);
+    if (kmode == kModeConeGrid)
+        return taps >= (groups >= 5 ? 9 : 16) && covered >= 5e4 && apart <= (stack_dtype == VI_F32 ? 0.9 : 3.0);
+    if (kmode == VI_MODE_CONE)
+        return taps >= (groups >= 5 ? 8 : 16) && covered >= 8e4 && apart <= (groups >= 5 ? 0.9 : 0.4);
+    return covered >= 8e4 && apart <= (groups >= 6 ? 1.2 : 0.4);  // shells, six taps and more
 }
+// LDS of a wave's stack window, of a workgroup's counters and opacity masks, and
+// of a CU
+constexpr uint32_t window_bytes(int kmode, int stack_dtype) { return 4u * kWinX * win_y(kmode) * win_z(kmode, stack_dtype); }
+constexpr uint32_t kStaticLds = 160u, kLdsBytes = 160u * 1024u;
 
 // host helpers shared by the API and the server
 int make_frame(const vi_volume* vol, const vi_tf* tf, const vi_slices* sl, const vi_camera* cam, int mode,

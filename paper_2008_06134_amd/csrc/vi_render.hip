@@ -1180,7 +1180,7 @@ __device__ __forceinline__ void group_count_add(const RenderFrame& F, GroupCount
 // its rays.
 constexpr size_t wave_words(int kmode, int stack_dtype, bool staged)
 {
-    const size_t w = staged ? kWinX * win_y(kmode) * win_z(kmode, stack_dtype) : 0;
+    const size_t w = staged ? window_bytes(kmode, stack_dtype) / 4 : 0;
     return w > 16 * kRayFields ? w : 16 * kRayFields;
 }
 constexpr size_t wave_bytes(int kmode, int stack_dtype, bool staged)
