@@ -11,9 +11,9 @@
 // written once.
 //
 // Mapping: one workgroup per run of consecutive elements of a layer, one
-// column per lane (in the tiled layout optionally C columns).  In the row
-// layout a run is a stretch of the layer's element range, border included
-// (build_rows); in the tiled layout a run of one stack row (build_tiled).
+// column per lane.  In the row layout a run is a stretch of the layer's element
+// range, border included (build_rows); in the tiled layout a run of one stack
+// row (build_tiled).
 // At every slab a workgroup stores its run as one contiguous stretch of the
 // layer (up to 4 KiB); many short runs spread over the layer
 // (64 x 4 texel tiles per workgroup) measured at half that write rate.  The
@@ -69,25 +69,6 @@ __device__ __forceinline__ float q_frac(int64_t H)
 }
 __device__ __forceinline__ float q_to_float(int64_t H) { return (float)H * (1.0f / 1099511627776.0f); }
 
-// Tiled layout, (C, B): columns per lane, slabs per batch; a lane's C columns are NT apart (CONSEC = 0: each store instruction of a
-// wave covers 64 neighbouring texels) or adjacent (CONSEC = 1: one
-// C-element store per lane)
-#ifndef VI_BUILD_C
-#define VI_BUILD_C 1
-#endif
-#ifndef VI_BUILD_BATCH
-#define VI_BUILD_BATCH 2
-#endif
-#ifndef VI_BUILD_CONSEC
-#define VI_BUILD_CONSEC 0
-#endif
-constexpr int kBuildC = VI_BUILD_C, kBuildB = VI_BUILD_BATCH;
-constexpr bool kBuildConsec = VI_BUILD_CONSEC != 0;
-
-// The slabs of a column whose midpoints lie in the cube: k in [k_in, k_out]
-// (empty when k_in > k_out), exactly as the per-slab test lo <= h_k <= hi
-// on all three axes decides it: per axis a half-line or interval of k from
-// an exact integer division of Q40 values.
 // floor(a / b) for b > 0, as far as it lies in [-1, n] (otherwise some value
 // beyond that end): an estimate in float, within 2^-21 (n + 1) of the quotient
 // clamped to [-1, n], corrected by the exact remainder.  (A 64-bit division is
@@ -101,6 +82,10 @@ __device__ __forceinline__ int floor_div(int64_t a, int64_t b, int n)
     else if (r >= b) ++k;
     return k;
 }
+// The slabs of a column whose midpoints lie in the cube: k in [k_in, k_out]
+// (empty when k_in > k_out), exactly as the per-slab test lo <= h_k <= hi
+// on all three axes decides it: per axis a half-line or interval of k from
+// exact quotients of Q40 values.
 __device__ __forceinline__ void slab_range(const int64_t H[3], const int64_t A[3], int n, int64_t lo, int64_t hi,
                                            int* k_in, int* k_out)
 {
@@ -136,17 +121,16 @@ __device__ __forceinline__ int wave_max(int v)
     return v;
 }
 
-// One stack texel: transmittance (F32), optical depth in base-2 units
-// -log2 T (BF16), or the transmittance 2^-tau of the float optical depth
-// rounded to half precision (F16).
+// One texel of a tiled stack: transmittance (F32) or optical depth in base-2
+// units, -log2 T (BF16).
 // (The stack is below 4 GiB: byte offsets in 32 bits, so a store takes the
 // stack's base from scalar registers.)
 template <int OUT_DTYPE>
 __device__ __forceinline__ void put_texel(void* out, uint32_t at, float T, float tau)
 {
+    static_assert(OUT_DTYPE == VI_F32 || OUT_DTYPE == VI_BF16, "half stacks have the row layout");
     if (OUT_DTYPE == VI_F32) *(float*)((char*)out + (at << 2)) = T;
-    else if (OUT_DTYPE == VI_BF16) *(uint16_t*)((char*)out + (at << 1)) = f32_to_bf16(tau);
-    else *(__half*)((char*)out + (at << 1)) = __float2half_rn(fast_exp2(-tau));
+    else *(uint16_t*)((char*)out + (at << 1)) = f32_to_bf16(tau);
 }
 
 // An empty statement that reads a fetched footprint's registers.  Placed
@@ -282,18 +266,16 @@ __device__ __forceinline__ void slab_step(const BuildParams& P, const float* s_a
     }
 }
 
-// Tiled layout: one workgroup per run of NT * C texels of one stack row,
-// lane l owning columns l, l + NT, ..., l + NT (C - 1) of the run (or C
-// adjacent ones).  Slabs in front of a wave's columns' union of cube
-// intervals and behind it are stored without touching the volume; inside,
-// batches of B slabs: positions and empty-space verdicts, then every volume
-// load of the batch, and only then the arithmetic and the stores -- one
-// wait per batch, with C * B footprints in flight.
+// Tiled layout: one workgroup per run of NT texels of one stack row, a column a
+// lane.  Slabs in front of a wave's columns' union of cube intervals and behind it
+// are stored without touching the volume; inside, batches of kTiledSlabs slabs:
+// positions and empty-space verdicts, then every volume load of the batch, and
+// only then the arithmetic and the stores -- one wait per batch.
+constexpr int kTiledSlabs = 2;
 template <typename VT, int LAYOUT, int OUT_DTYPE, bool PT, int NT>
 __device__ __forceinline__ void build_tiled(const BuildParams& P)
 {
-    constexpr int C = kBuildC, B = kBuildB;
-    constexpr int CS = kBuildConsec ? 1 : NT;  // stride between a lane's columns
+    constexpr int B = kTiledSlabs;
     extern __shared__ float s_alpha[];  // K alphas, then the occupancy bits
     uint32_t* s_bits = (uint32_t*)(s_alpha + P.K);
     stage_build_tables(P, s_alpha, s_bits);
@@ -302,89 +284,61 @@ __device__ __forceinline__ void build_tiled(const BuildParams& P)
     const uint32_t cnc = use_bits ? P.occ.nc : 1u;
     __syncthreads();
 
-    const uint32_t runs = ((uint32_t)P.res + NT * C - 1) / (NT * C);
+    const uint32_t runs = ((uint32_t)P.res + NT - 1) / NT;
     uint32_t row, run;
     if (!row_run_of(blockIdx.x, (uint32_t)P.res, runs, &row, &run)) return;
-    const int i0 = (int)(run * NT * C) + (kBuildConsec ? C * (int)threadIdx.x : (int)threadIdx.x);
-    const int j = (int)row;
+    const int i = (int)(run * NT + threadIdx.x), j = (int)row;
+    const bool col = i < P.res;
 
-    int64_t H[C][3], A[C][3];
-    float ex[C];
-    int kin[C], kout[C];
-    bool col[C];
-    uint32_t at[C];
-    int kmin = P.n, kmax = -1;
-#pragma unroll
-    for (int c = 0; c < C; ++c) {
-        const int i = i0 + CS * c;
-        col[c] = i < P.res;
-        column_setup<PT>(P, i, j, col[c], H[c], A[c], &ex[c], &kin[c], &kout[c]);
-        at[c] = stack_oj(j, P.row_tiles32) + stack_oi(i);
-        kmin = min(kmin, kin[c]);
-        kmax = max(kmax, kout[c]);
-    }
+    int64_t H[3], A[3];
+    float ex;
+    int kin, kout;
+    column_setup<PT>(P, i, j, col, H, A, &ex, &kin, &kout);
+    uint32_t at = stack_oj(j, P.row_tiles32) + stack_oi(i);
     // the wave's slabs with any midpoint in the cube: [kmin, kmax]
-    kmin = __builtin_amdgcn_readfirstlane(wave_min(kmin));
-    kmax = __builtin_amdgcn_readfirstlane(wave_max(kmax));
+    const int kmin = __builtin_amdgcn_readfirstlane(wave_min(kin));
+    const int kmax = __builtin_amdgcn_readfirstlane(wave_max(kout));
     const uint32_t layer = P.layer;
 
     // slabs in front of the cube: the light arrives unattenuated
-    for (int k = 0; k < min(kmin, P.n); ++k)
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-            if (col[c]) put_texel<OUT_DTYPE>(P.out, at[c], 1.0f, 0.0f);
-            at[c] += layer;
-        }
+    for (int k = 0; k < min(kmin, P.n); ++k) {
+        if (col) put_texel<OUT_DTYPE>(P.out, at, 1.0f, 0.0f);
+        at += layer;
+    }
 
     const VT* __restrict__ vol = (const VT*)P.vol;
     const VolIndex VI_ = {1u, P.vsy, P.vsz};
-    float T[C], tau[C];
+    float T = 1.0f, tau = 0.0f;
     const int kstart = kmin < P.n ? kmin : 0;
-#pragma unroll
-    for (int c = 0; c < C; ++c) {
-        T[c] = 1.0f, tau[c] = 0.0f;
-        for (int a = 0; a < 3; ++a) H[c][a] += (int64_t)kstart * A[c][a];  // positions at slab kmin
-    }
+    for (int a = 0; a < 3; ++a) H[a] += (int64_t)kstart * A[a];  // positions at slab kmin
     const bool darken = P.darken > 0.0f;
 
     for (int k0 = kmin; k0 <= kmax; k0 += B) {
-        SlabProbe sp[C][B];
-        RawFoot<VT, LAYOUT> raw[C][B];
+        SlabProbe sp[B];
+        RawFoot<VT, LAYOUT> raw[B];
 #pragma unroll
-        for (int c = 0; c < C; ++c) {
+        for (int u = 0; u < B; ++u)
+            sp[u] = probe_slab(P, H[0] + (int64_t)u * A[0], H[1] + (int64_t)u * A[1], H[2] + (int64_t)u * A[2], k0 + u,
+                               kin, kout, s_bits, cshift, cnc);
+        for (int a = 0; a < 3; ++a) H[a] += (int64_t)B * A[a];
 #pragma unroll
-            for (int u = 0; u < B; ++u)
-                sp[c][u] = probe_slab(P, H[c][0] + (int64_t)u * A[c][0], H[c][1] + (int64_t)u * A[c][1],
-                                      H[c][2] + (int64_t)u * A[c][2], k0 + u, kin[c], kout[c], s_bits, cshift, cnc);
-            for (int a = 0; a < 3; ++a) H[c][a] += (int64_t)B * A[c][a];
-        }
-#pragma unroll
-        for (int c = 0; c < C; ++c)
-#pragma unroll
-            for (int u = 0; u < B; ++u)
-                if (sp[c][u].fetch)
-                    foot_load_g<VT, LAYOUT>(raw[c][u], sp[c][u].wx, sp[c][u].wy, vol, VI_, P.N, sp[c][u].gx,
-                                            sp[c][u].gy, sp[c][u].gz);
+        for (int u = 0; u < B; ++u)
+            if (sp[u].fetch)
+                foot_load_g<VT, LAYOUT>(raw[u], sp[u].wx, sp[u].wy, vol, VI_, P.N, sp[u].gx, sp[u].gy, sp[u].gz);
 #pragma unroll
         for (int u = 0; u < B; ++u) {
             if (k0 + u > kmax) break;
-#pragma unroll
-            for (int c = 0; c < C; ++c) {
-                if (sp[c][u].fetch) slab_step<VT, LAYOUT, OUT_DTYPE>(P, s_alpha, raw[c][u], sp[c][u], ex[c], darken,
-                                                                     T[c], tau[c]);
-                if (col[c]) put_texel<OUT_DTYPE>(P.out, at[c], T[c], tau[c]);
-                at[c] += layer;
-            }
+            if (sp[u].fetch) slab_step<VT, LAYOUT, OUT_DTYPE>(P, s_alpha, raw[u], sp[u], ex, darken, T, tau);
+            if (col) put_texel<OUT_DTYPE>(P.out, at, T, tau);
+            at += layer;
         }
     }
 
     // slabs behind the cube: the transmittance stays as it left the cube
-    for (int k = max(kmax + 1, kmin < P.n ? kmin : P.n); k < P.n; ++k)
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-            if (col[c]) put_texel<OUT_DTYPE>(P.out, at[c], T[c], tau[c]);
-            at[c] += layer;
-        }
+    for (int k = max(kmax + 1, kmin < P.n ? kmin : P.n); k < P.n; ++k) {
+        if (col) put_texel<OUT_DTYPE>(P.out, at, T, tau);
+        at += layer;
+    }
 }
 
 // Row layout.  A layer, border and padding included, is one run of LS
@@ -589,9 +543,8 @@ static hipError_t launch_rows(const BuildParams& p, hipStream_t s)
 template <typename VT, int LAYOUT, int OUT_DTYPE, bool PT, int NT>
 static hipError_t launch_tiled(const BuildParams& p, hipStream_t s)
 {
-    constexpr uint32_t per_group = (uint32_t)NT * kBuildC;
     const size_t lds = build_table_bytes(p.K, std::max(p.occ.words + p.occ.swords, 1u));
-    const uint32_t runs = ((uint32_t)p.res + per_group - 1) / per_group;
+    const uint32_t runs = ((uint32_t)p.res + NT - 1) / NT;
     hipLaunchKernelGGL((build_tiled_kernel<VT, LAYOUT, OUT_DTYPE, PT, NT>), dim3(row_run_grid((uint32_t)p.res, runs)),
                        dim3(NT), lds, s, p);
     return hipGetLastError();

@@ -89,7 +89,6 @@ __device__ __forceinline__ F2 f2_dot3(const F2* a, const F2* b)
     return f2_add(f2_add(f2_mul(a[0], b[0]), f2_mul(a[1], b[1])), f2_mul(a[2], b[2]));
 }
 
-// One voxel, normalised and clamped to [0,1] before interpolation.
 // Element idx of an array below 4 GiB, addressed with a 32-bit byte offset
 // (the load then takes the base from scalar registers: no 64-bit address
 // arithmetic per load).  Stacks and one copy of a volume's voxels are
@@ -99,30 +98,6 @@ template <typename T>
 __device__ __forceinline__ T ld32(const void* __restrict__ base, uint32_t idx)
 {
     return *(const T*)((const char*)base + idx * (uint32_t)sizeof(T));
-}
-
-template <typename VT>
-__device__ __forceinline__ float voxel_norm(const VT* __restrict__ v, uint32_t idx, float scale);
-
-template <>
-__device__ __forceinline__ float voxel_norm<uint8_t>(const uint8_t* __restrict__ v, uint32_t idx, float scale)
-{
-    return clampf01((float)ld32<uint8_t>(v, idx) * scale);
-}
-template <>
-__device__ __forceinline__ float voxel_norm<uint16_t>(const uint16_t* __restrict__ v, uint32_t idx, float scale)
-{
-    return clampf01((float)ld32<uint16_t>(v, idx) * scale);
-}
-template <>
-__device__ __forceinline__ float voxel_norm<__half>(const __half* __restrict__ v, uint32_t idx, float scale)
-{
-    return clampf01(__half2float(ld32<__half>(v, idx)) * scale);
-}
-template <>
-__device__ __forceinline__ float voxel_norm<float>(const float* __restrict__ v, uint32_t idx, float scale)
-{
-    return clampf01(ld32<float>(v, idx) * scale);
 }
 
 // Element offsets of the two volume layouts, separable per axis so the
@@ -182,6 +157,7 @@ template <typename VT> struct RawFoot<VT, VI_LAYOUT_LINEAR> {
 };
 template <typename VT> struct RawFoot<VT, VI_LAYOUT_QUAD4> { typename QuadRaw<VT>::T a, b; };
 
+// One voxel, normalised and clamped to [0,1] before interpolation.
 __device__ __forceinline__ float norm1(uint8_t x, float scale) { return clampf01((float)x * scale); }
 __device__ __forceinline__ float norm1(uint16_t x, float scale) { return clampf01((float)x * scale); }
 __device__ __forceinline__ float norm1(__half x, float scale) { return clampf01(__half2float(x) * scale); }

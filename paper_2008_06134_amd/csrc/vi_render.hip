@@ -30,7 +30,8 @@ namespace vi {
 // in base-2 units, tau2 = -log2 T (Eq. 6's exponent summed over the slabs in
 // front, over ln 2), so that each texel converts to T = 2^-tau2 with one
 // exponential before the interpolation; a half-precision stack holds T
-// (from the float optical depth), converted with no exponential.
+// (from the float optical depth), converted with no exponential, and has the row
+// layout only.
 template <int SDT>
 __device__ __forceinline__ float stack_texel(const void* __restrict__ S, uint32_t idx);
 
@@ -44,12 +45,6 @@ __device__ __forceinline__ float stack_texel<VI_BF16>(const void* __restrict__ S
 {
     return fast_exp2(-bf16_to_f32(((const uint16_t*)S)[idx]));
 }
-template <>
-__device__ __forceinline__ float stack_texel<VI_F16>(const void* __restrict__ S, uint32_t idx)
-{
-    return __half2float(((const __half*)S)[idx]);
-}
-
 // Row layout: the two texels (i, i+1) of one bilinear row, element e and
 // e+1, with one load: 8 bytes (4-byte aligned) for float, 4 bytes (2-byte
 // aligned, which global loads allow) for bfloat16.
@@ -1307,10 +1302,13 @@ __device__ __forceinline__ void render_tiles(const RenderFrame* __restrict__ fra
 
 // The kernels, one per mode.  Over a float row stack the shell, the ring cone
 // and the lattice are held to six waves per SIMD (80 VGPRs, no spills): the
-// lattice 1155 -> 1094 us, the cone 1208 -> 1195; over the other row stacks
-// and modes to five (point cone 737 -> 722 us; six spill, 785).  The tiled
-// layout's lookups keep the compiler's four (1010 us for the default-argument
-// frame; five 1031, six 1083).
+// lattice 1155 -> 1094 us, the cone 1208 -> 1195.  Five holds the point cones (105
+// to 96 VGPRs: 256^3 float 771 -> 728 us, half 835 -> 800; six spill, 863 and 900)
+// and the staged half ring cone (100 to 91: 768 -> 686); the unlit, shadow, Phong,
+// point shell and 2-byte shell kernels take 55 to 79 registers whatever is asked
+// for and run in the same time.  The tiled layout's lookups keep the compiler's
+// four (with the branches that tap_load names five and six were slower; without
+// them five lets the bfloat16 decoding spill its time, ring cone 1310 -> 1565 us).
 template <int MODE, int SDT, int SL>
 constexpr int kMinWaves = SL != VI_STACK_ROWS ? 1
                           : SDT == VI_F32 && (MODE == VI_MODE_SHELL || MODE == VI_MODE_CONE || MODE == kModeConeGrid)
