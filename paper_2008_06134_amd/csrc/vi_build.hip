@@ -268,14 +268,12 @@ __device__ __forceinline__ void slab_step(const BuildParams& P, const float* s_a
 
 // Tiled layout: one workgroup per run of NT texels of one stack row, a column a
 // lane.  Slabs in front of a wave's columns' union of cube intervals and behind it
-// are stored without touching the volume; inside, batches of kTiledSlabs slabs:
-// positions and empty-space verdicts, then every volume load of the batch, and
-// only then the arithmetic and the stores -- one wait per batch.
-constexpr int kTiledSlabs = 2;
-template <typename VT, int LAYOUT, int OUT_DTYPE, bool PT, int NT>
+// are stored without touching the volume; inside, batches of B slabs: positions
+// and empty-space verdicts, then every volume load of the batch, and only then
+// the arithmetic and the stores -- one wait per batch.
+template <typename VT, int LAYOUT, int OUT_DTYPE, bool PT, int NT, int B>
 __device__ __forceinline__ void build_tiled(const BuildParams& P)
 {
-    constexpr int B = kTiledSlabs;
     extern __shared__ float s_alpha[];  // K alphas, then the occupancy bits
     uint32_t* s_bits = (uint32_t*)(s_alpha + P.K);
     stage_build_tables(P, s_alpha, s_bits);
@@ -522,10 +520,10 @@ __global__ __launch_bounds__(NW * 64) void build_rows_kernel(BuildParams P)
 {
     build_rows<VT, LAYOUT, OUT_DTYPE, PT, NW, D>(P);
 }
-template <typename VT, int LAYOUT, int OUT_DTYPE, bool PT, int NT>
+template <typename VT, int LAYOUT, int OUT_DTYPE, bool PT, int NT, int B>
 __global__ __launch_bounds__(NT) void build_tiled_kernel(BuildParams P)
 {
-    build_tiled<VT, LAYOUT, OUT_DTYPE, PT, NT>(P);
+    build_tiled<VT, LAYOUT, OUT_DTYPE, PT, NT, B>(P);
 }
 
 template <typename VT, int LAYOUT, int OUT_DTYPE, bool PT, int NW, int D>
@@ -540,12 +538,12 @@ static hipError_t launch_rows(const BuildParams& p, hipStream_t s)
     return hipGetLastError();
 }
 
-template <typename VT, int LAYOUT, int OUT_DTYPE, bool PT, int NT>
+template <typename VT, int LAYOUT, int OUT_DTYPE, bool PT, int NT, int B>
 static hipError_t launch_tiled(const BuildParams& p, hipStream_t s)
 {
     const size_t lds = build_table_bytes(p.K, std::max(p.occ.words + p.occ.swords, 1u));
     const uint32_t runs = ((uint32_t)p.res + NT - 1) / NT;
-    hipLaunchKernelGGL((build_tiled_kernel<VT, LAYOUT, OUT_DTYPE, PT, NT>), dim3(row_run_grid((uint32_t)p.res, runs)),
+    hipLaunchKernelGGL((build_tiled_kernel<VT, LAYOUT, OUT_DTYPE, PT, NT, B>), dim3(row_run_grid((uint32_t)p.res, runs)),
                        dim3(NT), lds, s, p);
     return hipGetLastError();
 }
@@ -588,9 +586,16 @@ static hipError_t launch_build_k(const BuildParams& p, hipStream_t s)
         // row of 256 leave three in four idle; but beyond 256 a row in one
         // workgroup is the faster (u16 quads, 1024 | 256 lanes: 366^2 110.7 |
         // 114.8 us, 480^2 224 | 234; linear 340^2 207 | 221) unless stretches
-        // of 256 fill it (512^2 363 | 347).
-        if (p.res > 512 || (p.res > 256 && p.res % 256 != 0)) return launch_tiled<VT, LAYOUT, OUT_DTYPE, PT, 1024>(p, s);
-        return launch_tiled<VT, LAYOUT, OUT_DTYPE, PT, 256>(p, s);
+        // of 256 fill it (512^2 363 | 347).  Large linear volumes, whose columns
+        // wait for lines of their own, take four slabs in flight (without a map, before
+        // their rows came as pairs | two slabs | four: 512^3 u8 and 1024^2 bfloat16 2577 |
+        // 2765 | 1836, float 3053 | 3090 | 2505; 450^3 and 900^2 1395 | 1427 | 1256; 384^3
+        // and 768^2 980 | 838 | 931).
+        if constexpr (LAYOUT == VI_LAYOUT_LINEAR)
+            if (p.res > 800) return launch_tiled<VT, LAYOUT, OUT_DTYPE, PT, 1024, 4>(p, s);
+        if (p.res > 512 || (p.res > 256 && p.res % 256 != 0))
+            return launch_tiled<VT, LAYOUT, OUT_DTYPE, PT, 1024, 2>(p, s);
+        return launch_tiled<VT, LAYOUT, OUT_DTYPE, PT, 256, 2>(p, s);
     }
     return hipErrorInvalidValue;
 }
