@@ -564,17 +564,23 @@ static hipError_t launch_build_k(const BuildParams& p, hipStream_t s)
         // and 768^2 344 | 346 | 450, 512^3 and 1024^2 681 | 788 | 892.
         // Footprints of eight loads (or of two of 16 bytes) keep two slabs in
         // flight: 256^3 bricks 210 with 16 waves, 147 with 8; 512^3 754 and
-        // 884.  Linear volumes, whose gathers touch the most lines, change
-        // over a little earlier, to four slabs in flight of 2-byte voxels:
-        // without a map, 320^3 and 640^2 529 with 8 waves, 707 with 16 and
-        // four slabs; 384^3 and 768^2 1197 and 1027; 512^3 2792 and 1876
-        // (2164 with two; float voxels 916 with two, 1089 with four).
+        // 884.
         constexpr bool kLinear = LAYOUT == VI_LAYOUT_LINEAR, kLight = LAYOUT == VI_LAYOUT_QUAD4 && sizeof(VT) <= 2;
-        // Quads without bits, where every slab of every column is fetched, change
-        // over earlier too (16 waves | 8: 380^3 u8 and 600^2 354 | 317, 445^3
-        // half and 520^2 339 | 260, 697^2 321 | 363).
-        if (p.rlayer > (kLinear ? 500000u : kLight && !p.occ.bits ? 430000u : 600000u))
-            return launch_rows<VT, LAYOUT, OUT_DTYPE, PT, 16, kLinear && sizeof(VT) <= 2 ? 4 : 2>(p, s);
+        // Quads and linear volumes without bits, where every slab of every column
+        // is fetched, change over earlier (16 waves | 8: 380^3 u8 quads and 600^2 354 |
+        // 317, 445^3 half and 520^2 339 | 260, 697^2 321 | 363; linear u16 320^3 and 640^2
+        // 707 | 526, 337^3 and 665^2 606 | 706, 360^3 and 720^2 828 | 1038; with bits 337^3
+        // 304 | 263, 360^3 399 | 377).
+        if (p.rlayer > ((kLinear || kLight) && !p.occ.bits ? 430000u : 600000u)) {
+            // The largest linear volumes of 2-byte voxels and less take four slabs
+            // in flight (two | four: u16 337^3 and 665^2 606 | 632, 384^3 and 768^2 1061 |
+            // 1023, 420^3 and 840^2 1257 | 1149, 512^3 and 1024^2 2163 | 1875), except
+            // under a point light, whose columns spread (512^3 1984 | 1988, 420^3 1153 |
+            // 1199).
+            if constexpr (kLinear && sizeof(VT) <= 2 && !PT)
+                if (p.rlayer > 560000u) return launch_rows<VT, LAYOUT, OUT_DTYPE, PT, 16, 4>(p, s);
+            return launch_rows<VT, LAYOUT, OUT_DTYPE, PT, 16, 2>(p, s);
+        }
         if constexpr (kLight) {
             if (p.rlayer <= 160000u) return launch_rows<VT, LAYOUT, OUT_DTYPE, PT, 4, 4>(p, s);
             return launch_rows<VT, LAYOUT, OUT_DTYPE, PT, 8, 4>(p, s);

@@ -89,6 +89,10 @@ struct RenderFrame {
     // transfer function
     const float* tf;
     int K;
+    // bytes of LDS of the tables: K entries of the transfer function, then the
+    // occupancy bits, or the K next-opaque indices of a map without bits, up to 16
+    // (beside K: a launch's first waves wait for every line of the frame they read)
+    uint32_t tables;
     // stack
     const void* stack;
     const void* stack_base;  // the buffer itself (rows: layer -1, row -2, column -2)
@@ -166,9 +170,6 @@ struct RenderFrame {
     float4* out;
     unsigned long long* samples;  // [0] segments marched, [1] (count_opaque) segments composited with alpha > 0
     int count_opaque;
-    // bytes of LDS of the tables: K entries of the transfer function, then the
-    // occupancy bits, or the K next-opaque indices of a map without bits, up to 16
-    uint32_t tables;
     int windowed;  // whether the taps fit a stack window (rows, directional)
     int wide;      // rows: layer offsets need 32-bit products
 };
