@@ -566,12 +566,14 @@ static hipError_t launch_build_k(const BuildParams& p, hipStream_t s)
         // flight: 256^3 bricks 210 with 16 waves, 147 with 8; 512^3 754 and
         // 884.
         constexpr bool kLinear = LAYOUT == VI_LAYOUT_LINEAR, kLight = LAYOUT == VI_LAYOUT_QUAD4 && sizeof(VT) <= 2;
-        // Quads and linear volumes without bits, where every slab of every column
-        // is fetched, change over earlier (16 waves | 8: 380^3 u8 quads and 600^2 354 |
-        // 317, 445^3 half and 520^2 339 | 260, 697^2 321 | 363; linear u16 320^3 and 640^2
-        // 707 | 526, 337^3 and 665^2 606 | 706, 360^3 and 720^2 828 | 1038; with bits 337^3
-        // 304 | 263, 360^3 399 | 377).
-        if (p.rlayer > ((kLinear || kLight) && !p.occ.bits ? 430000u : 600000u)) {
+        // Without bits, where every slab of every column is fetched, the change comes
+        // earlier (16 waves | 8: 380^3 u8 quads and 600^2 354 | 317, 445^3 half and
+        // 520^2 339 | 260, 697^2 321 | 363; float quads 337^3 and 665^2 394 | 405, 384^3
+        // and 768^2 574 | 716; linear u16 320^3 and 640^2 707 | 526, 337^3 and 665^2 606 |
+        // 706; bricks 350^3 and 690^2 481 | 402, 360^3 and 720^2 587 | 592, 384^3 and
+        // 768^2 636 | 662; with bits linear 337^3 304 | 263, 360^3 399 | 377, u16 quads
+        // 384^3 344 | 346).
+        if (p.rlayer > (p.occ.bits ? 600000u : LAYOUT == VI_LAYOUT_BRICK4 ? 510000u : 430000u)) {
             // The largest linear volumes of 2-byte voxels and less take four slabs
             // in flight (two | four: u16 337^3 and 665^2 606 | 632, 384^3 and 768^2 1061 |
             // 1023, 420^3 and 840^2 1257 | 1149, 512^3 and 1024^2 2163 | 1875), except
