@@ -247,7 +247,7 @@ constexpr int win_z(int kmode, int stack_dtype)
 // of a step's samples one window holds; and where large tables leave room for
 // few workgroups the waves go that hide the wait.  The lines lie where 4,200
 // frames with the window on and off cross over (time without / with it,
-// geometric means; profiles/stack_windows.md):
+// geometric means):
 //   taps: lattices of 1 and 4 taps 0.77 and 0.89, of 9 1.07, of 25 1.33; 2-byte
 //     rings of at most 4 taps 0.87, of 8 1.04;
 //   covered, from / below: lattices of 9 taps and more 1.26 / 1.00 at 50 K (0.91
