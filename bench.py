@@ -48,9 +48,9 @@ MEASURED = {
     # 1024^2 f32 stack in rows, 1920x1080), mean of the three launches of bench --steps 2 --warmup 1
     # (lights 0, 0, 1); per launch: FETCH_SIZE / WRITE_SIZE in KiB, SQ_INSTS_VALU, GRBM_GUI_ACTIVE
     # (summed over the 8 XCDs), TA_TA_BUSY_sum and the other SQ counters of the same passes
-    ("build", "large", "rows", 16, "quads"): {"sha256": "c90012ce9c0a42bbef6b310640e5beed774215c778539e9229d6a5e5cb1c18b7", "fetch_kib": 301321.1, "write_kib": 2124109.0, "valu_insts": 157766497, "gui_cycles": 12304360, "ta_busy": 258308316, "vmem_rd": 1231265, "vmem_wr": 2122306, "waves": 16896, "wave_cycles": 2734467174, "busy_cycles": 47506051, "wait_inst_any": 534655918, "lds_insts": 10196915, "salu_insts": 49459832, "tcp_accesses": 68912724, "tcc_read_req": 14857722, "tcc_hit": 26876124, "tcc_miss": 21946933},
-    ("render_shell", "large", "rows", 16, "quads"): {"sha256": "81c6f9bfbfd9ee8285716be32c696cb1e4ab6bdebaabee33621758ff2d61308e", "fetch_kib": 110965.9, "write_kib": 33445.5, "valu_insts": 373559767, "gui_cycles": 17223566, "ta_busy": 355972193, "vmem_rd": 18043157, "vmem_wr": 148647, "waves": 130560, "wave_cycles": 2026064347, "busy_cycles": 59821143, "wait_inst_any": 528694096, "lds_insts": 7220882, "salu_insts": 88481821, "tcp_accesses": 445936634, "tcc_read_req": 24281610, "tcc_hit": 22795959, "tcc_miss": 2053813},
-    ("render_cone", "large", "rows", 16, "quads"): {"sha256": "81c6f9bfbfd9ee8285716be32c696cb1e4ab6bdebaabee33621758ff2d61308e", "fetch_kib": 129953.5, "write_kib": 33789.7, "valu_insts": 408098723, "gui_cycles": 20712290, "ta_busy": 442681538, "vmem_rd": 23052805, "vmem_wr": 148647, "waves": 130560, "wave_cycles": 2355032209, "busy_cycles": 71020793, "wait_inst_any": 795112506, "lds_insts": 7400251, "salu_insts": 92683815, "tcp_accesses": 576002956, "tcc_read_req": 46664639, "tcc_hit": 44869310, "tcc_miss": 2365761},
+    ("build", "large", "rows", 16, "quads"): {"sha256": "8b378cbc2ffe6a2fb8bc79690a927de18f11d65d84274f33214b0c6d1d2234e1", "fetch_kib": 302712.6, "write_kib": 2124135.4, "valu_insts": 157766497, "gui_cycles": 12145297, "ta_busy": 261712930, "vmem_rd": 1231265, "vmem_wr": 2122306, "waves": 16896, "wave_cycles": 2749863616, "busy_cycles": 47775111, "wait_inst_any": 537086419, "lds_insts": 10196915, "salu_insts": 49459832, "tcp_accesses": 68912724, "tcc_read_req": 14857097, "tcc_hit": 26857418, "tcc_miss": 21965021},
+    ("render_shell", "large", "rows", 16, "quads"): {"sha256": "70f1f8ebebb897b29800a358146328fab95452250e55d6e7c7b4d0f16a9f1abc", "fetch_kib": 110837.5, "write_kib": 33449.4, "valu_insts": 373559767, "gui_cycles": 17308791, "ta_busy": 356375888, "vmem_rd": 18043157, "vmem_wr": 148647, "waves": 130560, "wave_cycles": 2033727055, "busy_cycles": 59955991, "wait_inst_any": 527132162, "lds_insts": 7220882, "salu_insts": 87776537, "tcp_accesses": 445936634, "tcc_read_req": 24392201, "tcc_hit": 22903260, "tcc_miss": 2057386},
+    ("render_cone", "large", "rows", 16, "quads"): {"sha256": "70f1f8ebebb897b29800a358146328fab95452250e55d6e7c7b4d0f16a9f1abc", "fetch_kib": 130210.5, "write_kib": 33795.4, "valu_insts": 408098723, "gui_cycles": 20740538, "ta_busy": 442793176, "vmem_rd": 23052805, "vmem_wr": 148647, "waves": 130560, "wave_cycles": 2359265945, "busy_cycles": 70692836, "wait_inst_any": 805374456, "lds_insts": 7400251, "salu_insts": 91978531, "tcp_accesses": 576002956, "tcc_read_req": 46662057, "tcc_hit": 44859964, "tcc_miss": 2369513},
 }
 
 
